@@ -45,7 +45,7 @@ template <typename R>
 __global__ void k_fft_pass(const FftGridPass*, int64_t, const int64_t*, const typename Cplx<R>::T*,
                            typename Cplx<R>::T*, const int64_t*);
 hipError_t launch_qr(int H, double* rec, int stride, int64_t np, const int64_t* list, const unsigned* list_count,
-                     SolveCounters* counters, unsigned* queue, int waves, hipStream_t st);
+                     SolveCounters* counters, unsigned* queue, int waves, bool many, hipStream_t st);
 hipError_t launch_assemble(int precision, const SolveArgs& a, double* rec, int64_t p0, int64_t np, int waves,
                            hipStream_t st);
 hipError_t launch_score(const SolveArgs& a, const double* rec, int64_t p0, int64_t np, int waves,
@@ -729,6 +729,11 @@ int64_t grid_waves(const ftp_plan* P, int wpc, int64_t np) {
   return std::max<int64_t>(1, std::min<int64_t>(w, np));
 }
 
+// Companion solve of np pairs: several matrices per wavefront once one per
+// wavefront would put more than one or two on a SIMD (results do not depend
+// on it).
+bool qr_many(const ftp_plan* P, int64_t np) { return np > (int64_t)6 * P->n_cu; }
+
 // Per-frequency stage over pair chunks: assemble -> roots -> score.  Roots:
 // companion QR (plain); network features -> MLP -> Newton + Sturm -> Aberth
 // on the unconfirmed pairs -> companion QR on what Aberth leaves (learned,
@@ -829,8 +834,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
     hipEvent_t r0 = root_ev();
     if (r0) HIP_TRY(hipEventRecord(r0, st));
     if (solver == FTP_SOLVER_PLAIN) {
-      HIP_TRY(launch_qr(P->H, rec, RL.stride, np, nullptr, nullptr, B.counters, ctr + 4, w_qr,
-                        st));
+      HIP_TRY(launch_qr(P->H, rec, RL.stride, np, nullptr, nullptr, B.counters, ctr + 4, w_qr, qr_many(P, np), st));
     } else {
       // the network's seeds: for every pair's first round (FTP_FLAG_SEEDS_ALL),
       // else for the pairs the first round leaves (list and its device count)
@@ -954,13 +958,14 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
       hipEvent_t rc2 = learn_ev();
       if (rc2) HIP_TRY(hipEventRecord(rc2, st));
       // what the Aberth tier leaves is usually nothing or a few frequencies:
-      // a launch of one wave per CU serves it through the queue.  Above
-      // D = 64 (or with the forced fallback) the Sturm count is refused on
-      // most frequencies and the list holds most of them: the plain solve's
-      // launch shape
-      const bool big_list = 6 * P->H - 2 > 64 || (P->opt.flags & FTP_FLAG_FORCE_FALLBACK);
+      // a launch of one wave per CU serves it through the queue, one matrix
+      // per wave.  Above D = 64 the list holds what the second Newton round
+      // left: the plain solve's grid.  With the forced fallback it holds every
+      // frequency: the plain solve's launch
+      const bool forced = (P->opt.flags & FTP_FLAG_FORCE_FALLBACK) != 0;
+      const bool big_list = 6 * P->H - 2 > 64 || forced;
       HIP_TRY(launch_qr(P->H, rec, RL.stride, np, B.fb2_list, ctr + 1, B.counters, ctr + 4,
-                        big_list ? w_qr : std::min(w_qr, (int)grid_waves(P, 1, np)), st));
+                        big_list ? w_qr : std::min(w_qr, (int)grid_waves(P, 1, np)), forced && qr_many(P, np), st));
     }
     hipEvent_t r1 = root_ev();
     if (r1) HIP_TRY(hipEventRecord(r1, st));
@@ -1622,7 +1627,7 @@ int ftp_root_counts(ftp_plan* P, const double* sums, const double* lc_stats, dou
     aa.clear8 = ctr;
     HIP_TRY(launch_assemble(P->opt.precision, aa, rec, p0, np, (int)grid_waves(P, P->tune.assemble_wpc, np), st));
     HIP_TRY(launch_qr(P->H, rec, RL.stride, np, nullptr, nullptr, P->counters.as<SolveCounters>(), ctr + 4,
-                      (int)grid_waves(P, P->tune.qr_wpc, np), st));
+                      (int)grid_waves(P, P->tune.qr_wpc, np), qr_many(P, np), st));
     HIP_TRY(launch_root_counts(rec, P->H, np, sturm_count + p0, companion_real + p0,
                                (int)grid_waves(P, P->tune.newton_wpc, np), st));
   }

@@ -12,10 +12,7 @@
 //                Cayley polynomial f(x) = (1 + x^2)^K R(phi0 + 2 atan x), a real
 //                polynomial of degree D = 6H - 2 whose real roots are the real
 //                phases (leading coefficient R(phi0 + pi));
-//   k_qr<D>    : eigenvalues of the real companion matrix of f by Francis
-//                double-shift QR in LDS; every eigenvalue is mapped back to
-//                psi and projected onto the unit circle (a complex pair gives
-//                one candidate);
+//   k_qr       : eigenvalues of the real companion matrix of f (ftp_qr.hip);
 //   k_score    : P = YM^2 / (YY MM) at every candidate, best by P with the
 //                documented tie rule, Newton polish on R(theta) kept only if P
 //                does not drop, outputs theta_2, theta_1, theta_3.
@@ -42,18 +39,6 @@ __device__ __forceinline__ double rdlane(double v, int src) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// 1/sqrt(s) from the hardware estimate refined by two Newton steps (a few
-// ulp; the Householder step is backward stable to that level).
-__device__ __forceinline__ double fast_rsq(double s) {
-  double y = __builtin_amdgcn_rsq(s);
-  const double h = 0.5 * s;
-  y = y * fma(-h * y, y, 1.5);
-  y = y * fma(-h * y, y, 1.5);
-  return y;
-}
-
-// ------------------------------------------------------------------ QR
-
 // f_c = sum_j rc[j] T[j][c] over the Cayley table's rows j = 0..K (column
 // `col`, row stride D + 1): the table loads of eight rows are issued before
 // their multiply-adds, so their latency is paid once per eight rows; the
@@ -77,481 +62,6 @@ __device__ __forceinline__ double cayley_dot(const double* rc, const double* col
   }
   if (jx <= K) acc0 = fma(rc[jx], col[jx * (D + 1)], acc0);
   return acc0 + acc1;
-}
-
-// Eigenvalues of the N x N upper Hessenberg matrix A (LDS, leading dim N + 1,
-// N <= 64), EISPACK hqr structure, eigenvalues only: Francis double-shift
-// sweeps over the active window [l, m], deflating at negligible subdiagonals.
-// Lane j owns column j in the row update of a chase step and row j in the
-// column update; the next bulge column is broadcast from the updating lanes'
-// registers.  Returns the number of sweeps, or -1 when the iteration limit is
-// reached (the remaining diagonal entries are then used as estimates).
-// Storage of the N x N upper Hessenberg matrix the QR iteration works on.
-// Dense: row-major with leading dimension N + 1.  Packed: column j holds rows
-// 0 .. min(j + 3, N - 1) (the Hessenberg band and the chase's bulge, which
-// never leaves it) at cs(j) + i: (N - 3)(N - 4)/2 + 4 (N - 3) + 3 N doubles,
-// 15 KB instead of 27 KB at N = 58, so twice as many matrices fit the LDS
-// of a compute unit (the iteration is latency-bound: occupancy is its
-// throughput).
-template <int N>
-struct DenseHess {
-  double* A;
-  __device__ __forceinline__ double& operator()(int i, int j) const { return A[i * (N + 1) + j]; }
-};
-template <int N>
-struct PackedHess {
-  double* P;
-  __host__ __device__ static constexpr int cs(int j) {
-    return ((j < N - 3 ? j : N - 3) * ((j < N - 3 ? j : N - 3) - 1)) / 2 + 4 * (j < N - 3 ? j : N - 3) +
-           (j - (j < N - 3 ? j : N - 3)) * N;
-  }
-  __device__ __forceinline__ double& operator()(int i, int j) const { return P[cs(j) + i]; }
-};
-
-template <int N, typename Acc>
-__device__ __forceinline__ int hqr_wave(const Acc& X, double* wr, double* wi, const int lane) {
-  double anorm = 0.0;
-  if (lane < N) {
-    for (int j = (lane > 0 ? lane - 1 : 0); j < N; ++j) anorm += fabs(X(lane, j));
-  }
-  anorm = wave_sum(anorm);
-  if (anorm == 0.0) anorm = 1.0;
-  int m = N - 1, its = 0, sweeps = 0;
-  constexpr int maxit = 30 * N;
-  bool failed = false;
-  while (m >= 0) {
-    bool ok = false;
-    if (lane >= 1 && lane <= m) {
-      double sd = fabs(X(lane - 1, lane - 1)) + fabs(X(lane, lane));
-      if (sd == 0.0) sd = anorm;
-      ok = fabs(X(lane, lane - 1)) <= kEps * sd;
-    }
-    const unsigned long long mask = __ballot(ok);
-    const int l = mask ? 63 - __clzll(mask) : 0;
-    if (l == m) {
-      if (lane == 0) { wr[m] = X(m, m); wi[m] = 0.0; }
-      m -= 1;
-      its = 0;
-      continue;
-    }
-    if (l == m - 1) {
-      const double a = X(m - 1, m - 1), b = X(m - 1, m);
-      const double c = X(m, m - 1), d = X(m, m);
-      const double p = 0.5 * (a - d);
-      const double q = p * p + b * c;
-      if (lane == 0) {
-        if (q >= 0.0) {
-          double z = sqrt(q);
-          z = p + copysign(z, p);
-          const double e1 = d + z;
-          const double e2 = z != 0.0 ? d - b * c / z : e1;
-          wr[m - 1] = e1; wr[m] = e2; wi[m - 1] = 0.0; wi[m] = 0.0;
-        } else {
-          const double z = sqrt(-q);
-          wr[m - 1] = d + p; wr[m] = d + p; wi[m - 1] = z; wi[m] = -z;
-        }
-      }
-      m -= 2;
-      its = 0;
-      continue;
-    }
-    if (sweeps >= maxit) { failed = true; break; }
-    double S, T;
-    const double amm = X(m, m), am1 = X(m - 1, m - 1);
-    if (its == 10 || its == 20) {
-      const double sx = fabs(X(m, m - 1)) + fabs(X(m - 1, m - 2));
-      const double c = amm + 0.75 * sx;
-      S = 2.0 * c;
-      T = c * c - 0.4375 * sx * sx;
-    } else {
-      S = am1 + amm;
-      T = am1 * amm - X(m - 1, m) * X(m, m - 1);
-    }
-    ++its;
-    ++sweeps;
-    const double all = X(l, l), al1 = X(l + 1, l);
-    double x = all * all + X(l, l + 1) * al1 - S * all + T;
-    double y = al1 * (all + X(l + 1, l + 1) - S);
-    double z = (l + 2 <= m) ? X(l + 2, l + 1) * al1 : 0.0;
-    for (int k = l; k <= m - 1; ++k) {
-      const bool three = k < m - 1;
-      const double s2 = x * x + y * y + z * z;
-      double a0n = 0.0;
-      if (s2 > 0.0) {
-        const double inv = fast_rsq(s2);
-        const double nrm = s2 * inv;
-        const double alpha = -copysign(nrm, x);
-        const double ax = fabs(x);
-        const double tau = 1.0 + ax * inv;                         // (alpha - x) / alpha
-        const double rv = copysign(fast_rcp_d(ax + nrm), x);        // 1 / (x - alpha)
-        const double v1 = y * rv, v2 = z * rv;
-        // row update: rows k..k+2, columns k..m (lane = column); the bulge
-        // column k-1 becomes (alpha, 0, 0)
-        if (lane >= k && lane <= m) {
-          const double b0 = X(k, lane), b1 = X(k + 1, lane);
-          const double b2 = three ? X(k + 2, lane) : 0.0;
-          const double w = tau * (b0 + v1 * b1 + v2 * b2);
-          X(k, lane) = b0 - w;
-          X(k + 1, lane) = b1 - w * v1;
-          if (three) X(k + 2, lane) = b2 - w * v2;
-        } else if (k > l && lane == k - 1) {
-          X(k, lane) = alpha;
-          X(k + 1, lane) = 0.0;
-          if (three) X(k + 2, lane) = 0.0;
-        }
-        wave_sync();
-        // column update: columns k..k+2, rows l..min(k+3, m) (lane = row)
-        const int ihi = k + 3 < m ? k + 3 : m;
-        if (lane >= l && lane <= ihi) {
-          const double c0 = X(lane, k), c1 = X(lane, k + 1);
-          const double c2 = three ? X(lane, k + 2) : 0.0;
-          const double w = tau * (c0 + v1 * c1 + v2 * c2);
-          a0n = c0 - w;
-          X(lane, k) = a0n;
-          X(lane, k + 1) = c1 - w * v1;
-          if (three) X(lane, k + 2) = c2 - w * v2;
-        }
-        wave_sync();
-        if (k + 1 <= m - 1) {
-          x = rdlane(a0n, k + 1);
-          y = rdlane(a0n, k + 2);
-          z = (k + 1 < m - 1) ? rdlane(a0n, k + 3) : 0.0;
-        }
-      } else if (k + 1 <= m - 1) {
-        x = X(k + 1, k);
-        y = X(k + 2, k);
-        z = (k + 1 < m - 1) ? X(k + 3, k) : 0.0;
-      }
-    }
-  }
-  wave_sync();
-  if (failed) {
-    if (lane <= m) { wr[lane] = X(lane, lane); wi[lane] = 0.0; }
-    wave_sync();
-    return -1;
-  }
-  return sweeps;
-}
-
-// Balancing (Parlett & Reinsch, Numer. Math. 13 (1969); LAPACK gebal): a
-// diagonal similarity by powers of 2, exact in floating point, that brings the
-// off-diagonal 1-norms of each row and column within a factor of 2.  The
-// companion matrix of the Cayley polynomial has entries spread over many
-// orders of magnitude (binomial growth with D), and without this step the QR
-// iteration loses the roots' accuracy relative to the matrix norm.
-template <int N, typename Acc>
-__device__ __forceinline__ void balance_wave(const Acc& X, const int lane) {
-  for (int sweep = 0; sweep < 16; ++sweep) {
-    bool done = true;
-    for (int i = 0; i < N; ++i) {
-      // off-diagonal entries of column i and row i inside the band that can
-      // be nonzero (rows up to the column + 3)
-      const bool off = lane < N && lane != i;
-      double c = wave_sum(off && lane <= i + 3 ? fabs(X(lane, i)) : 0.0);
-      const double r = wave_sum(off && i <= lane + 3 ? fabs(X(i, lane)) : 0.0);
-      if (!(c > 0.0) || !(r > 0.0) || !isfinite(c) || !isfinite(r)) continue;   // (also ends the loops below)
-      const double s = c + r;
-      double f = 1.0, g = 0.5 * r;
-      while (c < g) { f *= 2.0; c *= 4.0; }
-      g = 2.0 * r;
-      while (c >= g) { f *= 0.5; c *= 0.25; }
-      if ((c + r) / f < 0.95 * s) {
-        done = false;
-        const double fi = 1.0 / f;
-        if (lane < N) {
-          if (i <= lane + 3) X(i, lane) *= fi;
-          if (lane <= i + 3) X(lane, i) *= f;
-        }
-        wave_sync();
-      }
-    }
-    if (done) break;
-  }
-}
-
-// The same two steps for 64 < N <= 128 (degree D = 6H - 2 up to 88): lane j
-// owns rows (columns) j and j + 64, and the bulge column is broadcast from
-// whichever of the two registers holds the row.
-__device__ __forceinline__ double rdlane2(double v0, double v1, int r) {
-  return r < 64 ? rdlane(v0, r) : rdlane(v1, r - 64);
-}
-
-template <int N>
-__device__ __forceinline__ int hqr_wave2(double* A, double* wr, double* wi, const int lane) {
-  static_assert(N > 64 && N <= 128, "two rows per lane");
-  constexpr int ld = N + 1;
-  const int j1 = lane + 64;
-  const bool has1 = j1 < N;
-  double anorm = 0.0;
-  for (int j = (lane > 0 ? lane - 1 : 0); j < N; ++j) anorm += fabs(A[lane * ld + j]);
-  if (has1) {
-    for (int j = j1 - 1; j < N; ++j) anorm += fabs(A[j1 * ld + j]);
-  }
-  anorm = wave_sum(anorm);
-  if (anorm == 0.0) anorm = 1.0;
-  int m = N - 1, its = 0, sweeps = 0;
-  constexpr int maxit = 30 * N;
-  bool failed = false;
-  while (m >= 0) {
-    bool ok0 = false, ok1 = false;
-    if (lane >= 1 && lane <= m) {
-      double sd = fabs(A[(lane - 1) * ld + lane - 1]) + fabs(A[lane * ld + lane]);
-      if (sd == 0.0) sd = anorm;
-      ok0 = fabs(A[lane * ld + lane - 1]) <= kEps * sd;
-    }
-    if (has1 && j1 <= m) {
-      double sd = fabs(A[(j1 - 1) * ld + j1 - 1]) + fabs(A[j1 * ld + j1]);
-      if (sd == 0.0) sd = anorm;
-      ok1 = fabs(A[j1 * ld + j1 - 1]) <= kEps * sd;
-    }
-    const unsigned long long mk0 = __ballot(ok0), mk1 = __ballot(ok1);
-    const int l = mk1 ? 127 - __clzll(mk1) : (mk0 ? 63 - __clzll(mk0) : 0);
-    if (l == m) {
-      if (lane == 0) { wr[m] = A[m * ld + m]; wi[m] = 0.0; }
-      m -= 1;
-      its = 0;
-      continue;
-    }
-    if (l == m - 1) {
-      const double a = A[(m - 1) * ld + m - 1], b = A[(m - 1) * ld + m];
-      const double c = A[m * ld + m - 1], d = A[m * ld + m];
-      const double p = 0.5 * (a - d);
-      const double q = p * p + b * c;
-      if (lane == 0) {
-        if (q >= 0.0) {
-          double z = sqrt(q);
-          z = p + copysign(z, p);
-          const double e1 = d + z;
-          const double e2 = z != 0.0 ? d - b * c / z : e1;
-          wr[m - 1] = e1; wr[m] = e2; wi[m - 1] = 0.0; wi[m] = 0.0;
-        } else {
-          const double z = sqrt(-q);
-          wr[m - 1] = d + p; wr[m] = d + p; wi[m - 1] = z; wi[m] = -z;
-        }
-      }
-      m -= 2;
-      its = 0;
-      continue;
-    }
-    if (sweeps >= maxit) { failed = true; break; }
-    double S, T;
-    const double amm = A[m * ld + m], am1 = A[(m - 1) * ld + m - 1];
-    if (its == 10 || its == 20) {
-      const double sx = fabs(A[m * ld + m - 1]) + fabs(A[(m - 1) * ld + m - 2]);
-      const double c = amm + 0.75 * sx;
-      S = 2.0 * c;
-      T = c * c - 0.4375 * sx * sx;
-    } else {
-      S = am1 + amm;
-      T = am1 * amm - A[(m - 1) * ld + m] * A[m * ld + m - 1];
-    }
-    ++its;
-    ++sweeps;
-    const double all = A[l * ld + l], al1 = A[(l + 1) * ld + l];
-    double x = all * all + A[l * ld + l + 1] * al1 - S * all + T;
-    double y = al1 * (all + A[(l + 1) * ld + l + 1] - S);
-    double z = (l + 2 <= m) ? A[(l + 2) * ld + l + 1] * al1 : 0.0;
-    for (int k = l; k <= m - 1; ++k) {
-      const bool three = k < m - 1;
-      const double s2 = x * x + y * y + z * z;
-      double a0n[2] = {0.0, 0.0};
-      if (s2 > 0.0) {
-        const double inv = fast_rsq(s2);
-        const double nrm = s2 * inv;
-        const double alpha = -copysign(nrm, x);
-        const double ax = fabs(x);
-        const double tau = 1.0 + ax * inv;
-        const double rv = copysign(fast_rcp_d(ax + nrm), x);
-        const double v1 = y * rv, v2 = z * rv;
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-          const int j = lane + 64 * sl;
-          if (j >= k && j <= m) {
-            const double b0 = A[k * ld + j], b1 = A[(k + 1) * ld + j];
-            const double b2 = three ? A[(k + 2) * ld + j] : 0.0;
-            const double w = tau * (b0 + v1 * b1 + v2 * b2);
-            A[k * ld + j] = b0 - w;
-            A[(k + 1) * ld + j] = b1 - w * v1;
-            if (three) A[(k + 2) * ld + j] = b2 - w * v2;
-          } else if (k > l && j == k - 1) {
-            A[k * ld + j] = alpha;
-            A[(k + 1) * ld + j] = 0.0;
-            if (three) A[(k + 2) * ld + j] = 0.0;
-          }
-        }
-        wave_sync();
-        const int ihi = k + 3 < m ? k + 3 : m;
-#pragma unroll
-        for (int sl = 0; sl < 2; ++sl) {
-          const int i = lane + 64 * sl;
-          if (i >= l && i <= ihi) {
-            const double c0 = A[i * ld + k], c1 = A[i * ld + k + 1];
-            const double c2 = three ? A[i * ld + k + 2] : 0.0;
-            const double w = tau * (c0 + v1 * c1 + v2 * c2);
-            a0n[sl] = c0 - w;
-            A[i * ld + k] = a0n[sl];
-            A[i * ld + k + 1] = c1 - w * v1;
-            if (three) A[i * ld + k + 2] = c2 - w * v2;
-          }
-        }
-        wave_sync();
-        if (k + 1 <= m - 1) {
-          x = rdlane2(a0n[0], a0n[1], k + 1);
-          y = rdlane2(a0n[0], a0n[1], k + 2);
-          z = (k + 1 < m - 1) ? rdlane2(a0n[0], a0n[1], k + 3) : 0.0;
-        }
-      } else if (k + 1 <= m - 1) {
-        x = A[(k + 1) * ld + k];
-        y = A[(k + 2) * ld + k];
-        z = (k + 1 < m - 1) ? A[(k + 3) * ld + k] : 0.0;
-      }
-    }
-  }
-  wave_sync();
-  if (failed) {
-    for (int i = lane; i <= m; i += 64) { wr[i] = A[i * ld + i]; wi[i] = 0.0; }
-    wave_sync();
-    return -1;
-  }
-  return sweeps;
-}
-
-template <int N>
-__device__ __forceinline__ void balance_wave2(double* A, const int lane) {
-  static_assert(N > 64 && N <= 128, "two rows per lane");
-  constexpr int ld = N + 1;
-  const int j1 = lane + 64;
-  const bool has1 = j1 < N;
-  for (int sweep = 0; sweep < 16; ++sweep) {
-    bool done = true;
-    for (int i = 0; i < N; ++i) {
-      double cs = lane != i ? fabs(A[lane * ld + i]) : 0.0;
-      double rs = lane != i ? fabs(A[i * ld + lane]) : 0.0;
-      if (has1 && j1 != i) {
-        cs += fabs(A[j1 * ld + i]);
-        rs += fabs(A[i * ld + j1]);
-      }
-      double c = wave_sum(cs);
-      const double r = wave_sum(rs);
-      if (!(c > 0.0) || !(r > 0.0) || !isfinite(c) || !isfinite(r)) continue;
-      const double s = c + r;
-      double f = 1.0, g = 0.5 * r;
-      while (c < g) { f *= 2.0; c *= 4.0; }
-      g = 2.0 * r;
-      while (c >= g) { f *= 0.5; c *= 0.25; }
-      if ((c + r) / f < 0.95 * s) {
-        done = false;
-        const double fi = 1.0 / f;
-        A[i * ld + lane] *= fi;
-        A[lane * ld + i] *= f;
-        if (has1) {
-          A[i * ld + j1] *= fi;
-          A[j1 * ld + i] *= f;
-        }
-        wave_sync();
-      }
-    }
-    if (done) break;
-  }
-}
-
-// Packed storage where the dense matrix would hold a compute unit's LDS to
-// fewer than ~10 matrices (N >= 46); below, the dense layout's simpler
-// addressing is faster (measured: N = 34 dense 11.5 ms, packed 12.0 ms per
-// 5e4 matrices; N = 58 dense 412 ms, packed 292 ms per 3e5).
-__host__ __device__ inline constexpr bool qr_packed(int N) { return N >= 46 && N <= 64; }
-
-// doubles of the matrix storage of k_qr<N>, even so that the eigenvalue
-// arrays after it stay aligned
-__host__ __device__ inline size_t qr_mat_doubles(int N) {
-  const int j1 = N > 3 ? N - 3 : 0;   // PackedHess<N>::cs(N)
-  const size_t m = qr_packed(N) ? (size_t)((j1 * (j1 - 1)) / 2 + 4 * j1 + (N - j1) * N) : (size_t)N * (N + 1);
-  return (m + 1) & ~(size_t)1;
-}
-__host__ __device__ inline size_t qr_lds_bytes(int D) {
-  return (qr_mat_doubles(D) + 2 * (size_t)D + 2) * sizeof(double);
-}
-
-// Companion eigenvalues for the pairs of a chunk (or of a list of them).
-// Candidates theta_rel (relative to t_ref) go to rec.cand; NaN marks none.
-template <int N>
-__global__ __launch_bounds__(64) void k_qr(double* rec, int stride, int64_t np, const int64_t* list,
-                                           const unsigned int* list_count, SolveCounters* counters,
-                                           unsigned* queue) {
-  // the fallback tiers run beside the side stream's scoring: their waves
-  // take issue priority over it on a shared SIMD (the tiers are few, latency-bound
-  // waves on the step's critical path)
-  __builtin_amdgcn_s_setprio(2);
-  extern __shared__ double smq[];
-  double* A = smq;
-  double* wr = A + qr_mat_doubles(N);
-  double* wi = wr + N;
-  const int lane = wave_lane();
-  const RecLayout RL((N + 2) / 6);
-  int64_t total = np;
-  if (list) total = (int64_t)*list_count;
-  unsigned long long sweeps_acc = 0;
-  for (int64_t w = first_item(queue, lane); w < total; w = next_item(queue, lane, w)) {
-    const int64_t q = list ? list[w] : w;
-    double* R = rec + q * (int64_t)stride;
-    const int st = (int)R[RL.meta + M_STATUS];
-    if (st == ST_BAD_LC || st == ST_CONSTANT) continue;
-    const double* f = R + RL.f;
-    const double lead = f[N];
-    int sw;
-    if constexpr (N > 64) {
-      constexpr int ld = N + 1;
-      for (int i = lane; i < N; i += 64) {
-        for (int j = 0; j < N; ++j) A[i * ld + j] = 0.0;
-        if (i > 0) A[i * ld + i - 1] = 1.0;
-      }
-      wave_sync();
-      for (int c = lane; c < N; c += 64) A[c] = -f[N - 1 - c] / lead;
-      wave_sync();
-      balance_wave2<N>(A, lane);
-      sw = hqr_wave2<N>(A, wr, wi, lane);
-    } else {
-      // the companion matrix of f: zeros, the first row, the subdiagonal of ones
-      auto run = [&](const auto& X) {
-        for (int q = lane; q < (int)qr_mat_doubles(N); q += 64) A[q] = 0.0;
-        wave_sync();
-        if (lane < N) X(0, lane) = -f[N - 1 - lane] / lead;
-        if (lane >= 1 && lane < N) X(lane, lane - 1) = 1.0;
-        wave_sync();
-        balance_wave<N>(X, lane);
-        return hqr_wave<N>(X, wr, wi, lane);
-      };
-      if constexpr (qr_packed(N)) sw = run(PackedHess<N>{A});
-      else sw = run(DenseHess<N>{A});
-    }
-    if (sw < 0) {
-      if (lane == 0) R[RL.meta + M_STATUS] = (double)ST_NO_CONVERGE;
-    } else {
-      sweeps_acc += (unsigned long long)sw;
-    }
-    const double phi0 = R[RL.meta + M_PHI0];
-    bool real[2] = {false, false};
-#pragma unroll
-    for (int sl = 0; sl < (N > 64 ? 2 : 1); ++sl) {
-      const int c = lane + 64 * sl;
-      if (c < N) {
-        const double xr = wr[c], xi = wi[c];
-        double th = __longlong_as_double(0x7ff8000000000000ll);
-        if (xi >= 0.0 && isfinite(xr) && isfinite(xi)) th = phi0 + atan2(xr, 1.0 - xi) + atan2(xr, 1.0 + xi);
-        real[sl] = xi == 0.0 && isfinite(xr);
-        R[RL.cand + c] = th;
-      }
-    }
-    const unsigned long long rmask = __ballot(real[0]);
-    const unsigned long long rmask1 = N > 64 ? __ballot(real[1]) : 0ull;
-    if (lane == 0) {
-      R[RL.meta + M_REAL_LO] = (double)(unsigned)(rmask & 0xffffffffull);
-      R[RL.meta + M_REAL_HI] = (double)(unsigned)(rmask >> 32);
-      R[RL.meta + M_REAL_X] = (double)(unsigned)(rmask1 & 0xffffffffull);
-    }
-    wave_sync();
-  }
-  if (counters && lane == 0 && sweeps_acc) atomicAdd(&counter_slot(counters)->qr_sweeps, sweeps_acc);
 }
 
 // ------------------------------------------------------------- assemble
@@ -1463,37 +973,6 @@ __global__ void k_export_stats(const LcInfo* lcs, double* out) {
 }
 
 // ------------------------------------------------------------ launchers
-
-template <int N>
-static hipError_t launch_qr_n(double* rec, int stride, int64_t np, const int64_t* list,
-                              const unsigned* list_count, SolveCounters* counters, unsigned* queue, int waves,
-                              hipStream_t st) {
-  hipLaunchKernelGGL(k_qr<N>, dim3((unsigned)waves), dim3(64), qr_lds_bytes(N), st, rec, stride, np, list,
-                     list_count, counters, queue);
-  return hipGetLastError();
-}
-
-hipError_t launch_qr(int H, double* rec, int stride, int64_t np, const int64_t* list, const unsigned* list_count,
-                     SolveCounters* counters, unsigned* queue, int waves, hipStream_t st) {
-  switch (H) {
-    case 1: return launch_qr_n<4>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 2: return launch_qr_n<10>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 3: return launch_qr_n<16>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 4: return launch_qr_n<22>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 5: return launch_qr_n<28>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 6: return launch_qr_n<34>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 7: return launch_qr_n<40>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 8: return launch_qr_n<46>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 9: return launch_qr_n<52>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 10: return launch_qr_n<58>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 11: return launch_qr_n<64>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 12: return launch_qr_n<70>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 13: return launch_qr_n<76>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 14: return launch_qr_n<82>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    case 15: return launch_qr_n<88>(rec, stride, np, list, list_count, counters, queue, waves, st);
-    default: return hipErrorInvalidValue;
-  }
-}
 
 hipError_t launch_assemble(int precision, const SolveArgs& a, double* rec, int64_t p0, int64_t np, int waves,
                            hipStream_t st) {
