@@ -56,4 +56,53 @@ struct FusedMlpArgs {
   const unsigned* np_dev;   // nullable: rows past *np_dev (on the device) are skipped
 };
 
+// Rows of a training batch per workgroup of k_train_rows, and per partial sum
+// of the bias gradients.
+constexpr int kTileRows = 32;
+
+// Transposed bf16 weights of layers 1..3 of a network whose training runs
+// through k_train_rows: layer l + 1 at p[l], `nin` rows of ld[l] (nout[l] padded
+// with zeros to whole K slices); p[0] == nullptr for other networks.
+struct TransposedWeights {
+  uint16_t* p[3];
+  int64_t oW[3];            // offsets of these layers in the parameters
+  int nin, nout[3], ld[3];
+};
+
+// Forward, loss and backward of a batch (k_train_rows): width a multiple of 32
+// up to 256, din up to 256.
+struct TrainArgs {
+  const uint16_t* X;        // B x din bf16
+  int64_t B;
+  int din, width, dout;
+  const uint16_t* w;        // bf16 weights, layer l at w + oW[l]
+  const float* w32;         // FP32 parameters (biases at w32 + ob[l])
+  int64_t oW[4], ob[4];
+  const uint16_t* wt[3];    // transposed weights of layers 1..3 (TransposedWeights), rows of ldt[l]
+  int ldt[3];
+  const float* roots;       // B x R
+  const int* nroots;
+  int R;
+  float lam;
+  uint16_t* h[3];           // hidden activations, B x width
+  uint16_t* g[4];           // gradients at the layers' outputs (bf16), B x width (layer 3: B x dout)
+  float* loss;              // B
+  float* bias_part;         // per tile of kTileRows rows: 3 width + dout column sums
+};
+
+// Weight gradients of a batch (k_wgrad) and the final sums (k_grad_reduce).
+struct WgradArgs {
+  const uint16_t* g[4];     // gradients at the layers' outputs, B x nout[l]
+  const uint16_t* in[4];    // the layers' inputs, B x nin[l]
+  int nin[4], nout[4];
+  int64_t oW[4], ob[4];
+  int64_t B, rows;          // rows per split (a multiple of 32)
+  int splits;
+  float* wpart;             // splits x n_params
+  int64_t n_params;
+  const float* bias_part;   // btiles x (sum of nout)
+  int btiles;
+  int tiles[4], wblocks;    // filled in by the launcher
+};
+
 }  // namespace ftp

@@ -12,16 +12,9 @@
 #include <hip/hip_ext.h>
 #include "ftp_solve_common.h"
 #include "ftp_args.h"
+#include "ftp_mlp_tile.h"
 
 namespace ftp {
-
-typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8_t;
-
-// float -> bf16 bits by the hardware conversion (round to nearest even, one
-// instruction on gfx950; equal to f2bf for finite values), used by the
-// inference epilogues of k_dense_bf16 and k_mlp_fused alike
-__device__ __forceinline__ uint16_t bf16_rne(float x) { return __builtin_bit_cast(uint16_t, (__bf16)x); }
-typedef __attribute__((__vector_size__(4 * sizeof(float)))) float f32x4_t;
 
 // ------------------------------------------------------------------ GEMM
 
@@ -251,15 +244,6 @@ __global__ __launch_bounds__(256 * RW) void k_dense_bf16(DenseArgs d) {
 
 // --------------------------------------------------------- small kernels
 
-// db[n] = sum_m G[m, n] (G fp32, row stride ld)
-__global__ __launch_bounds__(256) void k_colsum(const float* G, int64_t M, int N, int64_t ld, float* out) {
-  const int n = blockIdx.x * 256 + threadIdx.x;
-  if (n >= N) return;
-  float s = 0.f;
-  for (int64_t m = 0; m < M; ++m) s += G[m * ld + n];
-  out[n] = s;
-}
-
 // Chamfer loss on the circle between seed vectors e_k = (u_k, v_k) and root
 // unit vectors r_j = (cos, sin) (one thread per sample):
 //   L_b = (1/n) sum_j min_k |e_k - r_j|^2 + lam (1/K) sum_k min_j |e_k - r_j|^2,
@@ -312,10 +296,12 @@ __global__ __launch_bounds__(256) void k_chamfer(const float* out, int64_t B, in
   }
 }
 
-// Adam (Kingma & Ba 2015) on FP32 master weights; writes the bf16 copy.
+// Adam (Kingma & Ba 2015) on FP32 master weights; writes the bf16 copy and,
+// where the network has them (wt.p[0] != nullptr), the transposed bf16 weights
+// of layers 1..3.
 __global__ __launch_bounds__(256) void k_adam(float* w, uint16_t* wb, const float* g, float* m, float* v,
                                               int64_t n, float lr, float b1, float b2, float eps, float c1,
-                                              float c2) {
+                                              float c2, TransposedWeights wt) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= n) return;
   const float gi = g[i];
@@ -325,7 +311,18 @@ __global__ __launch_bounds__(256) void k_adam(float* w, uint16_t* wb, const floa
   v[i] = vi;
   const float wi = w[i] - lr * (mi / c1) / (sqrtf(vi / c2) + eps);
   w[i] = wi;
-  wb[i] = f2bf(wi);
+  const uint16_t bi = f2bf(wi);
+  wb[i] = bi;
+  if (wt.p[0]) {
+#pragma unroll
+    for (int l = 0; l < 3; ++l) {
+      const int64_t q = i - wt.oW[l];
+      if (q >= 0 && q < (int64_t)wt.nin * wt.nout[l]) {
+        const int o = (int)(q / wt.nin), k = (int)(q - (int64_t)o * wt.nin);
+        wt.p[l][(int64_t)k * wt.ld[l] + o] = bi;
+      }
+    }
+  }
 }
 
 __global__ __launch_bounds__(256) void k_f32_to_bf16(const float* x, uint16_t* y, int64_t n) {
@@ -622,11 +619,6 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_colsum(const float* G, int64_t M, int N, int64_t ld, float* out, hipStream_t st) {
-  hipLaunchKernelGGL(k_colsum, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, G, M, N, ld, out);
-  return hipGetLastError();
-}
-
 hipError_t launch_chamfer(const float* out, int64_t B, int Kseeds, const float* roots, const int* nroots, int R,
                           float lam, float* loss_b, float* dout, uint16_t* dout_bf, hipStream_t st) {
   hipLaunchKernelGGL(k_chamfer, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, st, out, B, Kseeds, roots,
@@ -635,9 +627,9 @@ hipError_t launch_chamfer(const float* out, int64_t B, int Kseeds, const float* 
 }
 
 hipError_t launch_adam(float* w, uint16_t* wb, const float* g, float* m, float* v, int64_t n, float lr, float b1,
-                       float b2, float eps, float c1, float c2, hipStream_t st) {
+                       float b2, float eps, float c1, float c2, const TransposedWeights& wt, hipStream_t st) {
   hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, w, wb, g, m, v, n, lr, b1, b2,
-                     eps, c1, c2);
+                     eps, c1, c2, wt);
   return hipGetLastError();
 }
 
