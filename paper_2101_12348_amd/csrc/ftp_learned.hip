@@ -311,165 +311,216 @@ __device__ __forceinline__ double bperm_d(int addr, double v) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Four Sturm chains per wavefront, one per 16-lane row.  Lane 16 c + l holds
-// coefficients 16 r + l (r = 0..3) of chain c's members in registers, so a
-// member of up to 64 coefficients needs no LDS and every instruction of a
-// step serves four chains: the shift by one power of x is a row rotation
-// (DPP row_ror:1, lane 0 taking lane 15 of the register below), the two
+// Sturm chains, one per group of G lanes (16: four per wavefront, D < 64; 8:
+// eight, D < 32).  Lane l of a group holds R consecutive coefficients R l .. R l
+// + R - 1 of each member in registers, so the shift by one power of x moves one
+// register between lanes (DPP row_shr:1) and the rest by name; R falls from 4 to
+// 2 and 1 as the members' degree falls below 2 G and G (sturm_repack).  The two
 // coefficients a step needs from its own chain (the quotient's and the new
-// leading coefficient) come by ds_bpermute from the row's lane, and the
-// largest coefficient by a row all-reduction.  Per coefficient the arithmetic
-// is that of sturm_begin / sturm_step (scaled members with leading
-// coefficient +-1, quotients without division, the same step test on high
-// words), and a step only touches the registers below the member's degree
-// (NR of them), so late steps cost a quarter of early ones.
-struct Rows4State {
-  int hMA, hMB;   // hi(max |coefficient|) of the last two members
-  int m12, m13;   // smallest margins of the two step tests so far
-  int hmax;       // largest hi(max |t|) so far (finiteness)
-  int sp, vp;     // last member positive at +inf (0 / 1); sign changes at +inf
+// leading one) come by ds_bpermute.  Per coefficient the arithmetic is that of
+// sturm_begin / sturm_step (scaled members with leading coefficient +-1,
+// quotients without division).  Coefficients above a member's degree are not
+// cleared: they only ever move upwards, and the maxima leave them out.
+//
+// The tests of the steps (sturm_step_ok, as margins) are taken G steps at a
+// time: lane j of a group keeps step j's two high words (largest coefficient,
+// leading coefficient with its sign), and sturm_flush forms the margins and sign
+// changes of all of them at once.  A step is 35 vector instructions at R = 4
+// (22 at R = 1) for 64 / G chains; with the coefficients strided over the lanes
+// and the tests in every step it was 66 (36) for four.
+template <int G>
+struct SturmTests {
+  int hrS, hlS;     // this lane's step: hi(max |t|), high word of the leading coefficient
+  int n;            // steps held (wave-uniform)
+  int c1, c2;       // hi(max |coefficient|) of the last two members before them
+  int sp;           // sign of the last member before them at +inf (1: positive)
+  int m12, m13;     // smallest margins of the two tests so far (per lane)
+  int hmax;         // largest hi(max |t|) so far (finiteness; per lane)
+  int vp;           // sign changes at +inf so far (per lane)
 };
 
-// maximum of an int over each 16-lane row, left in every lane of the row
-__device__ __forceinline__ int row_max_int(int h) {
+__device__ __forceinline__ int bperm_i(int addr, int v) { return __builtin_amdgcn_ds_bpermute(addr, v); }
+
+// maximum of an int over each group, left in every lane of the group
+template <int G>
+__device__ __forceinline__ int group_max_int(int h) {
   h = max(h, dpp_i<0xB1, 0xf>(h));    // quad_perm [1, 0, 3, 2]
   h = max(h, dpp_i<0x4E, 0xf>(h));    // quad_perm [2, 3, 0, 1]
+  if constexpr (G == 8) return max(h, dpp_i<0x141, 0xf>(h));   // row_half_mirror
   h = max(h, dpp_i<0x124, 0xf>(h));   // row_ror:4
-  h = max(h, dpp_i<0x128, 0xf>(h));   // row_ror:8
-  return h;
+  return max(h, dpp_i<0x128, 0xf>(h));   // row_ror:8
+}
+template <int G>
+__device__ __forceinline__ int group_sum_int(int h) {
+  h += dpp_i<0xB1, 0xf>(h);
+  h += dpp_i<0x4E, 0xf>(h);
+  if constexpr (G == 8) return h + dpp_i<0x141, 0xf>(h);
+  h += dpp_i<0x124, 0xf>(h);
+  return h + dpp_i<0x128, 0xf>(h);
 }
 
-__device__ __forceinline__ void sturm4_begin(const double (&G)[4], double gtop, int D, int l, double (&A)[4],
-                                             double (&B)[4], double& bl, double& ab, Rows4State& S, bool& ok) {
-  const double ag = fabs(gtop), sgn = gtop > 0.0 ? 1.0 : -1.0;
-  const double sa = fast_rcp_d(ag + 1e-300), sb = fast_rcp_d(D * ag + 1e-300);
-  ok = ag > 0.0 && ag < INFINITY;
-  int hA = 0, hB = 0;
-  double nxt = dpp_d<0x12F>(G[0]);   // row_ror:15: lane l + 1 of the row (lane 0 at l = 15)
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int k = 16 * r + l;
-    const double up = r < 3 ? dpp_d<0x12F>(G[r < 3 ? r + 1 : 3]) : 0.0;
-    const double g1 = l == 15 ? up : nxt;   // coefficient k + 1
-    nxt = up;
-    const double dv = k < D ? (k + 1) * g1 : 0.0;
-    A[r] = k == D ? sgn : G[r] * sa;
-    B[r] = k == D - 1 ? sgn : dv * sb;
-    hA = max(hA, hiword(A[r]) & 0x7fffffff);
-    hB = max(hB, hiword(B[r]) & 0x7fffffff);
+// Tests and sign changes of the T.n steps held; gb4: byte address (4 x lane) of
+// the group's first lane.
+template <int G>
+__device__ __forceinline__ void sturm_flush(SturmTests<G>& T, int l, int gb4) {
+  const int ha = T.hlS & 0x7fffffff, hM = sturm_member_hi(T.hrS, ha), s = (int)((unsigned)T.hlS >> 31);
+  const int a1 = gb4 + (((l - 1) & (G - 1)) << 2), a2 = gb4 + (((l - 2) & (G - 1)) << 2);
+  const int x1 = bperm_i(a1, hM), x2 = bperm_i(a2, hM), xs = bperm_i(a1, s);
+  const int p1 = l >= 1 ? x1 : T.c1, p2 = l >= 2 ? x2 : (l == 1 ? T.c1 : T.c2), ps = l >= 1 ? xs : T.sp;
+  if (l < T.n) {
+    T.m12 = min(T.m12, T.hrS - max(p1, p2));
+    T.m13 = min(T.m13, ha - T.hrS);
+    T.hmax = max(T.hmax, T.hrS);
+    T.vp += s ^ ps;
   }
-  S.hMA = max(row_max_int(hA), kHi1);
-  S.hMB = row_max_int(hB);
-  S.m12 = S.m13 = 0x7fffffff;
-  S.hmax = 0;
-  S.sp = gtop > 0.0 ? 1 : 0;
-  S.vp = 0;
-  bl = sgn;
-  ab = 1.0;
+  // (a partial flush is the last: the carried values are those of full ones)
+  T.c1 = bperm_i(gb4 + ((G - 1) << 2), hM);
+  T.c2 = bperm_i(gb4 + ((G - 2) << 2), hM);
+  T.sp = bperm_i(gb4 + ((G - 1) << 2), s);
+  T.n = 0;
 }
 
-// Member q from the last two: A (older, degree db + 1) is overwritten by the
-// new member; B (degree db) is the newer.  db = D - q + 1; NR registers hold
-// every coefficient up to db + 1, so db itself lies in register NR - 1, or in
-// NR - 2 when db + 1 starts register NR - 1 (db % 16 == 15), and db - 1 one
-// register lower still when db % 16 == 0.
-template <int NR>
-__device__ __forceinline__ void sturm4_step(double (&A)[4], const double (&B)[4], double& bl, double& ab,
-                                            Rows4State& S, int db, int l, int pbase) {
-  double t[NR];
-  double below = 0.0;
+// Signs of the last two members' leading coefficients as sign bits.
+struct SturmSigns { int b, ab; };   // newer member; product with the older
+__device__ __forceinline__ double with_sign(double v, int signbit) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  return __longlong_as_double((long long)(u ^ ((unsigned long long)(unsigned)signbit << 32)));
+}
+
+// One step: from A (older, degree db + 1) and B (degree db), A becomes the
+// new member.  RQ = db % R.
+template <int G, int R, int RQ>
+__device__ __forceinline__ void sturm_rows_step(double (&A)[4], const double (&B)[4], SturmSigns& S, SturmTests<G>& T,
+                                                int db, int l, int gb4) {
+  constexpr int RL = (RQ + R - 1) % R;
+  const int lq = db / R, ll = (db - 1) / R;   // (R a power of two)
+  const double ab = from_hiword(S.ab ^ kHi1);
+  double t[R];
+  {
+    double sh = dpp_d<0x111>(B[R - 1]);   // row_shr:1, zero into lane 0
+    if (G == 8) sh = l == 0 ? 0.0 : sh;
+    t[0] = fma(-ab, sh, A[0]);
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const double rot = dpp_d<0x121>(B[r]);   // row_ror:1: lane l - 1 (lane 0: lane 15)
-    t[r] = fma(-ab, l == 0 ? below : rot, A[r]);
-    below = rot;
+    for (int r = 1; r < R; ++r) t[r] = fma(-ab, B[r - 1], A[r]);
   }
-  const int lq = db & 15;
-  const bool top = lq != 15;                          // db in register NR - 1 (else NR - 2)
-  const double tq = NR == 1 ? t[0] : (top ? t[NR - 1] : t[NR > 1 ? NR - 2 : 0]);
-  const double q0 = bperm_d(pbase + (lq << 2), tq) * bl;
-  // remainder: coefficients below db (the rest are zeroed)
+  const double q0 = with_sign(bperm_d(gb4 + (lq << 2), t[RQ]), S.b);
 #pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const double v = fma(-q0, B[r], t[r]);
-    if (r < NR - 2) {
-      t[r] = v;
-    } else if (r == NR - 2) {
-      t[r] = (top || l < lq) ? v : 0.0;
-    } else {
-      t[r] = (top && l < lq) ? v : 0.0;
-    }
+  for (int r = 0; r < R; ++r) t[r] = fma(-q0, B[r], t[r]);
+  const double lead = bperm_d(gb4 + (ll << 2), t[RL]);
+  // largest of the coefficients below db: all of a lane's, in lane lq its first RQ
+  double part = 0.0, all = fabs(t[0]);
+#pragma unroll
+  for (int r = 1; r < R; ++r) {
+    if (r == RQ) part = all;
+    all = fmax(all, fabs(t[r]));
   }
-  // the new leading coefficient, index db - 1
-  const int ll = (db - 1) & 15;
-  const int rl = (db - 1) >> 4, rtop = (db + 1) >> 4;   // rtop = NR - 1
-  const int drop = rtop - rl;                              // 0, 1 or 2 registers below the top
-  double tl = t[NR - 1];
-  if (NR > 1) tl = drop == 1 ? t[NR > 1 ? NR - 2 : 0] : tl;
-  if (NR > 2) tl = drop == 2 ? t[NR > 2 ? NR - 3 : 0] : tl;
-  const double lead = bperm_d(pbase + (ll << 2), tl);
-  int h = 0;
-#pragma unroll
-  for (int r = 0; r < NR; ++r) h = max(h, hiword(t[r]) & 0x7fffffff);
-  const int hr = row_max_int(h);
-  const int hlead = hiword(lead), ha = hlead & 0x7fffffff;
-  S.m12 = min(S.m12, hr - max(S.hMA, S.hMB));
-  S.m13 = min(S.m13, ha - hr);
-  S.hmax = max(S.hmax, hr);
-  S.hMA = S.hMB;
-  S.hMB = sturm_member_hi(hr, ha);
-  const int tp = (int)((unsigned)hlead >> 31);   // P_q = -t / |lead| positive at +inf
-  S.vp += tp ^ S.sp;
-  S.sp = tp;
+  int h = l < lq ? hiword(all) : 0;
+  if (RQ > 0) h = l == lq ? hiword(part) : h;
+  const int hr = group_max_int<G>(h), hlead = hiword(lead);
+  const bool mine = l == T.n;
+  T.hrS = mine ? hr : T.hrS;
+  T.hlS = mine ? hlead : T.hlS;
+  if (++T.n == G) sturm_flush<G>(T, l, gb4);
+  // P_q = -t / |lead|, its leading coefficient -sign(lead)
   const double sc = fast_rcp_d(fabs(lead) + 1e-300);
-  const double nb = from_hiword((hlead & 0x80000000) ^ 0xbff00000);   // -sign(lead)
 #pragma unroll
-  for (int r = 0; r < NR; ++r) A[r] = -t[r] * sc;
-  ab = bl * nb;
-  bl = nb;
+  for (int r = 0; r < R; ++r) A[r] = -t[r] * sc;
+  const int nb = ~hlead & (int)0x80000000;
+  S.ab = S.b ^ nb;
+  S.b = nb;
 }
 
-// steps q .. qend - 1 with NR registers; A holds the older member and B the
-// newer on entry and on return
-template <int NR>
-__device__ __forceinline__ void sturm4_phase(double (&A)[4], double (&B)[4], double& bl, double& ab, Rows4State& S,
-                                             int D, int& q, int qend, int l, int pbase) {
-  for (; q + 1 < qend; q += 2) {
-    sturm4_step<NR>(A, B, bl, ab, S, D - q + 1, l, pbase);
-    sturm4_step<NR>(B, A, bl, ab, S, D - q, l, pbase);
-  }
-  if (q < qend) {
-    sturm4_step<NR>(A, B, bl, ab, S, D - q + 1, l, pbase);
-    ++q;
+// R to R / 2 coefficients per lane.
+template <int R>
+__device__ __forceinline__ void sturm_repack(double (&X)[4], int l, int gb4) {
+  const int src = gb4 + ((l >> 1) << 2);
+  const bool odd = l & 1;
+  double y[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) y[r] = bperm_d(src, X[r]);
+#pragma unroll
+  for (int r = 0; r < R / 2; ++r) X[r] = odd ? y[r + R / 2] : y[r];
+}
+
+// Distinct real roots of the degree-D polynomial of this lane's group (D even,
+// D + 1 <= 4 G; C[r] = coefficient 4 l + r, zero above D; gtop = coefficient D),
+// or -1 when a step fails its test (`raw`: the count regardless).  All lanes
+// must be active.
+template <int G>
+__device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double gtop, int D, int lane, int& raw) {
+  const int l = lane & (G - 1), gb4 = (lane & ~(G - 1)) << 2;
+  double A[4], B[4];
+  SturmSigns S;
+  SturmTests<G> T;
+  bool ok;
+  {
+    const double ag = fabs(gtop), sgn = gtop > 0.0 ? 1.0 : -1.0;
+    const double sa = fast_rcp_d(ag + 1e-300), sb = fast_rcp_d(D * ag + 1e-300);
+    ok = ag > 0.0 && ag < INFINITY;
+    int hA = 0, hB = 0;
+    const double up = dpp_d<0x101>(C[0]);   // row_shl:1: coefficient 4 (l + 1) (used up to coefficient D)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const double x = A[r];
-      A[r] = B[r];
-      B[r] = x;
+      const int k = 4 * l + r;
+      const double g1 = r < 3 ? C[r < 3 ? r + 1 : 3] : up;   // coefficient k + 1
+      const double dv = k < D ? (k + 1) * g1 : 0.0;
+      A[r] = k == D ? sgn : C[r] * sa;
+      B[r] = k == D - 1 ? sgn : dv * sb;
+      hA = max(hA, hiword(A[r]) & 0x7fffffff);
+      hB = max(hB, hiword(B[r]) & 0x7fffffff);
+    }
+    T.c2 = max(group_max_int<G>(hA), kHi1);
+    T.c1 = group_max_int<G>(hB);
+    T.m12 = T.m13 = 0x7fffffff;
+    T.hmax = T.vp = T.n = T.hrS = T.hlS = 0;
+    T.sp = gtop > 0.0 ? 1 : 0;
+    S.b = gtop > 0.0 ? 0 : (int)0x80000000;
+    S.ab = 0;
+  }
+  int db = D - 1;   // degree of the newer member (odd)
+  if (db > 2 * G - 5) {
+    if ((db & 3) == 1) {
+      sturm_rows_step<G, 4, 1>(A, B, S, T, db, l, gb4);
+      sturm_rows_step<G, 4, 0>(B, A, S, T, db - 1, l, gb4);
+      db -= 2;
+    }
+#pragma unroll 1
+    for (; db > 2 * G - 5; db -= 4) {
+      sturm_rows_step<G, 4, 3>(A, B, S, T, db, l, gb4);
+      sturm_rows_step<G, 4, 2>(B, A, S, T, db - 1, l, gb4);
+      sturm_rows_step<G, 4, 1>(A, B, S, T, db - 2, l, gb4);
+      sturm_rows_step<G, 4, 0>(B, A, S, T, db - 3, l, gb4);
     }
   }
+  sturm_repack<4>(A, l, gb4);
+  sturm_repack<4>(B, l, gb4);
+#pragma unroll 1
+  for (; db > G - 3; db -= 2) {
+    sturm_rows_step<G, 2, 1>(A, B, S, T, db, l, gb4);
+    sturm_rows_step<G, 2, 0>(B, A, S, T, db - 1, l, gb4);
+  }
+  sturm_repack<2>(A, l, gb4);
+  sturm_repack<2>(B, l, gb4);
+#pragma unroll 1
+  for (; db > 1; db -= 2) {
+    sturm_rows_step<G, 1, 0>(A, B, S, T, db, l, gb4);
+    sturm_rows_step<G, 1, 0>(B, A, S, T, db - 1, l, gb4);
+  }
+  sturm_rows_step<G, 1, 0>(A, B, S, T, 1, l, gb4);
+  if (T.n) sturm_flush<G>(T, l, gb4);
+  const int m12 = -group_max_int<G>(-T.m12), m13 = -group_max_int<G>(-T.m13);
+  ok = ok && group_max_int<G>(T.hmax) < 0x7ff00000 && m12 > -kHiT12 && m13 > -kHiT13;
+  raw = D - 2 * group_sum_int<G>(T.vp);
+  return ok ? raw : -1;
 }
 
-// Distinct real roots of the degree-D polynomial of this lane's row (D + 1 <=
-// 64; G[r] = coefficient 16 r + (lane & 15), zero above D; gtop = coefficient
-// D), or -1 when a step fails its test (`raw`: the count regardless).  All
-// lanes must be active.
-__device__ __forceinline__ int sturm_count_rows4(const double (&G)[4], double gtop, int D, int lane, int& raw) {
-  const int l = lane & 15, pbase = (lane & 48) << 2;
-  double A[4], B[4], bl, ab;
-  Rows4State S;
-  bool ok;
-  sturm4_begin(G, gtop, D, l, A, B, bl, ab, S, ok);
-  // step q touches coefficients up to D - q + 2: four registers while that is
-  // at least 48, three down to 32, two down to 16, then one
-  int q = 2;
-  sturm4_phase<4>(A, B, bl, ab, S, D, q, min(D + 1, D - 45), l, pbase);
-  sturm4_phase<3>(A, B, bl, ab, S, D, q, min(D + 1, D - 29), l, pbase);
-  sturm4_phase<2>(A, B, bl, ab, S, D, q, min(D + 1, D - 13), l, pbase);
-  sturm4_phase<1>(A, B, bl, ab, S, D, q, D + 1, l, pbase);
-  ok = ok && S.hmax < 0x7ff00000 && S.m12 > -kHiT12 && S.m13 > -kHiT13;
-  raw = D - 2 * S.vp;
-  return ok ? raw : -1;
+// Lanes per Sturm chain at degree D < 64.
+__host__ __device__ inline constexpr int sturm_group(int D) { return D < 32 ? 8 : 16; }
+
+// C[r] = coefficient 4 l + r of f (zero above D), l the lane's index in its group.
+__device__ __forceinline__ void load_coefficients(const double* f, bool on, int D, int l, double (&C)[4]) {
+#pragma unroll
+  for (int r = 0; r < 4; ++r) C[r] = (on && 4 * l + r <= D) ? f[4 * l + r] : 0.0;
 }
 
 // Newton on R(theta) carried out on the Cayley polynomial.  With x = tan((theta
@@ -576,7 +627,7 @@ __device__ __forceinline__ double theta_from_u(double phi0, double u, int sg) {
 
 // Four frequencies per wavefront (H <= 10, D < 64): frequencies 4b .. 4b + 3
 // of the list.  Their four Sturm chains run side by side, one per 16-lane
-// row (sturm_count_rows4); then Newton runs on two of them at a time, lanes
+// row (sturm_count_groups); then Newton runs on two of them at a time, lanes
 // 0..31 for the first and 32..63 for the second, each half with min(32, D)
 // starts: the 2H network seeds and min(32, D) - 2H evenly spaced phases (all
 // evenly spaced without network).  The Newton steps are those of R in theta,
@@ -584,7 +635,8 @@ __device__ __forceinline__ double theta_from_u(double phi0, double u, int sg) {
 // merged one root per pass, and a half that has reached its count is frozen
 // while the other goes on.
 struct NewtonAcc {
-  unsigned long long iters, roots, fb;
+  int iters;   // this lane's
+  unsigned long long roots, fb;
 };
 
 // Newton on frequencies wA (lanes 0..31) and wA + 1 (lanes 32..63, if hasB)
@@ -677,19 +729,27 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
       if (half ? doneB : doneA) live = false;
     }
   }
-  acc.iters += (unsigned long long)wave_sum((double)its);
+  acc.iters += its;
   const double thw = theta_from_u(phi0, u, sg);
   const int nuA = __popcll(um & lo32), nuB = __popcll(um >> 32);
   const bool okA = cA >= 0 && nuA == cA, okB = cB >= 0 && nuB == cB;
   const bool ok = half ? okB : okA;
   const int nu = half ? nuB : nuA;
   double* cand = Rh + RL.cand;
-  if (cnt != -2 && ok)
-    for (int c = hl; c < D; c += 32) cand[c] = __longlong_as_double(0x7ff8000000000000ll);
-  lwave_sync();
-  // confirmed roots, or the distinct roots found, which start the Aberth
-  // iteration of a fallback frequency
-  if (cnt != -2 && ((um >> lane) & 1ull)) cand[__popcll(um & hmask & below)] = thw;
+  // confirmed roots: to the front of the half in lane order (a permutation of
+  // the half's lanes), NaN behind them; one store of the slots the scoring reads
+  const bool uniq = (um >> lane) & 1ull;
+  const int rank = uniq ? __popcll(um & hmask & below) : nu + __popcll(~um & hmask & below);
+  {
+    const unsigned long long v = (unsigned long long)__double_as_longlong(thw);
+    const int to = (32 * half + rank) << 2;
+    const int lo = __builtin_amdgcn_ds_permute(to, (int)(unsigned)(v & 0xffffffffull));
+    const int hi = __builtin_amdgcn_ds_permute(to, (int)(unsigned)(v >> 32));
+    const double r = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+    if (cnt != -2 && ok && hl < D) cand[hl] = hl < nu ? r : __longlong_as_double(0x7ff8000000000000ll);
+  }
+  // else the distinct roots found, which start the later tiers
+  if (cnt != -2 && !ok && uniq) cand[rank] = thw;
   if (cnt != -2 && !ok && hl == 0) {
     Rh[RL.meta + M_WARM] = (double)nu;
     Rh[RL.meta + M_COUNT] = (double)cnt;
@@ -707,66 +767,62 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
 // to 80, more spills, but more waves to cover the Sturm steps' latency);
 // which is faster depends on the workload and the grid, so the launch shape
 // picks it.
-template <int OCC>
+template <int G, int OCC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
-  const int lane = threadIdx.x & 63, row = lane >> 4, l = lane & 15;
+  constexpr int NC = 64 / G;   // frequencies per wavefront
+  const int lane = threadIdx.x & 63, row = lane / G, l = lane & (G - 1);
   const int H = a.H, D = 6 * H - 2;
   const int FS = D + 2;   // f and its reversal for each frequency, 16-byte aligned
   const RecLayout RL(H);
   NewtonAcc acc{0, 0, 0};
-  for (int64_t w0 = 4 * (int64_t)blockIdx.x; w0 < L.np; w0 += 4 * (int64_t)gridDim.x) {
-    // statuses of the four frequencies (inactive: past the end, rejected
-    // lightcurve, or P constant in theta_2)
-    int act = 0;
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (w0 + c < L.np) {
-        const int st = (int)L.rec[(w0 + c) * (int64_t)RL.stride + RL.meta + M_STATUS];
-        act |= (st != ST_BAD_LC && st != ST_CONSTANT) ? 1 << c : 0;
-      }
-    }
+  for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
+    // this group's frequency (inactive: past the end, rejected lightcurve, or P
+    // constant in theta_2)
+    bool mine = w0 + row < L.np;
+    double* Rr = L.rec + (w0 + (mine ? row : 0)) * (int64_t)RL.stride;
+    const int st = (int)Rr[RL.meta + M_STATUS];
+    mine = mine && st != ST_BAD_LC && st != ST_CONSTANT;
+    const unsigned long long act = __ballot(mine);
     if (!act) continue;
     if (L.flags & 1u) {   // forced fallback
-      if (l == 0 && ((act >> row) & 1)) {
+      if (l == 0 && mine) {
         const unsigned slot = atomicAdd(L.fb_count, 1u);
         L.fb_list[slot] = w0 + row;
-        double* Rr = L.rec + (w0 + row) * (int64_t)RL.stride;
         Rr[RL.meta + M_FALLBACK] = 1.0;
         Rr[RL.meta + M_WARM] = 0.0;
         Rr[RL.meta + M_COUNT] = -1.0;
       }
-      acc.fb += (unsigned long long)__popc((unsigned)act);
+      acc.fb += (unsigned long long)(__popcll(act) / G);
       continue;
     }
-    // lane 16 c + l: coefficients 16 r + l of frequency c (zero above D or
-    // for an inactive frequency); f and its reversal to LDS for Newton
-    const bool mine = (act >> row) & 1;
-    const double* f = L.rec + (w0 + (mine ? row : 0)) * (int64_t)RL.stride + RL.f;
-    double G[4];
+    // coefficients to registers, f and its reversal to LDS for Newton
+    const double* f = Rr + RL.f;
+    double C[4];
+    load_coefficients(f, mine, D, l, C);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int k = 16 * r + l;
-      G[r] = (mine && k <= D) ? f[k] : 0.0;
+      const int k = 4 * l + r;
       if (mine && k <= D) {
-        sml[2 * FS * row + k] = G[r];
-        sml[2 * FS * row + FS + D - k] = G[r];
+        sml[2 * FS * row + k] = C[r];
+        sml[2 * FS * row + FS + D - k] = C[r];
       }
     }
     const double gtop = mine ? f[D] : 0.0;
     lwave_sync();
     int raw;
-    int cnt = sturm_count_rows4(G, gtop, D, lane, raw);
+    int cnt = sturm_count_groups<G>(C, gtop, D, lane, raw);
     if (cnt < 2) cnt = -1;
     if (!mine) cnt = -2;
-    const int c0 = __builtin_amdgcn_readlane(cnt, 0), c1 = __builtin_amdgcn_readlane(cnt, 16);
-    const int c2 = __builtin_amdgcn_readlane(cnt, 32), c3 = __builtin_amdgcn_readlane(cnt, 48);
 #pragma unroll 1
-    for (int p = 0; p < 2; ++p) newton_pair(L, RL, H, w0 + 2 * p, p ? c2 : c0, p ? c3 : c1, sml + 4 * FS * p, lane, acc);
+    for (int p = 0; p < NC / 2; ++p)
+      newton_pair(L, RL, H, w0 + 2 * p, __builtin_amdgcn_readlane(cnt, 2 * p * G),
+                  __builtin_amdgcn_readlane(cnt, (2 * p + 1) * G), sml + 4 * FS * p, lane, acc);
   }
+  const unsigned long long iters = (unsigned long long)wave_sum((double)acc.iters);
   if (lane == 0 && a.counters) {
     SolveCounters* c = counter_slot(a.counters);
-    if (acc.iters) atomicAdd(&c->newton_iters, acc.iters);
+    if (iters) atomicAdd(&c->newton_iters, iters);
     if (acc.roots) atomicAdd(&c->roots_found, acc.roots);
     if (acc.fb) atomicAdd(&c->fallback, acc.fb);
   }
@@ -912,7 +968,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
 
 // Root counts of a record chunk (diagnostic of the count the learned and
 // uniform solvers trust): per pair, the Sturm count of the Cayley polynomial
-// f by the device code the Newton kernels use (sturm_count_rows4, four pairs
+// f by the device code the Newton kernels use (sturm_count_groups, four pairs
 // per wavefront, for H <= 10; sturm_count_line_reg for H = 11,
 // sturm_count_dd above), -1000 - n when the
 // chain fails its test (n: the count it reached regardless), -2 for an
@@ -923,22 +979,21 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
   const int lane = threadIdx.x & 63;
   const int D = 6 * H - 2;
   const RecLayout RL(H);
-  const bool four = D < 64;
-  const int64_t per = four ? 4 : 1;
+  const int G = D < 64 ? sturm_group(D) : 64;
+  const int per = 64 / G;
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < np; w0 += per * (int64_t)gridDim.x) {
     int cnt;
-    if (four) {
-      const int row = lane >> 4, l = lane & 15;
+    if (D < 64) {
+      const int row = lane / G, l = lane & (G - 1);
       const bool in = w0 + row < np;
       const double* f = rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f;
-      double G[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) G[r] = (in && 16 * r + l <= D) ? f[16 * r + l] : 0.0;
+      double C[4];
+      load_coefficients(f, in, D, l, C);
       int raw;
-      cnt = sturm_count_rows4(G, in ? f[D] : 0.0, D, lane, raw);
+      const double gtop = in ? f[D] : 0.0;
+      cnt = G == 8 ? sturm_count_groups<8>(C, gtop, D, lane, raw) : sturm_count_groups<16>(C, gtop, D, lane, raw);
       if (cnt < 0) cnt = -1000 - raw;
-      cnt = __builtin_amdgcn_readlane(cnt, 0) * (lane == 0) + __builtin_amdgcn_readlane(cnt, 16) * (lane == 1) +
-            __builtin_amdgcn_readlane(cnt, 32) * (lane == 2) + __builtin_amdgcn_readlane(cnt, 48) * (lane == 3);
+      cnt = __shfl(cnt, (lane * G) & 63);   // pair `lane` of the group to lane `lane`
     } else {
       const double* RA = rec + w0 * (int64_t)RL.stride;
       const double gv = RA[RL.f + lane];
@@ -1101,18 +1156,22 @@ hipError_t launch_newton_retry(const RetryArgs& A, int waves, hipStream_t st) {
 
 bool newton_four_per_wave(int H) { return 6 * H - 2 < 64; }
 
+template <int G>
+static void launch_newton_g(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+  const size_t lds = (size_t)(64 / G) * 2 * (6 * a.H) * sizeof(double);   // f and its reversal per frequency
+  const dim3 grid((unsigned)waves), block(64);
+  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<G, 6>), grid, block, lds, st, nullptr, done, 0, a, L);
+  else if (occ == 5) hipExtLaunchKernelGGL((k_newton_sturm4<G, 5>), grid, block, lds, st, nullptr, done, 0, a, L);
+  else hipExtLaunchKernelGGL((k_newton_sturm4<G, 4>), grid, block, lds, st, nullptr, done, 0, a, L);
+}
+
 // `done` (nullable): an event the launch itself records at the kernel's end
 // (no marker packet of its own on the stream); `occ`: 4, 5 or 6 (k_newton_sturm4).
 hipError_t launch_newton_sturm(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st,
                                hipEvent_t done) {
   if (newton_four_per_wave(a.H)) {
-    const size_t lds = (size_t)8 * (6 * a.H) * sizeof(double);   // 8 x (D + 2): f and its reversal, four pairs
-    if (occ == 6)
-      hipExtLaunchKernelGGL(k_newton_sturm4<6>, dim3((unsigned)waves), dim3(64), lds, st, nullptr, done, 0, a, L);
-    else if (occ == 5)
-      hipExtLaunchKernelGGL(k_newton_sturm4<5>, dim3((unsigned)waves), dim3(64), lds, st, nullptr, done, 0, a, L);
-    else
-      hipExtLaunchKernelGGL(k_newton_sturm4<4>, dim3((unsigned)waves), dim3(64), lds, st, nullptr, done, 0, a, L);
+    if (sturm_group(6 * a.H - 2) == 8) launch_newton_g<8>(a, L, waves, occ, st, done);
+    else launch_newton_g<16>(a, L, waves, occ, st, done);
   } else {
     hipExtLaunchKernelGGL(k_newton_sturm, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr, done, 0,
                           a, L);
