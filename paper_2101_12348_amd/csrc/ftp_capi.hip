@@ -1221,7 +1221,7 @@ namespace {
 // N_c(j) = sum_a (-1)^(c-a) C(j, a) C(D-j, c-a) (an integer, |N_c(j)| <= C(D, c)),
 // so f_c = Re(i^c sum_j rho_{j-K} N_c(j)) is rho.x (c even) or rho.y (c odd)
 // against N_c, with the sign of i^c's real or imaginary part.  Stored as
-// T[j (D + 1) + c] = s_c N_c(j), s_c = +1 for c = 0, 3 mod 4 and -1 for 1, 2.
+// T[c cayley_row(K) + j] = s_c N_c(j), s_c = +1 for c = 0, 3 mod 4 and -1 for 1, 2.
 // Exact integers up to D = 52; the entries of larger D round to doubles.
 // Only rows j = 0..K (D = 2K) are kept: N_c(D - j) = (-1)^c N_c(j) (a -> c - a
 // in the sum), and rho_{D-j} = conj(rho_j) since R is real, so the terms j and
@@ -1232,8 +1232,8 @@ std::vector<double> cayley_table(int D) {
     C[n][0] = 1;
     for (int k = 1; k <= n; ++k) C[n][k] = C[n - 1][k - 1] + (k <= n - 1 ? C[n - 1][k] : 0);
   }
-  const int K = D / 2;
-  std::vector<double> T((size_t)(K + 1) * (D + 1));
+  const int K = D / 2, LR = cayley_row(K);
+  std::vector<double> T((size_t)(D + 1) * LR, 0.0);
   for (int j = 0; j <= K; ++j)
     for (int c = 0; c <= D; ++c) {
       int64_t acc = 0;
@@ -1243,9 +1243,35 @@ std::vector<double> cayley_table(int D) {
         acc += ((c - a) & 1) ? -t : t;
       }
       const double sgn = (c % 4 == 0 || c % 4 == 3) ? 1.0 : -1.0;
-      T[(size_t)j * (D + 1) + c] = sgn * (double)acc;
+      T[(size_t)c * LR + j] = sgn * (double)acc;
     }
   return T;
+}
+
+// The template's factors of MM's coefficients in assemble_mu's order: row e - 1
+// (e = 1..2H) holds alpha_n alpha_m over n + m = e, then 2 alpha_n conj(alpha_m)
+// over n - m = e, n rising; then |alpha_n|^2, n = 1..H.
+void append_products(std::vector<double>& T, int H, const double2* al) {
+  const size_t o = T.size();
+  T.resize(o + 2 * template_products(H) + 2 * H, 0.0);
+  for (int e = 1; e <= 2 * H; ++e) {
+    int i = 0;
+    auto put = [&](double x, double y) {
+      T[o + 2 * ((size_t)(e - 1) * H + i)] = x;
+      T[o + 2 * ((size_t)(e - 1) * H + i) + 1] = y;
+      ++i;
+    };
+    for (int n = std::max(1, e - H); n <= std::min(e - 1, H); ++n) {
+      const double2 a = al[n - 1], b = al[e - n - 1];
+      put(std::fma(a.x, b.x, -(a.y * b.y)), std::fma(a.y, b.x, a.x * b.y));
+    }
+    for (int n = e + 1; n <= H; ++n) {
+      const double2 a = al[n - 1], b = al[n - e - 1];
+      put(2.0 * std::fma(a.x, b.x, a.y * b.y), 2.0 * std::fma(a.y, b.x, -(a.x * b.y)));
+    }
+  }
+  for (int n = 0; n < H; ++n)
+    T[o + 2 * template_products(H) + n] = std::fma(al[n].x, al[n].x, al[n].y * al[n].y);
 }
 
 // Plan for one template (n_band = 0) or for n_band band templates (c, s of
@@ -1333,6 +1359,7 @@ int plan_create_impl(ftp_plan** out, int n_band, int H, const double* c, const d
   const int D = 6 * H - 2;
   if (D < 64) {
     std::vector<double> ct = cayley_table(D);
+    append_products(ct, H, al.data());
     if ((rc = P->ctab.ensure(sizeof(double) * ct.size()))) {
       delete P;
       return rc;

@@ -39,28 +39,20 @@ __device__ __forceinline__ double rdlane(double v, int src) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// f_c = sum_j rc[j] T[j][c] over the Cayley table's rows j = 0..K (column
-// `col`, row stride D + 1): the table loads of eight rows are issued before
-// their multiply-adds, so their latency is paid once per eight rows; the
-// sums run in the order of a two-accumulator loop (even rows, odd rows).
-__device__ __forceinline__ double cayley_dot(const double* rc, const double* col, int K, int D) {
+// f_c = sum_j rc[j] T[c][j], j = 0..K, over row c of the Cayley table (rows of
+// cayley_row(K) doubles, 16-byte aligned like rc), in two sums, even and odd j.
+__device__ __forceinline__ double cayley_dot(const double* rc, const double* row, int K) {
   double acc0 = 0.0, acc1 = 0.0;
-  int jx = 0;
-  for (; jx + 7 <= K; jx += 8) {
-    double t[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) t[u] = col[(jx + u) * (D + 1)];
-#pragma unroll
-    for (int u = 0; u < 8; u += 2) {
-      acc0 = fma(rc[jx + u], t[u], acc0);
-      acc1 = fma(rc[jx + u + 1], t[u + 1], acc1);
-    }
+  const double2* r2 = reinterpret_cast<const double2*>(rc);
+  const double2* t2 = reinterpret_cast<const double2*>(row);
+  const int n2 = (K + 1) >> 1;
+#pragma unroll 4
+  for (int i = 0; i < n2; ++i) {
+    const double2 r = r2[i], t = t2[i];
+    acc0 = fma(r.x, t.x, acc0);
+    acc1 = fma(r.y, t.y, acc1);
   }
-  for (; jx + 1 <= K; jx += 2) {
-    acc0 = fma(rc[jx], col[jx * (D + 1)], acc0);
-    acc1 = fma(rc[jx + 1], col[(jx + 1) * (D + 1)], acc1);
-  }
-  if (jx <= K) acc0 = fma(rc[jx], col[jx * (D + 1)], acc0);
+  if (!(K & 1)) acc0 = fma(rc[K], row[K], acc0);
   return acc0 + acc1;
 }
 
@@ -98,32 +90,77 @@ __device__ __forceinline__ AsmLayout asm_layout(double* sm, int H, int nb) {
 }
 
 // Compact per-frequency working set of k_assemble2 (single band, D < 64):
-// Z, mu, eta, r, alpha and a scratch of max(8H + 2, K + 1) complex values
-// (assemble_r's MM and YM coefficient rows; later the rotated 2 rho_j).
+// Z, mu, eta, r and a scratch of 8H + 2 complex values (assemble_r's MM and YM
+// coefficient rows; later the rotated 2 rho_j, two rows of cayley_row(K)).
 __host__ __device__ inline int asm2_doubles(int H) {
-  const int K = 3 * H - 1;
-  const int scr = 8 * H + 2 > K + 1 ? 8 * H + 2 : K + 1;
-  return 2 * ((3 * H + 1) + (2 * H + 1) + (H + 1) + (K + 1) + H + scr);
+  return 2 * ((3 * H + 1) + (2 * H + 1) + (H + 1) + 3 * H + (8 * H + 2));
 }
 __device__ __forceinline__ FreqWork asm2_layout(double* sm, int H, double2*& scr) {
-  const int K = 3 * H - 1;
   FreqWork W;
   double2* q = reinterpret_cast<double2*>(sm);
   W.Z = q; q += 3 * H + 1;
   W.mu = q; q += 2 * H + 1;
   W.eta = q; q += H + 1;
-  W.r = q; q += K + 1;
-  W.al = q; q += H;
+  W.r = q; q += 3 * H;
+  W.al = nullptr;
   scr = q;
   return W;
 }
 // Waves per workgroup of k_assemble2: they share one LDS copy of the Cayley
-// table ((K + 1) (D + 1) doubles, 14 KB at H = 10), which the dot products
-// read with LDS latency instead of the L2's.
+// table (14 KB at H = 10) and of the template's products, which the loops read
+// with LDS latency instead of the L2's.
 constexpr int kAsmWaves = 4;
-__host__ __device__ inline size_t asm2_lds_bytes(int H) {
+// Lanes per frequency of k_assemble2: sixteen where 3H and 2H + 1 fit them.
+__host__ __device__ inline constexpr int asm_group(int H) { return H <= 5 ? 16 : 32; }
+__host__ __device__ inline int asm2_table_doubles(int H) {
   const int K = 3 * H - 1, D = 2 * K;
-  return ((size_t)(K + 1) * (D + 1) + (size_t)kAsmWaves * 2 * asm2_doubles(H)) * sizeof(double);
+  return (D + 1) * cayley_row(K) + 2 * template_products(H) + 2 * H;
+}
+__host__ __device__ inline size_t asm2_lds_bytes(int H) {
+  return ((size_t)asm2_table_doubles(H) + (size_t)kAsmWaves * (64 / asm_group(H)) * asm2_doubles(H)) * sizeof(double);
+}
+
+// mu_e, e = 0..2H, of MM from the sums (see assemble_poly), on a group of nl
+// lanes, lane per e.  The pairs (n, m) of e are run in one loop: n + m = e first,
+// then n - m = e (m = |e - n|; conjugating Z_m turns the first form into the
+// second), with the template's factors alpha_n alpha_m and 2 alpha_n conj(alpha_m)
+// from the table `prod` in that order (row e - 1, H entries, zero where e has
+// fewer pairs).  e = 0: s = sum_n |alpha_n|^2 (1 - |Z_n|^2), whose terms the
+// lanes form and lane 0 adds in order (scr: H complex; pn: |alpha_n|^2).
+__device__ __forceinline__ void assemble_mu(const FreqWork& W, int H, int lane, int nl, const double2* prod,
+                                            const double* pn, double2* scr) {
+#pragma clang fp contract(off)
+  for (int n = lane; n < H; n += nl) {
+    const double2 z = W.Z[n + 1];
+    scr[n] = make_double2(pn[n], 1.0 - fma(z.x, z.x, z.y * z.y));
+  }
+  for (int e = lane + 1; e <= 2 * H; e += nl) {
+    const double2 Ze = W.Z[e];
+    const double2* P = prod + (e - 1) * H;
+    const int n0 = e > H ? e - H : 1;
+    double2 acc = make_double2(0.0, 0.0);
+#pragma unroll 2
+    for (int i = 0; i < H; ++i) {
+      int n = n0 + i;
+      n += n >= e ? 1 : 0;
+      const int m = abs(e - n);
+      const double2 a = W.Z[n], zm = W.Z[m], p = P[i];
+      const double by = n > e ? -zm.y : zm.y;
+      const double tx = Ze.x - fma(a.x, zm.x, -(a.y * by));
+      const double ty = Ze.y - fma(a.y, zm.x, a.x * by);
+      acc.x += fma(tx, p.x, ty * p.y);
+      acc.y += fma(tx, p.y, -(ty * p.x));
+    }
+    W.mu[e] = acc;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane == 0) {
+    double t = 0.0;
+#pragma unroll 4
+    for (int n = 0; n < H; ++n) t = fma(scr[n].x, scr[n].y, t);
+    W.mu[0] = make_double2(2.0 * t, 0.0);
+  }
 }
 
 // Shared-phase bands (Appendix A): trig coefficients of MM and YM from the
@@ -300,7 +337,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         // K): f_c = sum_{j<K} 2 rho'_j T[j][c] + rho'_K T[K][c].  Lane j forms
         // 2 rho_{j-K} (rho_0 once), lane c the dot product of column c.
         double* rx = reinterpret_cast<double*>(S.hb[0]);
-        double* ry = rx + (K + 1);
+        double* ry = rx + cayley_row(K);
         {
           const int d = lane - K;
           const double ec = __shfl(tab_c, (d * k0) & 15), es = __shfl(tab_s, (d * k0) & 15);
@@ -314,7 +351,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         wave_sync();
         if (lane <= D) {
           const double* rc = (lane & 1) ? ry : rx;
-          Rr[RL.f + lane] = cayley_dot(rc, a.ctab + lane, K, D);
+          Rr[RL.f + lane] = cayley_dot(rc, a.ctab + lane * cayley_row(K), K);
         }
       } else {
         for (int c = lane; c <= D; c += 64) {
@@ -365,38 +402,84 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   }
 }
 
-// Two frequencies per wavefront (single band, sums from the grids, D < 64):
-// frequencies 2b and 2b + 1 of the chunk on lanes 0..31 and 32..63, each half
-// with its own LDS working set.  The assembly's per-frequency loops have 3H,
-// 2H + 1, K + 1 or 16 lanes of work, which a half-wave holds, so one
-// instruction stream serves two frequencies; the Cayley dot products (D + 1
-// columns) take two rounds of 32.  Maxima and the rotation argmax are reduced
-// per half (row broadcast into lanes 31 and 63).  A pair with status
-// "constant" or from a rejected lightcurve still runs the (cheap) rotation and
-// dot products of its half, whose results are not written.
-template <typename R>
+// Maximum over a group of GL lanes (16 or 32), in every lane of it: of an int,
+// and of a double.
+template <int GL>
+__device__ __forceinline__ int group_max_i(int h, int half) {
+  h = max(h, dpp_i<0xB1, 0xf>(h));
+  h = max(h, dpp_i<0x4E, 0xf>(h));
+  h = max(h, dpp_i<0x141, 0xf>(h));
+  h = max(h, dpp_i<0x140, 0xf>(h));
+  if constexpr (GL == 16) return h;
+  h = max(h, dpp_i<0x142, 0xa>(h));
+  const int lo = __builtin_amdgcn_readlane(h, 31), hi = __builtin_amdgcn_readlane(h, 63);
+  return half ? hi : lo;
+}
+template <int GL>
+__device__ __forceinline__ double group_max_d(double v, int half) {
+  if constexpr (GL == 16) {
+    v = fmax(v, dpp_d<0xB1>(v));
+    v = fmax(v, dpp_d<0x4E>(v));
+    v = fmax(v, dpp_d<0x141>(v));
+    return fmax(v, dpp_d<0x140>(v));
+  } else {
+    double lo, hi;
+    half_max_d(v, lo, hi);
+    return half ? hi : lo;
+  }
+}
+__device__ __forceinline__ int abs2_hi(double2 z) {
+  return (int)((unsigned long long)__double_as_longlong(cabs2(z)) >> 32) & 0x7fffffff;
+}
+
+// Several frequencies per wavefront (single band, sums from the grids, D <
+// 64), one per group of GL lanes with its own LDS working set: two of 32 lanes,
+// or four of 16 where the template has at most five harmonics.  The assembly's
+// per-frequency loops have 3H, 2H + 1, K + 1 or 16 lanes of work, which a group
+// holds (the Cayley dot products, D + 1 columns, take two rounds), so one
+// instruction stream serves all of them; maxima and the rotation argmax are
+// reduced per group.  A pair with status "constant" or from a rejected lightcurve
+// still runs the (cheap) rotation and dot products, whose results are not
+// written.
+//
+// Bound by vector issue (70-90 % of the slots), so the loops are laid out for few
+// instructions: mu's pairs in one loop over the template's tabulated products,
+// rows of the Cayley table contiguous per lane, the rotation's sixteen phases
+// formed once.  Large H = 10 lightcurve (0.5
+// million frequencies) 575 -> 454 us; a batch round at H = 4, sixteen lanes per
+// frequency instead of 32 as well, 3.87 -> 1.75 ms.
+template <typename R, int GL>
 __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_assemble2(SolveArgs a, double* rec,
                                                                                           int64_t p0, int64_t np) {
   extern __shared__ double sma[];
-  const int lane = wave_lane(), half = lane >> 5, hl = lane & 31, wv = threadIdx.x >> 6;
+  constexpr int NG = 64 / GL;
+  const int lane = wave_lane(), half = lane >> 5, g = lane / GL, hl = lane & (GL - 1), wv = threadIdx.x >> 6;
   if (a.clear8 && blockIdx.x == 0 && threadIdx.x < 8) a.clear8[threadIdx.x] = 0u;
   const int H = a.H, K = 3 * H - 1, D = 2 * K;
   const RecLayout RL(H);
-  // the Cayley table, shared by the workgroup's waves
-  double* ctab = sma;
-  const int ntab = (K + 1) * (D + 1);
-  for (int i = threadIdx.x; i < ntab; i += 64 * kAsmWaves) ctab[i] = a.ctab[i];
+  // the Cayley table, the template's products and squares, shared by the
+  // workgroup's waves
+  const int LR = cayley_row(K), ntab = asm2_table_doubles(H);
+  for (int i = threadIdx.x; i < ntab; i += 64 * kAsmWaves) sma[i] = a.ctab[i];
+  const double* ctab = sma;
+  const double2* prod = reinterpret_cast<const double2*>(sma + (D + 1) * LR);
+  const double* pn = sma + (D + 1) * LR + 2 * template_products(H);
   double2* scr;
-  const FreqWork W = asm2_layout(sma + ntab + (2 * wv + half) * asm2_doubles(H), H, scr);
-  for (int q = hl; q < H; q += 32) W.al[q] = a.alpha[q];
+  const FreqWork W = asm2_layout(sma + ntab + (NG * wv + g) * asm2_doubles(H), H, scr);
   __syncthreads();
   double tab_c, tab_s;
   sincos(kTwoPi * (lane & 15) / 16.0, &tab_s, &tab_c);
+  // the rotation's candidate phases (lanes 0..15 of a group)
+  double2 rot;
+  sincos_small(kTwoPi * hl / 16.0 + kPi, rot.y, rot.x);
+  const double2 alk = hl < H ? a.alpha[hl] : make_double2(0.0, 0.0);
+  // MM, YM of order one: the squared threshold of the constant test below
+  const double ctol = 64.0 * kEps * (6.0 * H) * (2.0 * H + 1.0), ctol2 = ctol * ctol;
   const typename Cplx<R>::T* grids = reinterpret_cast<const typename Cplx<R>::T*>(a.grids);
   const int64_t gw = (int64_t)blockIdx.x * kAsmWaves + wv, nw = (int64_t)gridDim.x * kAsmWaves;
-  for (int64_t w0 = 2 * gw; w0 < np; w0 += 2 * nw) {
-    const bool has = w0 + half < np;                    // an empty second half repeats the first
-    const int64_t w = has ? w0 + half : w0;
+  for (int64_t w0 = NG * gw; w0 < np; w0 += NG * nw) {
+    const bool has = w0 + g < np;                    // an empty group repeats the first
+    const int64_t w = has ? w0 + g : w0;
     const int64_t pidx = p0 + w;
     double* Rr = rec + w * (int64_t)RL.stride;
     const int64_t lc = pair_lc(a, pidx);
@@ -404,76 +487,76 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
     const int64_t j = pidx - a.freq_off[lc] + 1;
     const bool bad = L.status != 0;
     if (hl == 0) W.Z[0] = make_double2(1.0, 0.0);
-    for (int q = hl; q < 3 * H; q += 32) {
-      const int g = q < 2 * H ? 0 : 1;
-      const int k = g == 0 ? q + 1 : q - 2 * H + 1;
-      W.Z[q + 1] = bad ? make_double2(0.0, 0.0) : gather_mode<R>(L, g, (int64_t)k * j, grids);
+    for (int q = hl; q < 3 * H; q += GL) {
+      const int gr = q < 2 * H ? 0 : 1;
+      const int k = gr == 0 ? q + 1 : q - 2 * H + 1;
+      W.Z[q + 1] = bad ? make_double2(0.0, 0.0) : gather_mode<R>(L, gr, (int64_t)k * j, grids);
     }
     wave_sync();
-    assemble_poly(W, H, hl, scr, 32);
+    assemble_mu(W, H, hl, GL, prod, pn, scr);
+    if (hl < H) {
+#pragma clang fp contract(off)
+      const double2 z = W.Z[2 * H + 1 + hl];   // eta_k = alpha_k conj(Zy_k)
+      W.eta[hl + 1] = make_double2(fma(alk.x, z.x, alk.y * z.y), fma(alk.y, z.x, -(alk.x * z.y)));
+    }
+    if (hl == 0) W.eta[0] = make_double2(0.0, 0.0);
+    wave_sync();
+    assemble_r(W, H, hl, scr, GL);
     const double ref = ref_cycles(j, L.df, L.tref);
-    double rmax = 0.0, mumax = 0.0, etamax = 0.0;
-    for (int d = hl; d <= K; d += 32) rmax = fmax(rmax, cabs2(W.r[d]));
-    for (int e = hl; e <= 2 * H; e += 32) mumax = fmax(mumax, cabs2(W.mu[e]));
-    for (int k = hl; k <= H; k += 32) etamax = fmax(etamax, cabs2(W.eta[k]));
-    rmax = sqrt(rmax);
-    mumax = sqrt(mumax);
-    etamax = sqrt(etamax);
-    {
-      double lo, hi;
-      half_max_abs_hi(rmax, lo, hi);
-      rmax = half ? hi : lo;
-      half_max_abs_hi(mumax, lo, hi);
-      mumax = half ? hi : lo;
-      half_max_abs_hi(etamax, lo, hi);
-      etamax = half ? hi : lo;
-    }
-    const double rscale = mumax * etamax * (6.0 * H) * (2.0 * H + 1.0);
-    const bool constant = !(rmax > 64.0 * kEps * rscale);
-    // rotation phi0: the 16 candidates of each half on its lanes 0..15
+    // R = 0 against rounding noise: largest squared magnitudes by their high
+    // words (within 2^-20)
+    int rmax = 0, mumax = 0, etamax = 0;
+    for (int d = hl; d <= K; d += GL) rmax = max(rmax, abs2_hi(W.r[d]));
+    for (int e = hl; e <= 2 * H; e += GL) mumax = max(mumax, abs2_hi(W.mu[e]));
+    if (hl <= H) etamax = abs2_hi(W.eta[hl]);
+    rmax = group_max_i<GL>(rmax, half);
+    mumax = group_max_i<GL>(mumax, half);
+    etamax = group_max_i<GL>(etamax, half);
+    auto from_hi = [](int h) { return __longlong_as_double((long long)((unsigned long long)(unsigned)h << 32)); };
+    const bool constant = !(from_hi(rmax) > ctol2 * (from_hi(mumax) * from_hi(etamax)));
+    // rotation phi0: the 16 candidates of each group on its lanes 0..15
     double Rv = -1.0;
-    if (hl < 16) Rv = fabs(eval_R_value(W, H, kTwoPi * hl / 16.0 + kPi));
-    double rm;
-    {
-      double lo, hi;
-      half_max_d(Rv, lo, hi);
-      rm = half ? hi : lo;
+    if (GL == 16 || hl < 16) {
+      double2 q = W.r[K];
+#pragma unroll 4
+      for (int d = K - 1; d >= 1; --d) q = cfma(q, rot, W.r[d]);
+      Rv = fabs(fma(2.0, fma(rot.x, q.x, -(rot.y * q.y)), W.r[0].x));
     }
-    const unsigned long long mask = __ballot(hl < 16 && Rv == rm);
-    const unsigned hm = half ? (unsigned)(mask >> 32) : (unsigned)mask;
+    const double rm = group_max_d<GL>(Rv, half);
+    const unsigned long long mask = __ballot((GL == 16 || hl < 16) && Rv == rm);
+    const unsigned hm = (unsigned)(mask >> (lane & ~(GL - 1))) & 0xffffu;
     const int k0 = hm ? __ffs(hm) - 1 : 0;
     const double phi0 = constant ? 0.0 : kTwoPi * k0 / 16.0;
-    // 2 rho_j = 2 r_{j-K} e^{i (j-K) phi0}, j = 0..K - 1, and rho_K (K + 1 <=
-    // 30 lanes: every lane takes part in the table reads), then the dot
-    // products over the table's rows j <= K (the terms j and D - j are equal)
+    // 2 rho_j = 2 r_{j-K} e^{i (j-K) phi0}, j = 0..K - 1, and rho_K (every lane
+    // takes part in the table reads), then the dot products over j <= K (the
+    // terms j and D - j are equal)
     double* rx = reinterpret_cast<double*>(scr);
-    double* ry = rx + (K + 1);
-    {
-      const int jx = hl, d = jx - K;
+    double* ry = rx + LR;
+    for (int jx = hl; jx < ((K + GL) & ~(GL - 1)); jx += GL) {
+#pragma clang fp contract(off)
+      const int d = jx - K;
       const int m = (d * k0) & 15;
       const double ec = __shfl(tab_c, m), es = __shfl(tab_s, m);
       if (jx <= K) {
-        const double2 rho = cmul(cconj(W.r[-d]), make_double2(ec, es));
+        const double2 rd = W.r[-d];
         const double wgt = jx < K ? 2.0 : 1.0;
-        rx[jx] = wgt * rho.x;
-        ry[jx] = wgt * rho.y;
+        rx[jx] = wgt * fma(rd.x, ec, rd.y * es);
+        ry[jx] = wgt * fma(rd.x, es, -(rd.y * ec));
       }
     }
     wave_sync();
     const bool write = has && !bad;
-    for (int c = hl; c <= D; c += 32) {
-      const double* rc = (c & 1) ? ry : rx;
-      const double fc = cayley_dot(rc, ctab + c, K, D);
+    for (int c = hl; c <= D; c += GL) {
+      const double fc = cayley_dot((c & 1) ? ry : rx, ctab + c * LR, K);
       if (write && !constant) Rr[RL.f + c] = fc;
     }
     if (write) {
-      for (int d = hl; d <= K; d += 32) { Rr[RL.r + 2 * d] = W.r[d].x; Rr[RL.r + 2 * d + 1] = W.r[d].y; }
-      for (int e = hl; e <= 2 * H; e += 32) { Rr[RL.mu + 2 * e] = W.mu[e].x; Rr[RL.mu + 2 * e + 1] = W.mu[e].y; }
-      for (int k = hl; k < H; k += 32) {
-        Rr[RL.eta + 2 * k] = W.eta[k + 1].x;
-        Rr[RL.eta + 2 * k + 1] = W.eta[k + 1].y;
-        Rr[RL.zw + 2 * k] = W.Z[k + 1].x;
-        Rr[RL.zw + 2 * k + 1] = W.Z[k + 1].y;
+      double2* r2 = reinterpret_cast<double2*>(Rr);
+      for (int d = hl; d <= K; d += GL) r2[RL.r / 2 + d] = W.r[d];
+      for (int e = hl; e <= 2 * H; e += GL) r2[RL.mu / 2 + e] = W.mu[e];
+      if (hl < H) {
+        r2[RL.eta / 2 + hl] = W.eta[hl + 1];
+        r2[RL.zw / 2 + hl] = W.Z[hl + 1];
       }
       if (hl == 0) {
         Rr[RL.meta + M_PHI0] = phi0;
@@ -977,14 +1060,18 @@ __global__ void k_export_stats(const LcInfo* lcs, double* out) {
 hipError_t launch_assemble(int precision, const SolveArgs& a, double* rec, int64_t p0, int64_t np, int waves,
                            hipStream_t st) {
   if (a.n_band == 0 && !a.sums_in && 6 * a.H - 2 < 64) {
-    // two frequencies per wavefront, kAsmWaves wavefronts per workgroup
+    // several frequencies per wavefront, kAsmWaves wavefronts per workgroup
     const size_t lds2 = asm2_lds_bytes(a.H);
-    const int64_t w2 = std::max<int64_t>(1, std::min<int64_t>(waves, (np + 1) / 2));
-    const int g2 = (int)((w2 + kAsmWaves - 1) / kAsmWaves);
-    if (precision == 1)
-      hipLaunchKernelGGL(k_assemble2<double>, dim3((unsigned)g2), dim3(64 * kAsmWaves), lds2, st, a, rec, p0, np);
-    else
-      hipLaunchKernelGGL(k_assemble2<float>, dim3((unsigned)g2), dim3(64 * kAsmWaves), lds2, st, a, rec, p0, np);
+    const int per = 64 / asm_group(a.H);
+    const int64_t w2 = std::max<int64_t>(1, std::min<int64_t>(waves, (np + per - 1) / per));
+    const dim3 grid((unsigned)((w2 + kAsmWaves - 1) / kAsmWaves)), block(64 * kAsmWaves);
+    if (precision == 1) {
+      if (per == 4) hipLaunchKernelGGL((k_assemble2<double, 16>), grid, block, lds2, st, a, rec, p0, np);
+      else hipLaunchKernelGGL((k_assemble2<double, 32>), grid, block, lds2, st, a, rec, p0, np);
+    } else {
+      if (per == 4) hipLaunchKernelGGL((k_assemble2<float, 16>), grid, block, lds2, st, a, rec, p0, np);
+      else hipLaunchKernelGGL((k_assemble2<float, 32>), grid, block, lds2, st, a, rec, p0, np);
+    }
     return hipGetLastError();
   }
   const size_t lds = asm_lds_bytes(a.H, a.n_band);

@@ -17,7 +17,8 @@ struct SolveArgs {
   const void* grids;             // float2 or double2 grids
   const double* sums_in;         // optional: per pair 3H complex sums (see gather)
   const double2* alpha;          // template alpha_n, n = 1..H (shared phase: n_band x H, band-major)
-  const double* ctab;            // Cayley-map table, rows j = 0..K of D + 1 doubles, D < 64 (see k_assemble)
+  const double* ctab;            // D < 64: Cayley-map table, rows c = 0..D of cayley_row(K) doubles (see k_assemble),
+                                 // then the template's products (template_products, complex) and |alpha_n|^2, n = 1..H
   int n_band;                    // 0: single band; > 0: shared-phase bands (lcs[0..n_band))
   int newton_cands;              // candidates of M_FALLBACK == 0 pairs are Newton-converged roots
   int H;
@@ -33,6 +34,13 @@ struct SolveArgs {
 };
 
 constexpr double kEps = 2.220446049250313e-16;
+
+// Row length of the Cayley table (K + 1 entries): even, so that rows are 16-byte
+// aligned, and twice an odd number, so that lanes on consecutive rows meet
+// distinct LDS banks.
+__host__ __device__ inline constexpr int cayley_row(int K) { return (((K + 2) / 2) | 1) * 2; }
+// Template products for the coefficients of MM: H per e = 1..2H (assemble_mu).
+__host__ __device__ inline constexpr int template_products(int H) { return 2 * H * H; }
 
 // Shared-memory size (bytes) of one wave's per-frequency working set.  The
 // Cayley-Horner buffers (4 (D+1) complex) alias the companion matrix, which is
@@ -179,21 +187,6 @@ __device__ __forceinline__ double wave_max_abs_hi(double v) {
   h = max(h, dpp_i<0x143, 0xc>(h));
   h = __builtin_amdgcn_readlane(h, 63);
   return __longlong_as_double((long long)((unsigned long long)(unsigned)h << 32));
-}
-
-// Per-half maximum of |v| from the high words (as wave_max_abs_hi): the row
-// stages, then row_bcast:15 into rows 1 and 3 leave the maximum of lanes
-// 0..31 in lane 31 and of lanes 32..63 in lane 63.
-__device__ __forceinline__ void half_max_abs_hi(double v, double& m_lo, double& m_hi) {
-  int h = (int)((unsigned long long)__double_as_longlong(v) >> 32) & 0x7fffffff;
-  h = max(h, dpp_i<0xB1, 0xf>(h));
-  h = max(h, dpp_i<0x4E, 0xf>(h));
-  h = max(h, dpp_i<0x141, 0xf>(h));
-  h = max(h, dpp_i<0x140, 0xf>(h));
-  h = max(h, dpp_i<0x142, 0xa>(h));
-  const int lo = __builtin_amdgcn_readlane(h, 31), hi = __builtin_amdgcn_readlane(h, 63);
-  m_lo = __longlong_as_double((long long)((unsigned long long)(unsigned)lo << 32));
-  m_hi = __longlong_as_double((long long)((unsigned long long)(unsigned)hi << 32));
 }
 
 // Exact per-half maximum of doubles: row stages of wave_max, then
@@ -367,12 +360,22 @@ __device__ __forceinline__ void assemble_r(const FreqWork& W, int H, int lane, d
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); __builtin_amdgcn_wave_barrier();
   for (int d = lane; d <= K; d += nl) {
+#pragma clang fp contract(off)
     double2 acc = make_double2(0.0, 0.0);
     double s = (double)(-3 * H - d);   // 3k - d
-    for (int k = -H; k <= H; ++k, s += 3.0) {
-      const double2 t = cmul(mf[d - k + 2 * H], ef[k + H]);
-      acc.x = fma(s, t.x, acc.x);
-      acc.y = fma(s, t.y, acc.y);
+    const double2* pm = mf + d + 3 * H;
+    const double2* pe = ef;
+    for (int part = 0; part < 2; ++part) {   // k = -H..-1, then 1..H (eta_0 = 0)
+#pragma unroll 2
+      for (int k = 0; k < H; ++k, s += 3.0) {
+        const double2 a = pm[-k], b = pe[k];
+        const double tx = fma(a.x, b.x, -(a.y * b.y)), ty = fma(a.y, b.x, a.x * b.y);
+        acc.x = fma(s, tx, acc.x);
+        acc.y = fma(s, ty, acc.y);
+      }
+      s += 3.0;
+      pm -= H + 1;
+      pe += H + 1;
     }
     W.r[d] = make_double2(-acc.y, acc.x);  // multiply by i
   }

@@ -1,0 +1,34 @@
+"""Several frequencies per wavefront at every harmonic count that takes them (H
+<= 10: sixteen or 32 lanes of the assembly, eight or sixteen of the Sturm
+chain), with the last group full, partly filled and alone: the assembly from
+the grids against the one-frequency assembly from the same sums, and the
+Sturm count against the companion matrix's real eigenvalues."""
+import numpy as np
+import pytest
+
+from synthetic import tiny_case
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H", range(1, 11))
+def test_grouped_assembly_and_counts(H):
+    import paper_2101_12348_amd as F
+
+    for n_f in (1, 2, 3, 5, 17, 31):
+        tmpl, lc = tiny_case(70 + H, n_obs=200, H=H, n_f=n_f, baseline=60.0, cadence="nightly")
+        args = (lc.t, lc.y, lc.sigma, lc.df)
+        plain = F.Plan(tmpl.c, tmpl.s, precision=F.FTP_FP64)
+        uniform = F.Plan(tmpl.c, tmpl.s, precision=F.FTP_FP64, solver=F.FTP_SOLVER_UNIFORM)
+        sums, st = plain.nfft_sums(*args, n_f)
+        tref, ybar, yy, _ = st.cpu().numpy()
+        for plan in (plain, uniform):
+            ref = plan.solve_sums(sums, tref, ybar, yy, lc.df)
+            out = plan.periodogram(*args, n_f)
+            assert np.array_equal(out["status"].cpu().numpy(), ref["status"].cpu().numpy())
+            # the power is stationary at the root: a root error of 1e-5 rad changes it by 1e-10
+            assert np.max(np.abs((out["power"] - ref["power"]).cpu().numpy())) <= 1e-10
+        sturm, real = (x.cpu().numpy() for x in plain.root_counts(sums, tref, ybar, yy, lc.df))
+        trusted = (sturm >= 0) & (real >= 0)
+        assert np.array_equal(sturm[trusted], real[trusted])
+        assert np.all((sturm >= 2) | (sturm <= -1000))
