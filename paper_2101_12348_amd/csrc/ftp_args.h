@@ -15,6 +15,7 @@ struct LearnArgs {
   unsigned int* fb_count;
   unsigned flags;           // bit 0: forced fallback (every pair to the list); bit 1: 2H starts only
   unsigned* queue;          // work counter (zeroed), or nullptr for grid striding
+  const double2* starts;    // H <= 10: evenly spaced starts per rotation (k_start_table)
 };
 
 // Second Newton round over the first round's list (k_newton_retry).

@@ -77,6 +77,7 @@ hipError_t launch_adam(float* w, uint16_t* wb, const float* g, float* m, float* 
 hipError_t launch_f32_to_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t st);
 hipError_t launch_features(double* rec, int H, int64_t np, uint16_t* X, int64_t ldx, int waves, hipStream_t st,
                            const int64_t* list = nullptr, const unsigned* list_count = nullptr);
+hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st);
 hipError_t launch_newton_retry(const RetryArgs& A, int waves, hipStream_t st);
 hipError_t launch_labels(const double* rec, int H, int64_t np, float* roots, int* nroots, int Rmax, int waves,
                          hipStream_t st);
@@ -410,6 +411,7 @@ struct ftp_plan {
   size_t grid_budget = (size_t)8 << 30;   // bytes of NFFT grids per chunk
   // device buffers
   DevBuf alpha, twiddle32, twiddle64, ctab;
+  double2* starts = nullptr;   // in ctab, D < 64 (k_start_table)
   DevBuf pw, py, tile_count, tile_off, cursor, block_sums,
       total, bucket, grids, fft_tab, fft_items, counters, stats_out, rec;
   DevBuf stat_part, stat_ticket;   // statistics kernel: partials per workgroup, ticket per lightcurve
@@ -964,6 +966,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         L.fb_list = B.fb_list;
         L.fb_count = ctr;
         L.flags = ((P->opt.flags & FTP_FLAG_FORCE_FALLBACK) ? 1u : 0u) | ((P->opt.flags & FTP_FLAG_2H_STARTS) ? 2u : 0u);
+        L.starts = P->starts;
         L.queue = nullptr;   // uniform work per pair: grid striding (a queue costs more than it balances)
         // with the side stream, the Newton kernel and the side scoring launch
         // record the fork and join events themselves: the scoring of the
@@ -1360,11 +1363,16 @@ int plan_create_impl(ftp_plan** out, int n_band, int H, const double* c, const d
   if (D < 64) {
     std::vector<double> ct = cayley_table(D);
     append_products(ct, H, al.data());
-    if ((rc = P->ctab.ensure(sizeof(double) * ct.size()))) {
+    // (then the first round's starts: 32 iterates for each of sixteen rotations)
+    const size_t nt_starts = sizeof(double2) * 16 * 32;
+    if ((rc = P->ctab.ensure(sizeof(double) * ct.size() + nt_starts))) {
       delete P;
       return rc;
     }
-    if (hipMemcpy(P->ctab.p, ct.data(), sizeof(double) * ct.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    P->starts = reinterpret_cast<double2*>(P->ctab.as<double>() + ct.size());
+    if (launch_start_table(P->starts, H, (P->opt.flags & FTP_FLAG_2H_STARTS) != 0, nullptr) != hipSuccess ||
+        hipStreamSynchronize(nullptr) != hipSuccess ||
+        hipMemcpy(P->ctab.p, ct.data(), sizeof(double) * ct.size(), hipMemcpyHostToDevice) != hipSuccess) {
       g_last_error = "plan setup copy failed";
       delete P;
       return FTP_E_HIP;

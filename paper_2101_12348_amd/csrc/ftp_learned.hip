@@ -17,12 +17,12 @@
 //   * if they do, the Newton roots are the candidate set; otherwise the
 //     frequency goes to the Aberth iteration (then, if that does not
 //     converge, to the companion-matrix solve) through device work lists.
-// For H <= 10 a wavefront takes four frequencies (k_newton_sturm4): their
-// Sturm sequences run one per 16-lane row with four coefficients per lane in
-// registers, and Newton runs on two of them at a time (32 starts each, at
-// most D).  For H = 11 a wavefront takes one (k_newton_sturm, 4H starts),
-// its Sturm sequence one coefficient per lane (the degree-64 coefficient
-// carried as a scalar; see sturm_begin).
+// For H <= 10 a wavefront takes four frequencies, for H <= 5 eight
+// (k_newton_sturm4): their Sturm sequences run one per group of sixteen or
+// eight lanes with four coefficients per lane in registers, and Newton runs on two
+// of them at a time (32 starts each, at most D).  For H = 11 a wavefront takes one
+// (k_newton_sturm, 4H starts), its Sturm sequence one coefficient per lane (the
+// degree-64 coefficient carried as a scalar; see sturm_begin).
 #include <hip/hip_ext.h>
 #include "ftp_solve_common.h"
 #include "ftp_args.h"
@@ -435,11 +435,11 @@ template <int R>
 __device__ __forceinline__ void sturm_repack(double (&X)[4], int l, int gb4) {
   const int src = gb4 + ((l >> 1) << 2);
   const bool odd = l & 1;
-  double y[R];
 #pragma unroll
-  for (int r = 0; r < R; ++r) y[r] = bperm_d(src, X[r]);
-#pragma unroll
-  for (int r = 0; r < R / 2; ++r) X[r] = odd ? y[r + R / 2] : y[r];
+  for (int r = 0; r < R / 2; ++r) {
+    const double lo = bperm_d(src, X[r]), hi = bperm_d(src, X[r + R / 2]);
+    X[r] = odd ? hi : lo;
+  }
 }
 
 // Distinct real roots of the degree-D polynomial of this lane's group (D even,
@@ -537,24 +537,30 @@ __device__ __forceinline__ void load_coefficients(const double* f, bool on, int 
 // flips.  One Newton step costs a real Horner pass of degree D for f and f'
 // (2D multiply-adds) in place of K complex multiply-adds for R and R' plus a
 // sine and cosine.  cp: coefficients of f (sg > 0) or of g (sg < 0) in
-// ascending order.  Returns the signed step s (theta moves by sg * s, clamped);
-// ok drops on a zero or non-finite step.
-__device__ __forceinline__ double newton_u_step(const double* cp, int D, int K, double& u, int& sg, bool& ok) {
+// ascending order, followed by zeros up to c = newton_top(D): zero leading
+// coefficients change no result, and with them every degree runs the four-step
+// body below without a remainder loop (at H = 4 two of ten steps, whose loads
+// and branches cost more than two whole steps).  Returns the signed step s (theta
+// moves by sg * s, clamped); ok drops on a zero or non-finite step.
+__host__ __device__ inline constexpr int newton_top(int D) { return ((D - 2 + 7) & ~7) + 2; }
+__device__ __forceinline__ double newton_u_step(const double* cp, int DP, int K, double& u, int& sg, bool& ok) {
   // f = E(v) + u O(v), v = u^2 (D even: E has the even powers up to D, O the
   // odd ones up to D - 1), f' = 2u E'(v) + O(v) + 2v O'(v): four independent
   // Horner chains of D/2 steps in place of two of D
   const double v = u * u;
-  double E = cp[D], dE = 0.0, O = cp[D - 1], dO = 0.0;
+  double E = cp[DP], dE = 0.0, O = cp[DP - 1], dO = 0.0;
   // (the new E and O are formed in the loaded coefficients' registers and the
   // derivatives in the old ones', so no step needs a register copy)
-#pragma unroll 4
-  for (int c = D - 2; c >= 2; c -= 2) {
-    const double a = cp[c], b = cp[c - 1];
-    const double nE = fma(E, v, a), nO = fma(O, v, b);
-    dE = fma(dE, v, E);
-    dO = fma(dO, v, O);
-    E = nE;
-    O = nO;
+  for (int c = DP - 2; c >= 8; c -= 8) {
+#pragma unroll
+    for (int i = 0; i < 8; i += 2) {
+      const double a = cp[c - i], b = cp[c - i - 1];
+      const double nE = fma(E, v, a), nO = fma(O, v, b);
+      dE = fma(dE, v, E);
+      dO = fma(dO, v, O);
+      E = nE;
+      O = nO;
+    }
   }
   dE = fma(dE, v, E);
   E = fma(E, v, cp[0]);
@@ -598,42 +604,41 @@ __device__ __forceinline__ void u_from_dir(double c, double s, double& u, int& s
   sg = in ? 1 : -1;
 }
 
-// atan(u) for |u| <= 1.  Two halvings, atan(u) = 2 atan(u / (1 + sqrt(1 +
-// u^2))), bring the argument below tan(pi / 16) < 0.199, where the Taylor
-// series through z^23 leaves a remainder below 2e-17 of the result.
-// (coefficients (-1)^n / (2n + 1), n = 11 .. 1, read through poly_table)
-static __constant__ double kAtanTab[11] = {
-    -1.0 / 23.0, 1.0 / 21.0, -1.0 / 19.0, 1.0 / 17.0, -1.0 / 15.0, 1.0 / 13.0,
-    -1.0 / 11.0, 1.0 / 9.0,  -1.0 / 7.0,  1.0 / 5.0,  -1.0 / 3.0};
-__device__ __forceinline__ double atan_unit(double u) {
-  const const_table T = poly_table((const_table)kAtanTab);
-  double z = u * fast_rcp_d(1.0 + sqrt(fma(u, u, 1.0)));
-  z = z * fast_rcp_d(1.0 + sqrt(fma(z, z, 1.0)));
-  const double z2 = z * z;
-  double p = T[0];
-#pragma unroll
-  for (int i = 1; i < 11; ++i) p = fma(p, z2, T[i]);
-  return 4.0 * fma(p * z2, z, z);
-}
-
-// Phase in [0, 2 pi) of the iterate: phi0 + 2 atan u (sg > 0), phi0 + pi sign(u)
-// - 2 atan u (sg < 0).
-__device__ __forceinline__ double theta_from_u(double phi0, double u, int sg) {
-  const double au = 2.0 * atan_unit(u);
-  double th = sg > 0 ? phi0 + au : phi0 + copysign(kPi, u) - au;
-  th = fma(-floor(th * (1.0 / kTwoPi)), kTwoPi, th);
-  return th >= kTwoPi ? th - kTwoPi : (th < 0.0 ? th + kTwoPi : th);
-}
-
-// Four frequencies per wavefront (H <= 10, D < 64): frequencies 4b .. 4b + 3
-// of the list.  Their four Sturm chains run side by side, one per 16-lane
-// row (sturm_count_groups); then Newton runs on two of them at a time, lanes
+// Four (H = 6..10) or eight (H <= 5) frequencies per wavefront, consecutive ones
+// of the list.  Their Sturm chains run side by side, a group of lanes each
+// (sturm_count_groups); then Newton runs on two of them at a time, lanes
 // 0..31 for the first and 32..63 for the second, each half with min(32, D)
 // starts: the 2H network seeds and min(32, D) - 2H evenly spaced phases (all
-// evenly spaced without network).  The Newton steps are those of R in theta,
-// evaluated on the Cayley polynomial (newton_u_step); converged roots are
-// merged one root per pass, and a half that has reached its count is frozen
-// while the other goes on.
+// evenly spaced without network, tabulated).  The Newton steps are those of R in
+// theta, evaluated on the Cayley polynomial (newton_u_step); converged roots are
+// merged one root of each half per pass, and a half that has reached its count is
+// frozen while the other goes on.
+//
+// Bound by vector issue and the latency of its serial chains (67 % of the
+// slots at six wavefronts per SIMD), so H is a template parameter: strides, loop
+// counts and LDS offsets are immediates, which fits six wavefronts without
+// spills (with H an argument 271 -> 144 MB read and 553 -> 285 MB written at H = 10
+// were spills).  That, the merge of both halves per pass, the tabulated starts
+// and phases left to the scoring: H = 10, 300 thousand frequencies 985 -> 890 us;
+// H = 6, 250 thousand 575 -> 495 us; H = 4, 4.2 million 5.4 -> 4.7 ms.
+// Starts of the first round for each frequency.
+__host__ __device__ inline constexpr int first_starts(int H, bool equal) {
+  return equal ? 2 * H : (6 * H - 2 < 32 ? 6 * H - 2 : 32);
+}
+// Evenly spaced starts of the first round for the sixteen rotations phi0 = 2
+// pi k / 16: entry 32 k + i the iterate (u, sg) of phase (i + 1/2) 2 pi / NS.
+__global__ __launch_bounds__(512) void k_start_table(double2* out, int NS) {
+  const int k = threadIdx.x >> 5, i = threadIdx.x & 31;
+  double s1, c1, u;
+  int sg;
+  const double phi0 = kTwoPi * k / 16.0;
+  double ang = (i + 0.5) * (kTwoPi / NS);
+  asm volatile("" : "+v"(ang));   // rounded before the difference
+  sincos_small(ang - phi0, s1, c1);
+  u_from_dir(c1, s1, u, sg);
+  out[threadIdx.x] = make_double2(u, (double)sg);
+}
+
 struct NewtonAcc {
   int iters;   // this lane's
   unsigned long long roots, fb;
@@ -642,16 +647,15 @@ struct NewtonAcc {
 // Newton on frequencies wA (lanes 0..31) and wA + 1 (lanes 32..63, if hasB)
 // with Sturm counts cA, cB (-2 inactive, -1 untrusted); f of each half and its
 // reversal in fb (LDS, 2 FS doubles per half).
-__device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout& RL, int H, int64_t wA, int cA, int cB,
+template <int H>
+__device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout& RL, int64_t wA, int cA, int cB,
                                             const double* fb, int lane, NewtonAcc& acc) {
   const int half = lane >> 5, hl = lane & 31;
   // starts per frequency: every lane of the half (at most D), or only 2H
   // (flag bit 1: the equal-starts comparison of seeds and evenly spaced phases)
-  const int K = 3 * H - 1, D = 2 * K, S = 2 * H, NS = (L.flags & 2u) ? S : (D < 32 ? D : 32);
-  const int FS = D + 2;
+  constexpr int K = 3 * H - 1, D = 2 * K, S = 2 * H, DP = newton_top(D), FS = DP + 2;
+  const int NS = first_starts(H, L.flags & 2u);
   const unsigned long long lo32 = 0xffffffffull;
-  const unsigned long long hmask = half ? ~lo32 : lo32;
-  const unsigned long long below = (1ull << lane) - 1ull;
   if (cA == -2 && cB == -2) return;
   double* Rh = L.rec + (wA + half) * (int64_t)RL.stride;   // this lane's frequency (unused when inactive)
   const int64_t wh = wA + half;
@@ -662,19 +666,24 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
   bool conv = false, live = cnt >= 0 && hl < NS;
   int its = 0;
   double prev_step = 1.0;
-  if (live) {
+  if (!L.seeds_out) {
+    // evenly spaced phases less phi0: tabulated for the sixteen rotations
+    const int k0 = (int)rint(phi0 * (16.0 / kTwoPi)) & 15;
+    const double2 t = L.starts[32 * k0 + hl];
+    u = t.x;
+    sg = (int)t.y;
+  } else if (live) {
     // start direction relative to phi0: a network seed (its output vector
     // is the root's direction in the canonical frame, rotated here by
     // -(canon + phi0)) or an evenly spaced phase less phi0
-    const bool seeded = L.seeds_out && hl < S;
     double bc = 1.0, bs = 0.0, ang;
-    if (seeded) {
+    if (hl < S) {
       const float* o = L.seeds_out + wh * 2 * S;
       bc = (double)o[2 * hl];
       bs = (double)o[2 * hl + 1];
       ang = -(Rh[RL.meta + M_CANON] + phi0);
     } else {
-      ang = (L.seeds_out ? (hl - S + 0.5) * (kTwoPi / (NS - S)) : (hl + 0.5) * (kTwoPi / NS)) - phi0;
+      ang = (hl - S + 0.5) * (kTwoPi / (NS - S)) - phi0;
     }
     double s1, c1;
     sincos_small(ang, s1, c1);
@@ -686,7 +695,7 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
   for (int it = 1; it <= 12 && !(doneA && doneB); ++it) {
     if (live && !conv) {
       bool ok;
-      const double sc = newton_u_step(sg > 0 ? fbase : fbase + FS, D, K, u, sg, ok);
+      const double sc = newton_u_step(sg > 0 ? fbase : fbase + FS, DP, K, u, sg, ok);
       if (!ok) {
         live = false;
       } else {
@@ -706,21 +715,30 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
       // theta moves by 2 |du| / (1 + u^2) (the cut at theta - phi0 = pi
       // sits where R is largest, far from any root).  Converged lanes no
       // longer move, so each check settles only the lanes converged since
-      // the last: one pass per root, from the lowest pending lane jj, marks
-      // every converged lane of its half within the tolerance of jj; jj is
-      // unique if none of them is lower, and the higher ones (also roots
-      // settled earlier) are not.
+      // the last: one pass takes the lowest pending lane jj of each half and
+      // marks every converged lane of the half within the tolerance of jj; jj
+      // is unique if none of them is lower, and the higher ones (also roots
+      // settled earlier) are not.  (Both halves per pass, the roots
+      // broadcast through LDS: against one half per pass through scalar
+      // registers it takes half the passes and a quarter of the vector
+      // instructions.)
       const double key = sg > 0 ? u : copysign(2.0, u) - u;
+      const double tol = 0.5e-8 * fma(u, u, 1.0);
       for (unsigned long long pend = cm & ~merged; pend;) {
-        const int jj = __builtin_ctzll(pend);
-        const double kj = lrdlane(key, jj), uj = lrdlane(u, jj);
-        const double tol = 0.5e-8 * fma(uj, uj, 1.0);
-        const unsigned long long bit = 1ull << jj;
-        const unsigned long long same = __ballot(fabs(key - kj) < tol) & cm & (jj < 32 ? lo32 : ~lo32);
-        const unsigned long long upto = (bit << 1) - 1ull;   // lanes 0..jj
-        U &= upto | ~same;
-        U = (same & (bit - 1ull)) ? (U & ~bit) : (U | bit);
-        pend &= ~(same | bit);
+        const unsigned pA = (unsigned)pend, pB = (unsigned)(pend >> 32);
+        const unsigned bA = pA & (0u - pA), bB = pB & (0u - pB);   // 0: none pending
+        const int jA = __builtin_ctz(pA | 0x80000000u), jB = __builtin_ctz(pB | 0x80000000u);
+        const int src = (half ? 32 + jB : jA) << 2;
+        const double kj = bperm_d(src, key), tj = bperm_d(src, tol);
+        const unsigned long long sm = __ballot(fabs(key - kj) < tj) & cm;
+        const unsigned sA = bA ? (unsigned)sm : 0u, sB = bB ? (unsigned)(sm >> 32) : 0u;
+        unsigned uA = (unsigned)U, uB = (unsigned)(U >> 32);
+        uA = (uA & ~sA) | (uA & (bA - 1u));   // lanes above jj within the tolerance are not unique
+        uB = (uB & ~sB) | (uB & (bB - 1u));
+        uA = (sA & (bA - 1u)) ? uA & ~bA : uA | bA;
+        uB = (sB & (bB - 1u)) ? uB & ~bB : uB | bB;
+        U = uA | ((unsigned long long)uB << 32);
+        pend &= ~((sA | bA) | ((unsigned long long)(sB | bB) << 32));
       }
       merged = cm;
       um = U;
@@ -730,26 +748,30 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
     }
   }
   acc.iters += its;
-  const double thw = theta_from_u(phi0, u, sg);
   const int nuA = __popcll(um & lo32), nuB = __popcll(um >> 32);
   const bool okA = cA >= 0 && nuA == cA, okB = cB >= 0 && nuB == cB;
   const bool ok = half ? okB : okA;
   const int nu = half ? nuB : nuA;
   double* cand = Rh + RL.cand;
-  // confirmed roots: to the front of the half in lane order (a permutation of
-  // the half's lanes), NaN behind them; one store of the slots the scoring reads
-  const bool uniq = (um >> lane) & 1ull;
-  const int rank = uniq ? __popcll(um & hmask & below) : nu + __popcll(~um & hmask & below);
+  // confirmed roots: their keys to the front of the half in lane order (a
+  // permutation of the half's lanes), NaN behind them; one store of the slots the
+  // scoring reads, which takes the phase only of the winner
+  const unsigned uh = half ? (unsigned)(um >> 32) : (unsigned)um, below = (1u << hl) - 1u;
+  const bool uniq = (uh >> hl) & 1u;
+  const int rank = uniq ? __popc(uh & below) : nu + __popc(~uh & below);
   {
-    const unsigned long long v = (unsigned long long)__double_as_longlong(thw);
+    const unsigned long long v = (unsigned long long)__double_as_longlong(sg > 0 ? u : copysign(2.0, u) - u);
     const int to = (32 * half + rank) << 2;
     const int lo = __builtin_amdgcn_ds_permute(to, (int)(unsigned)(v & 0xffffffffull));
     const int hi = __builtin_amdgcn_ds_permute(to, (int)(unsigned)(v >> 32));
     const double r = __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
     if (cnt != -2 && ok && hl < D) cand[hl] = hl < nu ? r : __longlong_as_double(0x7ff8000000000000ll);
   }
-  // else the distinct roots found, which start the later tiers
-  if (cnt != -2 && !ok && uniq) cand[rank] = thw;
+  // else the phases of the distinct roots found, which start the later tiers
+  if ((cA != -2 && !okA) || (cB != -2 && !okB)) {
+    const double thw = theta_from_u(phi0, u, sg);
+    if (cnt != -2 && !ok && uniq) cand[rank] = thw;
+  }
   if (cnt != -2 && !ok && hl == 0) {
     Rh[RL.meta + M_WARM] = (double)nu;
     Rh[RL.meta + M_COUNT] = (double)cnt;
@@ -762,20 +784,19 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
   lwave_sync();
 }
 
-// OCC: resident wavefronts per SIMD the register allocation is made for (4:
-// up to 128 VGPRs; 5: up to 96, a few spills outside the Newton loop; 6: up
-// to 80, more spills, but more waves to cover the Sturm steps' latency);
-// which is faster depends on the workload and the grid, so the launch shape
-// picks it.
-template <int G, int OCC>
+// OCC: resident wavefronts per SIMD the register allocation is made for (5: up
+// to 96 VGPRs, 6: up to 80, a spill or two at H = 6); which is faster depends on the
+// workload and the grid, so the launch shape picks it (below 5 takes the former).
+template <int H, int OCC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
+  constexpr int D = 6 * H - 2, G = sturm_group(D);
   constexpr int NC = 64 / G;   // frequencies per wavefront
+  constexpr int DP = newton_top(D), FS = DP + 2;   // f and its reversal for each frequency, 16-byte aligned
   const int lane = threadIdx.x & 63, row = lane / G, l = lane & (G - 1);
-  const int H = a.H, D = 6 * H - 2;
-  const int FS = D + 2;   // f and its reversal for each frequency, 16-byte aligned
   const RecLayout RL(H);
   NewtonAcc acc{0, 0, 0};
+  for (int k = D + 1 + l; k <= DP; k += G) sml[2 * FS * row + k] = sml[2 * FS * row + FS + k] = 0.0;
   for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
     // this group's frequency (inactive: past the end, rejected lightcurve, or P
     // constant in theta_2)
@@ -816,7 +837,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
     if (!mine) cnt = -2;
 #pragma unroll 1
     for (int p = 0; p < NC / 2; ++p)
-      newton_pair(L, RL, H, w0 + 2 * p, __builtin_amdgcn_readlane(cnt, 2 * p * G),
+      newton_pair<H>(L, RL, w0 + 2 * p, __builtin_amdgcn_readlane(cnt, 2 * p * G),
                   __builtin_amdgcn_readlane(cnt, (2 * p + 1) * G), sml + 4 * FS * p, lane, acc);
   }
   const unsigned long long iters = (unsigned long long)wave_sum((double)acc.iters);
@@ -835,14 +856,14 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
 // pass as in k_newton_sturm4, with the same stop rule.
 __host__ __device__ inline size_t learn_lds_bytes(int H) {
   const int D = 6 * H - 2;
-  return (size_t)(2 * (D + 2)) * sizeof(double);   // f and its reversal
+  return (size_t)(2 * (newton_top(D) + 2)) * sizeof(double);   // f and its reversal
 }
 
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_newton_sturm(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
   const int lane = threadIdx.x & 63;
   const int H = a.H, K = 3 * H - 1, D = 2 * K, S = 2 * H, NS = 2 * S;
-  const int FS = D + 2;
+  const int DP = newton_top(D), FS = DP + 2;
   const RecLayout RL(H);
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long iters_acc = 0, roots_acc = 0, fb_acc = 0;
@@ -861,10 +882,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       ++fb_acc;
       continue;
     }
-    for (int c = lane; c <= D; c += 64) {
-      const double fc = R[RL.f + c];
+    for (int c = lane; c <= DP; c += 64) {
+      const double fc = c <= D ? R[RL.f + c] : 0.0;
       sml[c] = fc;
-      sml[FS + D - c] = fc;
+      sml[FS + (c <= D ? D - c : c)] = fc;
     }
     const double gv = lane <= D ? R[RL.f + lane] : 0.0;
     const double gv1 = lane + 64 <= D ? R[RL.f + 64 + lane] : 0.0;
@@ -901,7 +922,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     for (int it = 1; it <= 12 && !done; ++it) {
       if (live && !conv) {
         bool ok;
-        const double sc = newton_u_step(sg > 0 ? sml : sml + FS, D, K, u, sg, ok);
+        const double sc = newton_u_step(sg > 0 ? sml : sml + FS, DP, K, u, sg, ok);
         if (!ok) {
           live = false;
         } else {
@@ -1039,7 +1060,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   extern __shared__ double sml[];
   const int lane = threadIdx.x & 63;
   const int H = A.H, K = 3 * H - 1, D = 2 * K, S = 2 * H;
-  const int FS = D + 2;
+  const int DP = newton_top(D), FS = DP + 2;
   const RecLayout RL(H);
   const unsigned long long below = (1ull << lane) - 1ull;
   const int64_t n = (int64_t)*A.count;
@@ -1056,10 +1077,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
       ++left_acc;
       continue;
     }
-    for (int c = lane; c <= D; c += 64) {
-      const double fc = R[RL.f + c];
+    for (int c = lane; c <= DP; c += 64) {
+      const double fc = c <= D ? R[RL.f + c] : 0.0;
       sml[c] = fc;
-      sml[FS + D - c] = fc;
+      sml[FS + (c <= D ? D - c : c)] = fc;
     }
     const int nu0 = (int)R[RL.meta + M_WARM];
     const double phi0 = R[RL.meta + M_PHI0];
@@ -1095,7 +1116,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     for (int it = 1; it <= 12 && !done; ++it) {
       if (live && !conv) {
         bool ok;
-        const double sc = newton_u_step(sg > 0 ? sml : sml + FS, D, K, u, sg, ok);
+        const double sc = newton_u_step(sg > 0 ? sml : sml + FS, DP, K, u, sg, ok);
         if (!ok) {
           live = false;
         } else {
@@ -1156,25 +1177,30 @@ hipError_t launch_newton_retry(const RetryArgs& A, int waves, hipStream_t st) {
 
 bool newton_four_per_wave(int H) { return 6 * H - 2 < 64; }
 
-template <int G>
-static void launch_newton_g(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
-  const size_t lds = (size_t)(64 / G) * 2 * (6 * a.H) * sizeof(double);   // f and its reversal per frequency
+template <int H>
+static void launch_newton_h(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+  constexpr int D = 6 * H - 2, NC = 64 / sturm_group(D);
+  const size_t lds = (size_t)NC * 2 * (newton_top(D) + 2) * sizeof(double);   // f and its reversal per frequency
   const dim3 grid((unsigned)waves), block(64);
-  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<G, 6>), grid, block, lds, st, nullptr, done, 0, a, L);
-  else if (occ == 5) hipExtLaunchKernelGGL((k_newton_sturm4<G, 5>), grid, block, lds, st, nullptr, done, 0, a, L);
-  else hipExtLaunchKernelGGL((k_newton_sturm4<G, 4>), grid, block, lds, st, nullptr, done, 0, a, L);
+  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6>), grid, block, lds, st, nullptr, done, 0, a, L);
+  else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5>), grid, block, lds, st, nullptr, done, 0, a, L);
 }
 
-// `done` (nullable): an event the launch itself records at the kernel's end
-// (no marker packet of its own on the stream); `occ`: 4, 5 or 6 (k_newton_sturm4).
+hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st) {
+  hipLaunchKernelGGL(k_start_table, dim3(1), dim3(512), 0, st, out, first_starts(H, equal));
+  return hipGetLastError();
+}
+
 hipError_t launch_newton_sturm(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st,
                                hipEvent_t done) {
-  if (newton_four_per_wave(a.H)) {
-    if (sturm_group(6 * a.H - 2) == 8) launch_newton_g<8>(a, L, waves, occ, st, done);
-    else launch_newton_g<16>(a, L, waves, occ, st, done);
-  } else {
-    hipExtLaunchKernelGGL(k_newton_sturm, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr, done, 0,
-                          a, L);
+  switch (a.H) {
+#define FTP_NEWTON(h) case h: launch_newton_h<h>(a, L, waves, occ, st, done); break;
+    FTP_NEWTON(1) FTP_NEWTON(2) FTP_NEWTON(3) FTP_NEWTON(4) FTP_NEWTON(5)
+    FTP_NEWTON(6) FTP_NEWTON(7) FTP_NEWTON(8) FTP_NEWTON(9) FTP_NEWTON(10)
+#undef FTP_NEWTON
+    default:
+      hipExtLaunchKernelGGL(k_newton_sturm, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr, done, 0,
+                            a, L);
   }
   return hipGetLastError();
 }

@@ -624,6 +624,8 @@ __device__ __forceinline__ Best select_best2(const double (&P)[2], const double 
 }
 
 __device__ __forceinline__ double wrap_2pi(double x) {
+  // a phase plus a rotation, both in [0, 2 pi): the difference is exact
+  if (x >= 0.0 && x < 2.0 * kTwoPi) return x >= kTwoPi ? x - kTwoPi : x;
   x = fmod(x, kTwoPi);
   if (x < 0.0) x += kTwoPi;
   if (x >= kTwoPi) x -= kTwoPi;
@@ -828,32 +830,17 @@ __device__ __forceinline__ double row_max_d(double v) {
   return v;
 }
 
-// select_best within each 16-lane row over two candidates per lane (slot 0:
-// candidate l, slot 1: candidate 16 + l of the row's frequency); the same
-// rule, and the same winner, as select_best over the row's candidates in
-// index order.  `slot` receives the winner's slot.
-__device__ __forceinline__ Best select_best_row(const double (&P)[2], const double (&th_rel)[2],
-                                                const double (&th_abs)[2], const double (&ym)[2],
-                                                const bool (&valid)[2], int lane, int& slot) {
-  const int row = lane >> 4;
-  const double p0 = valid[0] ? P[0] : -1.0, p1 = valid[1] ? P[1] : -1.0;
-  const double pmax = row_max_d(fmax(p0, p1));
-  const double lo = pmax - 1e-12 * fmax(pmax, 1e-300);
-  const bool n0 = valid[0] && p0 >= lo, n1 = valid[1] && p1 >= lo;
-  const double k0 = n0 ? ((ym[0] > 0.0 ? 0.0 : 8.0) + th_abs[0]) : 1e30;
-  const double k1 = n1 ? ((ym[1] > 0.0 ? 0.0 : 8.0) + th_abs[1]) : 1e30;
-  const double kmin = -row_max_d(-fmin(k0, k1));
-  const unsigned m0 = (unsigned)(__ballot(n0 && k0 == kmin) >> (16 * row)) & 0xffffu;
-  const unsigned m1 = (unsigned)(__ballot(n1 && k1 == kmin) >> (16 * row)) & 0xffffu;
-  slot = m0 ? 0 : (m1 ? 1 : 0);
-  const unsigned m = m0 ? m0 : m1;
-  Best b;
-  b.lane = (m ? __ffs(m) - 1 : 0) + 16 * row;
-  b.P = slot ? __shfl(p1, b.lane) : __shfl(p0, b.lane);
-  b.th_rel = slot ? __shfl(th_rel[1], b.lane) : __shfl(th_rel[0], b.lane);
-  b.th_abs = slot ? __shfl(th_abs[1], b.lane) : __shfl(th_abs[0], b.lane);
-  b.amp_sign = slot ? __shfl(ym[1], b.lane) : __shfl(ym[0], b.lane);
-  return b;
+// e^{i (theta - phi0)} of a root's key (see newton_pair): key = u = tan((theta -
+// phi0) / 2) for |key| <= 1, else sign(u) 2 - u with u its reciprocal.
+__device__ __forceinline__ double2 dir_from_key(double key) {
+  const bool in = fabs(key) <= 1.0;
+  const double u = in ? key : copysign(2.0, key) - key;
+  const double i = fast_rcp_d(fma(u, u, 1.0)), c = fma(-u, u, 1.0) * i;
+  return make_double2(in ? c : -c, 2.0 * u * i);
+}
+__device__ __forceinline__ double theta_from_key(double phi0, double key) {
+  const bool in = fabs(key) <= 1.0;
+  return theta_from_u(phi0, in ? key : copysign(2.0, key) - key, in ? 1 : -1);
 }
 
 // Scoring of the first round's Newton-root pairs (M_FALLBACK = 0), four
@@ -862,134 +849,201 @@ __device__ __forceinline__ Best select_best_row(const double (&P)[2], const doub
 // of a row take a second evaluation only when some row of the wavefront has
 // more than 16 roots (a frequency has ~12 real roots at H = 10).  The
 // candidates, tie rule and outputs of k_score, without the polish (the roots
-// are Newton-converged).
+// are Newton-converged).  The roots come as keys: e^{i theta} of a candidate is
+// rational in its key, and only winners need their phase (near ties, which
+// the smallest phase decides, form all of them).
 //
-// The record fields a row's lanes read (meta; mu_e, e = l, l + 16 <= 2H;
-// eta_k and Z_w k, k = l < H; candidates l, l + 16) are loaded one iteration
-// ahead, so that their latency overlaps the scoring of the current four pairs
-// (2H + 1 <= 31 and H <= 15: two, one, one and two per lane cover them).
+// A wavefront takes `per` consecutive frequencies (4..64, a multiple of 4).
+// Their winners wait in LDS and are finished together, a lane each: phase,
+// amplitude and the stores, which are contiguous.  The record fields a row's
+// lanes read (meta; mu_e, e = l, l + 16; eta_k and Z_w k, k = l + 1;
+// candidates l, l + 16) are loaded one iteration ahead.
+//
+// Bound by vector issue and LDS latency: H is a template parameter so that
+// the Horner chains unroll with their loads ahead of them.  Against one kernel
+// for all H that formed every candidate's phase by a sine and cosine and finished
+// each frequency by itself, with spills: large H = 10 (300 thousand frequencies)
+// 168 -> 98 us alone, batch round at H = 4 (4.2 million) 1.25 -> 0.71 ms.  Three
+// wavefronts per SIMD from H = 8 (their chains' loads would spill at four).
 struct Score4Fetch {
-  double st, fb, lc, ref, c0, c1;
-  double2 mu0, mu1, eta, zw;
+  double st, fb, lc, ref, phi0, c0, c1;
+  double mu0[2], mu1[2], eta[2], zw[2];
 };
 
-__device__ __forceinline__ void score4_fetch(const double* rec, const RecLayout& RL, int H, int ncand, int64_t np,
-                                             int64_t w0, int row, int l, Score4Fetch& F) {
+template <int H>
+__device__ __forceinline__ void score4_fetch(const double* rec, int64_t np, int64_t w0, int row, int l, Score4Fetch& F) {
+  constexpr int D = 6 * H - 2, NC = D < 32 ? D : 32;   // NC: the first round's starts per frequency
+  const RecLayout RL(H);
   const bool has = w0 + row < np;
   const double* Rr = rec + (has ? w0 + row : w0) * (int64_t)RL.stride;
-  const double2 z = make_double2(0.0, 0.0);
   const double qnan = __longlong_as_double(0x7ff8000000000000ll);
   F.st = Rr[RL.meta + M_STATUS];
   F.fb = has ? Rr[RL.meta + M_FALLBACK] : 1.0;   // past the end: scored, never written
   F.lc = Rr[RL.meta + M_LC];
   F.ref = Rr[RL.meta + M_REF];
+  F.phi0 = Rr[RL.meta + M_PHI0];
   const double2* mu = reinterpret_cast<const double2*>(Rr + RL.mu);
-  F.mu0 = l <= 2 * H ? mu[l] : z;
-  F.mu1 = l + 16 <= 2 * H ? mu[l + 16] : z;
-  F.eta = l < H ? reinterpret_cast<const double2*>(Rr + RL.eta)[l] : z;
-  F.zw = l < H ? reinterpret_cast<const double2*>(Rr + RL.zw)[l] : z;
-  F.c0 = l < ncand ? Rr[RL.cand + l] : qnan;
-  F.c1 = l + 16 < ncand ? Rr[RL.cand + l + 16] : qnan;
+  const int lh = l < H ? l : H - 1;
+  auto get = [](double (&d)[2], const double2* p) {
+    const double2 v = *p;
+    d[0] = v.x;
+    d[1] = v.y;
+  };
+  get(F.mu0, mu + (l < 2 * H ? l : 2 * H));
+  if constexpr (2 * H >= 16) get(F.mu1, mu + (l + 16 < 2 * H ? l + 16 : 2 * H));
+  get(F.eta, reinterpret_cast<const double2*>(Rr + RL.eta) + lh);
+  get(F.zw, reinterpret_cast<const double2*>(Rr + RL.zw) + lh);
+  F.c0 = Rr[RL.cand + (l < NC ? l : NC - 1)];
+  F.c1 = qnan;
+  if (l >= NC) F.c0 = qnan;
+  if (NC > 16) {
+    F.c1 = Rr[RL.cand + (l + 16 < NC ? l + 16 : NC - 1)];
+    if (l + 16 >= NC) F.c1 = qnan;
+  }
 }
 
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_score4(SolveArgs a, const double* rec,
-                                                                                       int64_t p0, int64_t np) {
+constexpr int kScorePer = 64;   // frequencies a wavefront takes at most
+// LDS of k_score4: per row MM's, YM's and Mbar's coefficients (4H + 1 complex: an
+// odd count, so that the rows' broadcasts meet distinct banks), then the winners.
+__host__ __device__ inline size_t score4_lds_bytes(int H) {
+  return (size_t)(4 * 2 * (4 * H + 1) + 7 * kScorePer) * sizeof(double) + kScorePer * sizeof(int);
+}
+
+template <int H>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(H >= 8 ? 3 : 4))) void k_score4(SolveArgs a, const double* rec,
+                                                                                       int64_t p0, int64_t np, int per) {
   extern __shared__ double sms[];
   const int lane = wave_lane(), row = lane >> 4, l = lane & 15;
-  const int H = a.H, K = 3 * H - 1, D = 2 * K;
-  const RecLayout RL(H);
-  FreqWork W;
+  double2* mu = reinterpret_cast<double2*>(sms) + row * (4 * H + 1);
+  double2* eta = mu + 2 * H;    // eta[k], k = 1..H
+  double2* zb = eta + H;        // zb[k] = alpha_k conj(Z_k), k = 1..H
+  double* fin = sms + 4 * 2 * (4 * H + 1);
+  int* fcode = reinterpret_cast<int*>(fin + 7 * kScorePer);
+  const double2 alk = l < H && !a.n_band ? a.alpha[l] : make_double2(1.0, 0.0);
+  double floor_mm;
   {
-    double2* q = reinterpret_cast<double2*>(sms + row * (score_lds_bytes(H) / sizeof(double)));
-    W.Z = q; q += 3 * H + 1;
-    W.mu = q; q += 2 * H + 1;
-    W.eta = q; q += H + 1;
-    W.r = q; q += K + 1;
-    W.al = q;
+    double s = 0.0;
+    if (!a.n_band)
+      for (int n = 0; n < H; ++n) s += cabs2(a.alpha[n]);
+    floor_mm = a.n_band ? a.mm_tau * a.lcs[0].mm_scale : a.mm_tau * s;
   }
-  for (int q = l; q < H; q += 16) W.al[q] = a.n_band ? make_double2(1.0, 0.0) : a.alpha[q];
-  wave_sync();
-  const double floor_mm = a.n_band ? a.mm_tau * a.lcs[0].mm_scale : mm_floor(W, H, a.mm_tau);
   const bool pos = (a.flags & kFlagPositiveAmp) != 0u;
-  const int ncand = D < 32 ? D : 32;   // the first round's starts per frequency
-  const int64_t step = 4 * (int64_t)gridDim.x;
+  double tab_c, tab_s;
+  sincos(kTwoPi * l / 16.0, &tab_s, &tab_c);
+  const int64_t wb = (int64_t)blockIdx.x * per, we = wb + per < np ? wb + per : np;
   Score4Fetch F;
-  int64_t w0 = 4 * (int64_t)blockIdx.x;
-  if (w0 < np) score4_fetch(rec, RL, H, ncand, np, w0, row, l, F);
-  for (; w0 < np; w0 += step) {
+  score4_fetch<H>(rec, we, wb, row, l, F);
+  for (int64_t w0 = wb; w0 < we; w0 += 4) {
     // this iteration's fields into LDS and registers, then the next
     // iteration's loads
-    const int64_t pidx = p0 + (w0 + row < np ? w0 + row : w0);
     const int st = (int)F.st;
     const bool mine = F.fb == 0.0;
-    const int64_t lc = (int64_t)F.lc;
-    const double ref = F.ref;
-    if (l <= 2 * H) W.mu[l] = F.mu0;
-    if (l + 16 <= 2 * H) W.mu[l + 16] = F.mu1;
+    const double lc = F.lc, ref = F.ref, phi0 = F.phi0;
+    if (l <= 2 * H) mu[l] = make_double2(F.mu0[0], F.mu0[1]);
+    if constexpr (2 * H >= 16) {
+      if (l + 16 <= 2 * H) mu[l + 16] = make_double2(F.mu1[0], F.mu1[1]);
+    }
     if (l < H) {
-      W.eta[l + 1] = F.eta;
-      W.Z[l + 1] = cconj(cmul(W.al[l], cconj(F.zw)));
+      eta[l + 1] = make_double2(F.eta[0], F.eta[1]);
+      zb[l + 1] = cmul(alk, make_double2(F.zw[0], -F.zw[1]));
     }
-    if (l == 0) W.eta[0] = make_double2(0.0, 0.0);
-    double th[2] = {0.0, 0.0};
-    bool valid[2] = {false, false};
-    if (st == ST_CONSTANT) {
-      th[0] = -kTwoPi * ref;
-      valid[0] = l == 0;
-    } else if (st != ST_BAD_LC) {
-      th[0] = F.c0;
-      th[1] = F.c1;
-#pragma unroll
-      for (int sl = 0; sl < 2; ++sl) {
-        valid[sl] = !isnan(th[sl]);
-        if (!valid[sl]) th[sl] = 0.0;
-      }
-    }
-    if (w0 + step < np) score4_fetch(rec, RL, H, ncand, np, w0 + step, row, l, F);
+    const double k0v = F.c0, k1v = F.c1;
+    const bool roots = st != ST_CONSTANT && st != ST_BAD_LC;
+    const bool valid0 = roots ? !isnan(k0v) : st == ST_CONSTANT && l == 0, valid1 = roots && !isnan(k1v);
+    if (w0 + 4 < we) score4_fetch<H>(rec, we, w0 + 4, row, l, F);
     wave_sync();
     // (the evaluation reads mu, eta and Z: the Newton roots take no polish on R)
-    const bool second = __ballot(valid[1]) != 0ull;   // wave-uniform
-    Cand c[2];
-    c[1] = Cand{0.0, 0.0, 0.0, 0.0};
+    const bool second = __ballot(valid1) != 0ull;   // wave-uniform
+    const int kr = (int)rint(phi0 * (16.0 / kTwoPi)) & 15;
+    const double rc = __shfl(tab_c, kr), rs = __shfl(tab_s, kr);
+    // P does not depend on the phase: theta_2 = 0 (absolute) is scored
+    const double th_const = -kTwoPi * ref;
+    const bool any_const = __ballot(st == ST_CONSTANT) != 0ull;
+    Cand c0 = Cand{0.0, 0.0, 0.0, 0.0}, c1 = c0;
 #pragma unroll 1
-    for (int sl = 0; sl < (second ? 2 : 1); ++sl) {
-      const Cand t = eval_candidate(W, H, sl ? th[1] : th[0]);
-      if (sl) c[1] = t; else c[0] = t;
-    }
-    const double mmmax = row_max_d(fmax(valid[0] ? c[0].MM : -1.0, valid[1] ? c[1].MM : -1.0));
-    int stout = st;
-    if (st != ST_BAD_LC && mmmax <= floor_mm) stout = ST_DEGENERATE;
-    bool ok[2];
+    for (int sl = second ? 1 : 0; sl >= 0; --sl) {
+      const bool v = (sl ? valid1 : valid0) && roots;
+      const double2 d = dir_from_key(v ? (sl ? k1v : k0v) : 0.0);
+      double2 psi = make_double2(fma(d.x, rc, -(d.y * rs)), fma(d.x, rs, d.y * rc));
+      if (any_const && st == ST_CONSTANT) sincos_small(th_const, psi.y, psi.x);
+      c1 = c0;
+      double2 m = mu[2 * H];
 #pragma unroll
-    for (int sl = 0; sl < 2; ++sl)
-      ok[sl] = valid[sl] && (c[sl].MM > floor_mm || stout == ST_DEGENERATE) && (!pos || c[sl].YM > 0.0);
-    const unsigned okm = (unsigned)(__ballot(ok[0] || ok[1]) >> (16 * row)) & 0xffffu;
-    const bool none = pos && stout != ST_DEGENERATE && okm == 0u;
-    const double P2[2] = {c[0].P, c[1].P}, ym2[2] = {c[0].YM, c[1].YM};
-    const double ta2[2] = {wrap_2pi(th[0] + kTwoPi * ref), wrap_2pi(th[1] + kTwoPi * ref)};
-    int bslot;
-    const Best b = select_best_row(P2, th, ta2, ym2, ok, lane, bslot);
-    Cand cb = {__shfl(c[0].P, b.lane), __shfl(c[0].YM, b.lane), __shfl(c[0].MM, b.lane), __shfl(c[0].Mbar, b.lane)};
-    if (bslot) cb = Cand{__shfl(c[1].P, b.lane), __shfl(c[1].YM, b.lane), __shfl(c[1].MM, b.lane), __shfl(c[1].Mbar, b.lane)};
-    if (l == 0 && mine) {
-      if (st == ST_BAD_LC) {
-        a.power[pidx] = 0.0; a.phase[pidx] = 0.0; a.amp[pidx] = 0.0; a.offset[pidx] = 0.0;
-        if (a.status) a.status[pidx] = ST_BAD_LC;
-      } else {
-        const LcInfo& L = a.lcs[lc];
-        const double sq = sqrt(L.yy);
-        double P = cb.P, amp = cb.MM > 0.0 ? cb.YM / cb.MM * sq : 0.0;
-        double off = L.ybar - cb.Mbar * amp;
-        double th_abs = wrap_2pi(b.th_rel + kTwoPi * ref);
-        if (stout == ST_DEGENERATE || none) { P = 0.0; amp = 0.0; off = L.ybar; th_abs = 0.0; }
-        a.power[pidx] = P;
-        a.phase[pidx] = th_abs;
-        a.amp[pidx] = amp;
-        a.offset[pidx] = off;
-        if (a.status) a.status[pidx] = (uint8_t)stout;
+      for (int k = 2 * H - 1; k >= 1; --k) m = cfma(m, psi, mu[k]);
+      double2 y = eta[H], b = zb[H];
+#pragma unroll
+      for (int k = H - 1; k >= 1; --k) {
+        y = cfma(y, psi, eta[k]);
+        b = cfma(b, psi, zb[k]);
       }
+      // the sums above stop at psi^1: one more factor psi
+      c0.MM = fma(2.0, m.x * psi.x - m.y * psi.y, mu[0].x);
+      c0.YM = 2.0 * (y.x * psi.x - y.y * psi.y);
+      c0.Mbar = 2.0 * (b.x * psi.x - b.y * psi.y);
+      c0.P = c0.MM > 0.0 ? c0.YM * c0.YM / c0.MM : 0.0;
+    }
+    auto row_bits = [&](bool x) { return (unsigned)(__ballot(x) >> (16 * row)) & 0xffffu; };
+    const bool above0 = valid0 && c0.MM > floor_mm, above1 = valid1 && c1.MM > floor_mm;
+    int stout = st;
+    if (st != ST_BAD_LC && row_bits(above0 || above1) == 0u) stout = ST_DEGENERATE;
+    const bool degen = stout == ST_DEGENERATE;
+    const bool ok0 = valid0 && (above0 || degen) && (!pos || c0.YM > 0.0);
+    const bool ok1 = valid1 && (above1 || degen) && (!pos || c1.YM > 0.0);
+    const bool none = pos && !degen && row_bits(ok0 || ok1) == 0u;
+    // the winner of each row, as select_best over its candidates in index order
+    const double v0 = ok0 ? c0.P : -1.0, v1 = ok1 ? c1.P : -1.0;
+    const double pmax = row_max_d(fmax(v0, v1));
+    const double lo = pmax - 1e-12 * fmax(pmax, 1e-300);
+    unsigned m0 = row_bits(ok0 && v0 >= lo), m1 = row_bits(ok1 && v1 >= lo);
+    if (__ballot(__popc(m0) + __popc(m1) > 1)) {
+      double kmin = 1e30, kk0 = 1e30, kk1 = 1e30;
+#pragma unroll 1
+      for (int sl = 0; sl < 2; ++sl) {
+        const double t = roots ? theta_from_key(phi0, sl ? (valid1 ? k1v : 0.0) : (valid0 ? k0v : 0.0)) : th_const;
+        const double kv = ((sl ? c1.YM : c0.YM) > 0.0 ? 0.0 : 8.0) + wrap_2pi(t + kTwoPi * ref);
+        if (sl) kk1 = ((m1 >> l) & 1u) ? kv : 1e30;
+        else kk0 = ((m0 >> l) & 1u) ? kv : 1e30;
+      }
+      kmin = -row_max_d(-fmin(kk0, kk1));
+      m0 = row_bits(((m0 >> l) & 1u) && kk0 == kmin);
+      m1 = row_bits(((m1 >> l) & 1u) && kk1 == kmin);
+    }
+    const unsigned mb = m0 ? m0 : m1;
+    const int bl = mb ? __ffs(mb) - 1 : 0;
+    if (l == bl) {
+      const bool s1 = m0 == 0u && m1 != 0u;
+      const int i = (int)(w0 - wb) + row;
+      fin[i] = s1 ? c1.P : c0.P;
+      fin[kScorePer + i] = s1 ? c1.YM : c0.YM;
+      fin[2 * kScorePer + i] = s1 ? c1.MM : c0.MM;
+      fin[3 * kScorePer + i] = s1 ? c1.Mbar : c0.Mbar;
+      fin[4 * kScorePer + i] = s1 ? k1v : k0v;
+      fin[5 * kScorePer + i] = ref;
+      fin[6 * kScorePer + i] = lc;
+      fcode[i] = stout | (none ? 256 : 0) | (mine ? 512 : 0) | (roots ? 1024 : 0) | (kr << 12);
     }
     wave_sync();
+  }
+  if (lane < (int)(we - wb)) {
+    const int code = fcode[lane], stout = code & 255;
+    if (!(code & 512)) return;
+    const int64_t pidx = p0 + wb + lane;
+    if (stout == ST_BAD_LC) {
+      a.power[pidx] = 0.0; a.phase[pidx] = 0.0; a.amp[pidx] = 0.0; a.offset[pidx] = 0.0;
+    } else {
+      const LcInfo& L = a.lcs[(int64_t)fin[6 * kScorePer + lane]];
+      const double YM = fin[kScorePer + lane], MM = fin[2 * kScorePer + lane], ref = fin[5 * kScorePer + lane];
+      const double th = (code & 1024) ? theta_from_key(kTwoPi * (code >> 12) / 16.0, fin[4 * kScorePer + lane]) : -kTwoPi * ref;
+      double P = fin[lane], amp = MM > 0.0 ? YM / MM * sqrt(L.yy) : 0.0;
+      double off = L.ybar - fin[3 * kScorePer + lane] * amp;
+      double th_abs = wrap_2pi(th + kTwoPi * ref);
+      if (stout == ST_DEGENERATE || (code & 256)) { P = 0.0; amp = 0.0; off = L.ybar; th_abs = 0.0; }
+      a.power[pidx] = P;
+      a.phase[pidx] = th_abs;
+      a.amp[pidx] = amp;
+      a.offset[pidx] = off;
+    }
+    if (a.status) a.status[pidx] = (uint8_t)stout;
   }
 }
 
@@ -1093,18 +1147,25 @@ hipError_t launch_score(const SolveArgs& a, const double* rec, int64_t p0, int64
   return hipGetLastError();
 }
 
-// Newton-candidate pairs four per wavefront (see k_score4); `done` (nullable):
-// an event the launch itself records at the kernel's end.
+// Newton-candidate pairs four per wavefront (see k_score4, H <= 10); `done`
+// (nullable): an event the launch itself records at the kernel's end.
 hipError_t launch_score_newton(const SolveArgs& a, const double* rec, int64_t p0, int64_t np, int waves, hipStream_t st,
                          hipEvent_t done) {
-  {
-    // the first round's roots (at most 32 per frequency) in two rounds of a
-    // 16-lane row: four frequencies per wavefront
-    const int w4 = (int)std::max<int64_t>(1, std::min<int64_t>(waves, (np + 3) / 4));
-    hipExtLaunchKernelGGL(k_score4, dim3((unsigned)w4), dim3(64), 4 * score_lds_bytes(a.H), st, nullptr, done, 0, a,
-                          rec, p0, np);
-    return hipGetLastError();
+  // consecutive frequencies per wavefront: more amortise the finish, fewer fill
+  // the chip (twice over at four wavefronts per SIMD)
+  const int w = std::max(1, std::min(waves, 8192));
+  const int64_t want = (np + w - 1) / w;
+  const int per = (int)std::min<int64_t>(kScorePer, std::max<int64_t>(4, (want + 3) & ~(int64_t)3));
+  const dim3 grid((unsigned)((np + per - 1) / per));
+  const size_t lds = score4_lds_bytes(a.H);
+  switch (a.H) {
+#define FTP_SCORE4(h) case h: hipExtLaunchKernelGGL((k_score4<h>), grid, dim3(64), lds, st, nullptr, done, 0, a, rec, p0, np, per); break;
+    FTP_SCORE4(1) FTP_SCORE4(2) FTP_SCORE4(3) FTP_SCORE4(4) FTP_SCORE4(5)
+    FTP_SCORE4(6) FTP_SCORE4(7) FTP_SCORE4(8) FTP_SCORE4(9) FTP_SCORE4(10)
+#undef FTP_SCORE4
+    default: return hipErrorInvalidValue;
   }
+  return hipGetLastError();
 }
 
 hipError_t launch_gather_sums(int precision, const SolveArgs& a, double* out, int blocks, hipStream_t st) {

@@ -527,6 +527,33 @@ __device__ __forceinline__ void sincos_small(double x, double& s, double& c) {
   c = ((q + 1) & 2) ? -cc : cc;
 }
 
+// atan(u) for |u| <= 1.  Two halvings, atan(u) = 2 atan(u / (1 + sqrt(1 +
+// u^2))), bring the argument below tan(pi / 16) < 0.199, where the Taylor
+// series through z^23 leaves a remainder below 2e-17 of the result.
+// (coefficients (-1)^n / (2n + 1), n = 11 .. 1, read through poly_table)
+static __constant__ double kAtanTab[11] = {
+    -1.0 / 23.0, 1.0 / 21.0, -1.0 / 19.0, 1.0 / 17.0, -1.0 / 15.0, 1.0 / 13.0,
+    -1.0 / 11.0, 1.0 / 9.0,  -1.0 / 7.0,  1.0 / 5.0,  -1.0 / 3.0};
+__device__ __forceinline__ double atan_unit(double u) {
+  const const_table T = poly_table((const_table)kAtanTab);
+  double z = u * fast_rcp_d(1.0 + sqrt(fma(u, u, 1.0)));
+  z = z * fast_rcp_d(1.0 + sqrt(fma(z, z, 1.0)));
+  const double z2 = z * z;
+  double p = T[0];
+#pragma unroll
+  for (int i = 1; i < 11; ++i) p = fma(p, z2, T[i]);
+  return 4.0 * fma(p * z2, z, z);
+}
+
+// Phase in [0, 2 pi) of the iterate: phi0 + 2 atan u (sg > 0), phi0 + pi sign(u)
+// - 2 atan u (sg < 0).
+__device__ __forceinline__ double theta_from_u(double phi0, double u, int sg) {
+  const double au = 2.0 * atan_unit(u);
+  double th = sg > 0 ? phi0 + au : phi0 + copysign(kPi, u) - au;
+  th = fma(-floor(th * (1.0 / kTwoPi)), kTwoPi, th);
+  return th >= kTwoPi ? th - kTwoPi : (th < 0.0 ? th + kTwoPi : th);
+}
+
 // psi b + c (complex multiply-add, four FMAs)
 __device__ __forceinline__ double2 cfma(double2 b, double2 psi, double2 c) {
   return make_double2(fma(b.x, psi.x, fma(-b.y, psi.y, c.x)), fma(b.x, psi.y, fma(b.y, psi.x, c.y)));
@@ -537,10 +564,7 @@ __device__ __forceinline__ double2 cfma(double2 b, double2 psi, double2 c) {
 // Mbar = 2 Re sum_{k=1}^{H} conj(W.Z[k]) psi^k, where W.Z[k] must hold the
 // conjugated psi^k coefficient of Mbar, conj(alpha_k conj(Z_k)) (the scoring
 // kernel converts the sums before calling).
-__device__ __forceinline__ Cand eval_candidate(const FreqWork& W, int H, double theta) {
-  double sn, cs;
-  sincos_small(theta, sn, cs);
-  const double2 psi = make_double2(cs, sn);
+__device__ __forceinline__ Cand eval_candidate_psi(const FreqWork& W, int H, double2 psi) {
   double2 m = W.mu[2 * H];
   for (int k = 2 * H - 1; k >= 1; --k) m = cfma(m, psi, W.mu[k]);
   double2 y = W.eta[H], b = cconj(W.Z[H]);
@@ -557,6 +581,11 @@ __device__ __forceinline__ Cand eval_candidate(const FreqWork& W, int H, double 
   c.Mbar = 2.0 * (b.x * psi.x - b.y * psi.y);
   c.P = MM > 0.0 ? YM * YM / MM : 0.0;
   return c;
+}
+__device__ __forceinline__ Cand eval_candidate(const FreqWork& W, int H, double theta) {
+  double sn, cs;
+  sincos_small(theta, sn, cs);
+  return eval_candidate_psi(W, H, make_double2(cs, sn));
 }
 
 // R(theta) alone (Horner in psi).

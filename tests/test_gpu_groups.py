@@ -32,3 +32,23 @@ def test_grouped_assembly_and_counts(H):
         trusted = (sturm >= 0) & (real >= 0)
         assert np.array_equal(sturm[trusted], real[trusted])
         assert np.all((sturm >= 2) | (sturm <= -1000))
+
+
+@pytest.mark.parametrize("H", [2, 3, 6, 10])
+def test_tied_roots_take_the_smallest_phase(H):
+    import paper_2101_12348_amd as F
+
+    # a template of even harmonics only has period pi: every maximum of the
+    # power comes twice, and the candidate of smaller phase is the answer
+    n_f = 67
+    tmpl, lc = tiny_case(90 + H, n_obs=200, H=H, n_f=n_f, baseline=60.0, cadence="nightly")
+    c, s = np.array(tmpl.c), np.array(tmpl.s)
+    c[0::2] = s[0::2] = 0.0
+    args = (lc.t, lc.y, lc.sigma, lc.df)
+    outs = [{k: v.cpu().numpy() for k, v in
+             F.Plan(c, s, precision=F.FTP_FP64, solver=solver).periodogram(*args, n_f).items()}
+            for solver in (F.FTP_SOLVER_PLAIN, F.FTP_SOLVER_UNIFORM)]
+    # stationary power: a root error of 1e-5 rad changes it by 1e-10; the phase by that error
+    assert np.max(np.abs(outs[0]["power"] - outs[1]["power"])) <= 1e-10
+    d = np.abs(outs[0]["phase"] - outs[1]["phase"])
+    assert np.max(np.minimum(d, 2.0 * np.pi - d)) <= 1e-5
