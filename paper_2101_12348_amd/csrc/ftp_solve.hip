@@ -116,8 +116,16 @@ __host__ __device__ inline int asm2_table_doubles(int H) {
   const int K = 3 * H - 1, D = 2 * K;
   return (D + 1) * cayley_row(K) + 2 * template_products(H) + 2 * H;
 }
-__host__ __device__ inline size_t asm2_lds_bytes(int H) {
-  return ((size_t)asm2_table_doubles(H) + (size_t)kAsmWaves * (64 / asm_group(H)) * asm2_doubles(H)) * sizeof(double);
+// nb > 0 (shared-phase bands): the Cayley table, then per band the 2H + 1
+// template products, the template and the weight share; per frequency the
+// bands' sums as well.
+__host__ __device__ inline int asm2_band_doubles(int H, int nb) {
+  const int K = 3 * H - 1;
+  return (2 * K + 1) * cayley_row(K) + 2 * nb * (3 * H + 2);
+}
+__host__ __device__ inline size_t asm2_lds_bytes(int H, int nb) {
+  const int tab = nb ? asm2_band_doubles(H, nb) : asm2_table_doubles(H);
+  return ((size_t)tab + (size_t)kAsmWaves * (64 / asm_group(H)) * (asm2_doubles(H) + nb * 6 * H)) * sizeof(double);
 }
 
 // mu_e, e = 0..2H, of MM from the sums (see assemble_poly), on a group of nl
@@ -173,9 +181,29 @@ __device__ __forceinline__ void assemble_mu(const FreqWork& W, int H, int lane, 
 // (T^b_0 = 2 sum_n |alpha^b_n|^2) the band's sum of M^2, and C_e the same
 // products of B (Mbar^2).  One band reduces to assemble_poly.  W.Z[1..H]
 // receive conj(B_n), which the scoring uses with unit alpha for Mbar.
-__device__ __forceinline__ void assemble_shared(const AsmLayout& S, int nb, int H, int lane) {
-  const FreqWork& W = S.W;
-  for (int q = lane; q < 2 * H; q += 64) {
+struct BandTables { const double2 *Zb, *T, *alb, *wsb; };
+__device__ __forceinline__ void band_tables(double2* alb, double2* wsb, double2* T, const SolveArgs& a, int tid, int nt) {
+  const int H = a.H, nb = a.n_band;
+  for (int q = tid; q < nb * H; q += nt) alb[q] = a.alpha[q];
+  for (int b = tid; b < nb; b += nt) wsb[b] = make_double2(a.lcs[b].wsum, 0.0);
+  __syncthreads();
+  for (int q = tid; q < nb * (2 * H + 1); q += nt) {
+    const int b = q / (2 * H + 1), e = q % (2 * H + 1);
+    const double2* al = alb + b * H;
+    double2 acc = make_double2(0.0, 0.0);
+    if (e == 0) {
+      for (int n = 0; n < H; ++n) acc.x += 2.0 * cabs2(al[n]);
+    } else {
+      const int nlo = e - H > 1 ? e - H : 1;
+      const int nhi = e - 1 < H ? e - 1 : H;
+      for (int n = nlo; n <= nhi; ++n) acc = cadd(acc, cmul(al[n - 1], al[e - n - 1]));
+      for (int n = e + 1; n <= H; ++n) acc = cadd(acc, cscale(cmul(al[n - 1], cconj(al[n - e - 1])), 2.0));
+    }
+    T[q] = acc;
+  }
+}
+__device__ __forceinline__ void assemble_shared(const BandTables& S, const FreqWork& W, int nb, int H, int lane, int nl) {
+  for (int q = lane; q < 2 * H; q += nl) {
     const int n = (q % H) + 1;
     const bool isy = q >= H;
     double2 acc = make_double2(0.0, 0.0);
@@ -188,7 +216,7 @@ __device__ __forceinline__ void assemble_shared(const AsmLayout& S, int nb, int 
   }
   if (lane == 0) W.eta[0] = make_double2(0.0, 0.0);
   wave_sync();
-  for (int e = lane; e <= 2 * H; e += 64) {
+  for (int e = lane; e <= 2 * H; e += nl) {
     double2 acc = make_double2(0.0, 0.0);
     for (int b = 0; b < nb; ++b) {
       const double2 ze = e == 0 ? S.wsb[b] : S.Zb[b * 3 * H + e - 1];
@@ -248,23 +276,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   if (nb == 0) {
     for (int q = lane; q < H; q += 64) S.W.al[q] = a.alpha[q];
   } else {
-    for (int q = lane; q < nb * H; q += 64) S.alb[q] = a.alpha[q];
-    for (int b = lane; b < nb; b += 64) S.wsb[b] = make_double2(a.lcs[b].wsum, 0.0);
-    wave_sync();
-    for (int q = lane; q < nb * (2 * H + 1); q += 64) {
-      const int b = q / (2 * H + 1), e = q % (2 * H + 1);
-      const double2* al = S.alb + b * H;
-      double2 acc = make_double2(0.0, 0.0);
-      if (e == 0) {
-        for (int n = 0; n < H; ++n) acc.x += 2.0 * cabs2(al[n]);
-      } else {
-        const int nlo = e - H > 1 ? e - H : 1;
-        const int nhi = e - 1 < H ? e - 1 : H;
-        for (int n = nlo; n <= nhi; ++n) acc = cadd(acc, cmul(al[n - 1], al[e - n - 1]));
-        for (int n = e + 1; n <= H; ++n) acc = cadd(acc, cscale(cmul(al[n - 1], cconj(al[n - e - 1])), 2.0));
-      }
-      S.T[q] = acc;
-    }
+    band_tables(S.alb, S.wsb, S.T, a, lane, 64);
   }
   wave_sync();
   // e^{2 pi i m / 16}, m = lane mod 16: the rotation phases d phi0 are
@@ -300,7 +312,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
         S.Zb[q] = gather_mode<R>(a.lcs[b], g, (int64_t)k * j, grids);
       }
       wave_sync();
-      assemble_shared(S, nb, H, lane);
+      assemble_shared(BandTables{S.Zb, S.T, S.alb, S.wsb}, W, nb, H, lane, 64);
       assemble_r(W, H, lane, S.hb[0]);
     }
     double rmax = 0.0, mumax = 0.0, etamax = 0.0;
@@ -432,8 +444,8 @@ __device__ __forceinline__ int abs2_hi(double2 z) {
   return (int)((unsigned long long)__double_as_longlong(cabs2(z)) >> 32) & 0x7fffffff;
 }
 
-// Several frequencies per wavefront (single band, sums from the grids, D <
-// 64), one per group of GL lanes with its own LDS working set: two of 32 lanes,
+// Several frequencies per wavefront (D < 64; sums from the grids, given, or of
+// shared-phase bands), one per group of GL lanes with its own LDS working set: two of 32 lanes,
 // or four of 16 where the template has at most five harmonics.  The assembly's
 // per-frequency loops have 3H, 2H + 1, K + 1 or 16 lanes of work, which a group
 // holds (the Cayley dot products, D + 1 columns, take two rounds), so one
@@ -442,30 +454,42 @@ __device__ __forceinline__ int abs2_hi(double2 z) {
 // still runs the (cheap) rotation and dot products, whose results are not
 // written.
 //
-// Bound by vector issue (70-90 % of the slots), so the loops are laid out for few
+// Bound by vector issue (60-65 % of the slots) and, up to H = 5, by writing the
+// records (750 bytes each at H = 4), so the loops are laid out for few
 // instructions: mu's pairs in one loop over the template's tabulated products,
 // rows of the Cayley table contiguous per lane, the rotation's sixteen phases
-// formed once.  Large H = 10 lightcurve (0.5
-// million frequencies) 575 -> 454 us; a batch round at H = 4, sixteen lanes per
-// frequency instead of 32 as well, 3.87 -> 1.75 ms.
-template <typename R, int GL>
+// formed once, and for the grids H as a template parameter (loops and LDS
+// offsets unroll; 10-14 % of the time).  Large H = 10 lightcurve (300 thousand
+// frequencies) 575 -> 402 us; a batch round at H = 4 (4.2 million), sixteen lanes
+// per frequency instead of 32 as well, 3.87 -> 1.65 ms; three bands at H = 6 (50
+// thousand frequencies), one per wavefront before, 184 -> 104 us.
+// HT: H, or 0 to take it from the arguments.  MODE: the sums' source.
+enum { kFromGrids = 0, kFromSums = 1, kFromBands = 2 };
+template <typename R, int GL, int HT, int MODE>
 __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_assemble2(SolveArgs a, double* rec,
                                                                                           int64_t p0, int64_t np) {
   extern __shared__ double sma[];
   constexpr int NG = 64 / GL;
   const int lane = wave_lane(), half = lane >> 5, g = lane / GL, hl = lane & (GL - 1), wv = threadIdx.x >> 6;
   if (a.clear8 && blockIdx.x == 0 && threadIdx.x < 8) a.clear8[threadIdx.x] = 0u;
-  const int H = a.H, K = 3 * H - 1, D = 2 * K;
+  const int H = HT ? HT : a.H, K = 3 * H - 1, D = 2 * K;
   const RecLayout RL(H);
-  // the Cayley table, the template's products and squares, shared by the
-  // workgroup's waves
-  const int LR = cayley_row(K), ntab = asm2_table_doubles(H);
-  for (int i = threadIdx.x; i < ntab; i += 64 * kAsmWaves) sma[i] = a.ctab[i];
+  const int nb = MODE == kFromBands ? a.n_band : 0;
+  // the Cayley table, the template's products and squares (or the bands'),
+  // shared by the workgroup's waves
+  const int LR = cayley_row(K), nct = (D + 1) * LR;
+  const int ntab = MODE == kFromBands ? asm2_band_doubles(H, nb) : asm2_table_doubles(H);
+  for (int i = threadIdx.x; i < (MODE == kFromBands ? nct : ntab); i += 64 * kAsmWaves) sma[i] = a.ctab[i];
   const double* ctab = sma;
-  const double2* prod = reinterpret_cast<const double2*>(sma + (D + 1) * LR);
-  const double* pn = sma + (D + 1) * LR + 2 * template_products(H);
+  const double2* prod = reinterpret_cast<const double2*>(sma + nct);
+  const double* pn = sma + nct + 2 * template_products(H);
   double2* scr;
-  const FreqWork W = asm2_layout(sma + ntab + (NG * wv + g) * asm2_doubles(H), H, scr);
+  double* const work = sma + ntab + (NG * wv + g) * (asm2_doubles(H) + nb * 6 * H);
+  const FreqWork W = asm2_layout(work, H, scr);
+  double2* const Zb = reinterpret_cast<double2*>(work + asm2_doubles(H));
+  double2* const bt = reinterpret_cast<double2*>(sma + nct);
+  const BandTables B{Zb, bt, bt + nb * (2 * H + 1), bt + nb * (3 * H + 1)};
+  if (MODE == kFromBands) band_tables(bt + nb * (2 * H + 1), bt + nb * (3 * H + 1), bt, a, threadIdx.x, 64 * kAsmWaves);
   __syncthreads();
   double tab_c, tab_s;
   sincos(kTwoPi * (lane & 15) / 16.0, &tab_s, &tab_c);
@@ -486,18 +510,39 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
     const LcInfo& L = a.lcs[lc];
     const int64_t j = pidx - a.freq_off[lc] + 1;
     const bool bad = L.status != 0;
-    if (hl == 0) W.Z[0] = make_double2(1.0, 0.0);
-    for (int q = hl; q < 3 * H; q += GL) {
-      const int gr = q < 2 * H ? 0 : 1;
-      const int k = gr == 0 ? q + 1 : q - 2 * H + 1;
-      W.Z[q + 1] = bad ? make_double2(0.0, 0.0) : gather_mode<R>(L, gr, (int64_t)k * j, grids);
-    }
-    wave_sync();
-    assemble_mu(W, H, hl, GL, prod, pn, scr);
-    if (hl < H) {
+    if constexpr (MODE == kFromBands) {
+      // every band's sums of this frequency (grids of lightcurves 0..nb-1)
+      for (int q = hl; q < nb * 3 * H; q += GL) {
+        const int b = q / (3 * H), qq = q % (3 * H);
+        const int gr = qq < 2 * H ? 0 : 1;
+        const int k = gr == 0 ? qq + 1 : qq - 2 * H + 1;
+        Zb[q] = bad ? make_double2(0.0, 0.0) : gather_mode<R>(a.lcs[b], gr, (int64_t)k * j, grids);
+      }
+      wave_sync();
+      assemble_shared(B, W, nb, H, hl, GL);
+    } else {
+      if (hl == 0) W.Z[0] = make_double2(1.0, 0.0);
+      for (int q = hl; q < 3 * H; q += GL) {
+        double2 z = make_double2(0.0, 0.0);
+        if (!bad) {
+          if constexpr (MODE == kFromSums) {
+            z = reinterpret_cast<const double2*>(a.sums_in)[pidx * 3 * H + q];
+            if (q >= 2 * H) z = cscale(z, L.inv_sqrt_yy);
+          } else {
+            const int gr = q < 2 * H ? 0 : 1;
+            const int k = gr == 0 ? q + 1 : q - 2 * H + 1;
+            z = gather_mode<R>(L, gr, (int64_t)k * j, grids);
+          }
+        }
+        W.Z[q + 1] = z;
+      }
+      wave_sync();
+      assemble_mu(W, H, hl, GL, prod, pn, scr);
+      if (hl < H) {
 #pragma clang fp contract(off)
-      const double2 z = W.Z[2 * H + 1 + hl];   // eta_k = alpha_k conj(Zy_k)
-      W.eta[hl + 1] = make_double2(fma(alk.x, z.x, alk.y * z.y), fma(alk.y, z.x, -(alk.x * z.y)));
+        const double2 z = W.Z[2 * H + 1 + hl];   // eta_k = alpha_k conj(Zy_k)
+        W.eta[hl + 1] = make_double2(fma(alk.x, z.x, alk.y * z.y), fma(alk.y, z.x, -(alk.x * z.y)));
+      }
     }
     if (hl == 0) W.eta[0] = make_double2(0.0, 0.0);
     wave_sync();
@@ -1111,21 +1156,38 @@ __global__ void k_export_stats(const LcInfo* lcs, double* out) {
 
 // ------------------------------------------------------------ launchers
 
+template <typename R>
+static void launch_assemble2(const SolveArgs& a, double* rec, int64_t p0, int64_t np, unsigned wg, hipStream_t st) {
+  const dim3 grid(wg), block(64 * kAsmWaves);
+  const size_t lds = asm2_lds_bytes(a.H, a.n_band);
+  const bool g16 = asm_group(a.H) == 16;
+  if (a.n_band) {
+    if (g16) hipLaunchKernelGGL((k_assemble2<R, 16, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
+    else hipLaunchKernelGGL((k_assemble2<R, 32, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
+    return;
+  }
+  if (a.sums_in) {
+    if (g16) hipLaunchKernelGGL((k_assemble2<double, 16, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
+    else hipLaunchKernelGGL((k_assemble2<double, 32, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
+    return;
+  }
+  switch (a.H) {
+#define FTP_ASM(h) case h: hipLaunchKernelGGL((k_assemble2<R, asm_group(h), h, kFromGrids>), grid, block, lds, st, a, rec, p0, np); break;
+    FTP_ASM(1) FTP_ASM(2) FTP_ASM(3) FTP_ASM(4) FTP_ASM(5)
+    FTP_ASM(6) FTP_ASM(7) FTP_ASM(8) FTP_ASM(9) FTP_ASM(10)
+#undef FTP_ASM
+  }
+}
+
 hipError_t launch_assemble(int precision, const SolveArgs& a, double* rec, int64_t p0, int64_t np, int waves,
                            hipStream_t st) {
-  if (a.n_band == 0 && !a.sums_in && 6 * a.H - 2 < 64) {
+  if (6 * a.H - 2 < 64 && asm2_lds_bytes(a.H, a.n_band) <= ((size_t)64 << 10)) {
     // several frequencies per wavefront, kAsmWaves wavefronts per workgroup
-    const size_t lds2 = asm2_lds_bytes(a.H);
+    // (many bands of many harmonics do not fit its LDS: one per wavefront)
     const int per = 64 / asm_group(a.H);
     const int64_t w2 = std::max<int64_t>(1, std::min<int64_t>(waves, (np + per - 1) / per));
-    const dim3 grid((unsigned)((w2 + kAsmWaves - 1) / kAsmWaves)), block(64 * kAsmWaves);
-    if (precision == 1) {
-      if (per == 4) hipLaunchKernelGGL((k_assemble2<double, 16>), grid, block, lds2, st, a, rec, p0, np);
-      else hipLaunchKernelGGL((k_assemble2<double, 32>), grid, block, lds2, st, a, rec, p0, np);
-    } else {
-      if (per == 4) hipLaunchKernelGGL((k_assemble2<float, 16>), grid, block, lds2, st, a, rec, p0, np);
-      else hipLaunchKernelGGL((k_assemble2<float, 32>), grid, block, lds2, st, a, rec, p0, np);
-    }
+    if (precision == 1) launch_assemble2<double>(a, rec, p0, np, (unsigned)((w2 + kAsmWaves - 1) / kAsmWaves), st);
+    else launch_assemble2<float>(a, rec, p0, np, (unsigned)((w2 + kAsmWaves - 1) / kAsmWaves), st);
     return hipGetLastError();
   }
   const size_t lds = asm_lds_bytes(a.H, a.n_band);
