@@ -594,16 +594,6 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
   return c;
 }
 
-// Iterate (u, sg) of the phase whose direction is (c, s) (any length r > 0)
-// relative to phi0: tan(alpha / 2) = s / (r + c), taken while c >= 0 (|u| <=
-// 1); otherwise its reciprocal, (r + c) / s = s / (r - c).
-__device__ __forceinline__ void u_from_dir(double c, double s, double& u, int& sg) {
-  const double r = sqrt(fma(c, c, s * s));
-  const bool in = c >= 0.0;
-  u = s * fast_rcp_d(fmax(in ? r + c : r - c, 1e-300));
-  sg = in ? 1 : -1;
-}
-
 // Four (H = 6..10) or eight (H <= 5) frequencies per wavefront, consecutive ones
 // of the list.  Their Sturm chains run side by side, a group of lanes each
 // (sturm_count_groups); then Newton runs on two of them at a time, lanes

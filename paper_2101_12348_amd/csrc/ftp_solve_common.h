@@ -527,6 +527,16 @@ __device__ __forceinline__ void sincos_small(double x, double& s, double& c) {
   c = ((q + 1) & 2) ? -cc : cc;
 }
 
+// Iterate (u, sg) of the phase whose direction is (c, s) (any length r > 0)
+// relative to phi0: tan(alpha / 2) = s / (r + c), taken while c >= 0 (|u| <=
+// 1); otherwise its reciprocal, (r + c) / s = s / (r - c).
+__device__ __forceinline__ void u_from_dir(double c, double s, double& u, int& sg) {
+  const double r = sqrt(fma(c, c, s * s));
+  const bool in = c >= 0.0;
+  u = s * fast_rcp_d(fmax(in ? r + c : r - c, 1e-300));
+  sg = in ? 1 : -1;
+}
+
 // atan(u) for |u| <= 1.  Two halvings, atan(u) = 2 atan(u / (1 + sqrt(1 +
 // u^2))), bring the argument below tan(pi / 16) < 0.199, where the Taylor
 // series through z^23 leaves a remainder below 2e-17 of the result.
