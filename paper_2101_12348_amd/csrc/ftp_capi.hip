@@ -426,7 +426,6 @@ struct ftp_plan {
   std::vector<FftGridPass> h_fft;
   std::vector<int64_t> h_items;
   std::vector<int64_t> fft_round_tab_off, fft_round_n, fft_round_items;
-  std::vector<int> fft_round_el;   // log2 of the largest LDS block (elements) a round's passes use
   // per-chunk tables (lightcurve plans, offsets, FFT passes) packed into one
   // pinned host buffer and sent with one copy; the d_* pointers point into
   // d_stage
@@ -493,12 +492,12 @@ int validate_template(int H, const double* c, const double* s) {
 int default_msp(int precision) { return precision == FTP_FP64 ? 12 : 7; }
 
 // FFT pass plan: passes (largest stride first) with in-LDS sizes.
-// log2 of the elements one FFT workgroup holds in LDS (64 KB)
-int fft_max_el(int precision) { return precision == FTP_FP64 ? 12 : 13; }
+// log2 of the elements one FFT workgroup takes (35 KB of LDS with its padding)
+int fft_block_log2(int precision) { return precision == FTP_FP64 ? 11 : 12; }
 
 void fft_plan(int L, int precision, int* npass, int* lp) {
   const int last = precision == FTP_FP64 ? 11 : 12;   // largest single pass (twiddle table)
-  const int wide = fft_max_el(precision) - 4;         // earlier passes: 16 columns per workgroup
+  const int wide = precision == FTP_FP64 ? 8 : 9;     // earlier passes: at least 8 columns per workgroup
   if (L <= last) { *npass = 1; lp[0] = L; return; }
   const int rest = L - last;
   const int npre = (rest + wide - 1) / wide;
@@ -679,9 +678,9 @@ int run_nfft(ftp_plan* P, int64_t n_lc, int64_t n_pts, int64_t n_grid, int64_t n
   const C* tw = reinterpret_cast<const C*>(P->opt.precision == FTP_FP64 ? P->twiddle64.p : P->twiddle32.p);
   int64_t item_base = 0;
   for (size_t r = 0; r < P->fft_round_n.size(); ++r) {
-    // LDS for the round's largest block only (more workgroups per CU)
-    hipLaunchKernelGGL(k_fft_pass<R>, dim3((unsigned)P->fft_round_items[r]), dim3(256),
-                       sizeof(C) << P->fft_round_el[r], st,
+    const int el = fft_block_log2(P->opt.precision);
+    hipLaunchKernelGGL(k_fft_pass<R>, dim3((unsigned)P->fft_round_items[r]), dim3(1u << (el - 4)),
+                       (sizeof(C) << el) + (sizeof(C) << (el - 4)) + (sizeof(C) << (el - 6)), st,
                        P->d_fft + P->fft_round_tab_off[r], P->fft_round_n[r], P->d_items + item_base, tw,
                        P->grids.as<C>(), P->tile_off.as<int64_t>());
     item_base += P->fft_round_n[r] + 1;
@@ -704,12 +703,10 @@ void build_fft_tables(ftp_plan* P) {
   P->fft_round_tab_off.clear();
   P->fft_round_n.clear();
   P->fft_round_items.clear();
-  P->fft_round_el.clear();
   for (int r = 0; r < max_pass; ++r) {
     P->fft_round_tab_off.push_back((int64_t)tab.size());
     int64_t it = 0;
     int64_t cnt = 0;
-    int el = 0;
     for (const LcInfo& L : P->h_lc) {
       for (int g = 0; g < 2; ++g) {
         if (L.npass[g] <= r) continue;
@@ -722,17 +719,17 @@ void build_fft_tables(ftp_plan* P) {
         int consumed = 0;
         for (int q = 0; q <= r; ++q) consumed += L.lp[g][q];
         fp.ls = fp.log2n - consumed;
-        const int maxel = fft_max_el(P->opt.precision);
-        fp.lcols = std::min(fp.ls, std::min(4, maxel - fp.lp));
-        el = std::max(el, fp.lp + fp.lcols);
+        // the last pass's k is the mode's high digit: modes -mc .. mmax - mc
+        const int64_t mmax = g == 0 ? 2LL * P->H * L.n_f : (int64_t)P->H * L.n_f, n = 1LL << fp.log2n;
+        fp.khi = (int)((mmax - L.mc[g]) >> (fp.log2n - fp.lp));
+        fp.klo = (int)((n - std::max<int64_t>(L.mc[g], 1)) >> (fp.log2n - fp.lp));
         tab.push_back(fp);
-        it += 1LL << (fp.log2n - fp.lp - fp.lcols);
+        it += 1LL << (fp.log2n - fft_block_log2(P->opt.precision));
         ++cnt;
       }
     }
     P->fft_round_n.push_back(cnt);
     P->fft_round_items.push_back(it);
-    P->fft_round_el.push_back(el);
   }
   // item_begin arrays per round, laid out after each other (with sentinel)
   for (int r = 0; r < max_pass; ++r) {

@@ -14,7 +14,8 @@ constexpr int kFixedShift = 60;       // fixed-point scale 2^60 for exact accumu
 constexpr int kMaxPasses = 4;
 constexpr int64_t kScanSingleMax = 1024 * 16;   // tile counts the one-workgroup scan handles (16 per thread)
 constexpr int64_t kLcBlock = 1024;   // pairs per entry of the lightcurve hint table of a batch
-constexpr int kTwiddleN = 4096;       // size of the in-LDS twiddle table (w_4096^r)
+constexpr int kTwiddleLog = 12;
+constexpr int kTwiddleN = 1 << kTwiddleLog;   // size of the twiddle table (w_4096^r)
 
 // Per-lightcurve record.  The host fills the plan part; k_prep_stats fills the
 // statistics part on the device.
@@ -88,7 +89,8 @@ struct FftGridPass {
   int64_t tile_base;       // first pass of the grid: global index of its first spreading tile
                            // (tiles that received no point were not written and read as zero);
                            // later passes: -1
-  int log2n, lp, ls, lcols;  // log2 of size, pass size, stride, columns per item
+  int log2n, lp, ls;       // log2 of size, pass size, stride
+  int khi, klo;            // last pass (ls = 0): k <= khi and k >= klo hold the gathered modes
 };
 
 // Solve statistics, in kCounterSlots copies: each wavefront adds to copy

@@ -15,7 +15,7 @@
 //              LDS as 2^60 fixed-point integers.  Integer addition is
 //              associative, so the grid is bit-for-bit independent of the
 //              order in which points arrive and no global atomics touch it;
-//   fft      : multi-pass in-place FFT, each pass an LDS-resident radix-2
+//   fft      : multi-pass in-place FFT, each pass a workgroup-resident radix-2
 //              transform over strided columns; the output stays in mixed-radix
 //              digit-reversed order, which the gather undoes by index math.
 #include "ftp_internal.h"
@@ -574,151 +574,244 @@ __global__ __launch_bounds__(256) void k_spread(const LcInfo* __restrict__ lcs, 
 
 // ------------------------------------------------------------ FFT pass
 
+__device__ __forceinline__ float fma_r(float a, float b, float c) { return fmaf(a, b, c); }
+__device__ __forceinline__ double fma_r(double a, double b, double c) { return fma(a, b, c); }
+__device__ __forceinline__ float ldexp_r(float x, int e) { return ldexpf(x, e); }
+__device__ __forceinline__ double ldexp_r(double x, int e) { return ldexp(x, e); }
 __device__ __forceinline__ void cs_pi(float x, float& s, float& c) { sincospif(x, &s, &c); }
 __device__ __forceinline__ void cs_pi(double x, double& s, double& c) { sincospi(x, &s, &c); }
 
 // One pass: for each block b and column j0 (0 <= j0 < s = 2^ls), the np-point
 // transform Y[k] = sum_m x[b np s + j0 + s m] w_np^{m k} (w = e^{+2 pi i/.}),
 // followed by the twiddle w_{np s}^{j0 k}; Y[k] is written back in place at
-// b np s + j0 + s k.  A workgroup owns 2^lcols adjacent columns.
+// b np s + j0 + s k.  In-place radix-2 decimation in frequency, output in
+// bit-reversed order; pairs of stages (spans S and S/2) are one radix-4 step on
+// x[i], x[i + S/2], x[i + S], x[i + 3S/2] (i = 2S-block base + r, r < S/2):
+//   y0 = x0 + x2, y2 = (x0 - x2) w_{2S}^r, y1 = x1 + x3, y3 = (x1 - x3) w_{2S}^r i,
+//   z0 = y0 + y1, z1 = (y0 - y1) w_S^r,   z2 = y2 + y3, z3 = (y2 - y3) w_S^r,
+// exactly the two radix-2 stages (w_{2S}^{r + S/2} = w_{2S}^r i and
+// w_S^r = (w_{2S}^r)^2 taken from the table); an odd stage count ends with one
+// radix-2 stage.
+//
+// A thread holds sixteen elements and does two radix-4 steps on them in
+// registers, so a pass of 4096 points has three exchanges of data instead of
+// seven: the first step's elements come straight from memory and the last one's
+// go straight back, two trips through LDS between them.  A workgroup owns 2^EL
+// elements, 2^(EL - LP) adjacent columns, whatever the pass (35 KB of LDS with
+// the padding that keeps its rows on distinct banks: four workgroups per CU).
+// Of the last pass only the k whose modes are gathered are written (half of them
+// at an oversampling of two).
+//
+// Bound by memory latency at four wavefronts per SIMD (40-70 % of the issue
+// slots, the most in earlier passes, whose twiddles cost a sine and cosine per
+// element).  Against one radix-4 step per trip through LDS (FP32, then FP64): a
+// grid pair of 2^24 + 2^23 points 344 -> 249 us and 660 -> 485 us for three passes,
+// five of 2^21 + 2^20 212 -> 118 us for two.
+template <typename C>
+__device__ __forceinline__ C tw_mul(C d, C w) {
+#pragma clang fp contract(off)
+  C o;
+  o.x = fma_r(d.x, w.x, -(d.y * w.y));
+  o.y = fma_r(d.y, w.x, d.x * w.y);
+  return o;
+}
+
+// One radix-4 step in place (unit: both twiddles are 1).
+template <bool UNIT, typename C>
+__device__ __forceinline__ void radix4(C& x0, C& x1, C& x2, C& x3, C w, C w2) {
+#pragma clang fp contract(off)
+  C y0, y1, y2, d, v;
+  y0.x = x0.x + x2.x; y0.y = x0.y + x2.y;
+  d.x = x0.x - x2.x; d.y = x0.y - x2.y;
+  y2 = UNIT ? d : tw_mul(d, w);
+  y1.x = x1.x + x3.x; y1.y = x1.y + x3.y;
+  d.x = x1.x - x3.x; d.y = x1.y - x3.y;
+  v = UNIT ? d : tw_mul(d, w);   // y3 = v i
+  x0.x = y0.x + y1.x; x0.y = y0.y + y1.y;
+  d.x = y0.x - y1.x; d.y = y0.y - y1.y;
+  x1 = UNIT ? d : tw_mul(d, w2);
+  x2.x = y2.x - v.y; x2.y = y2.y + v.x;
+  d.x = y2.x + v.y; d.y = y2.y - v.x;
+  if (UNIT) {
+    x3 = d;
+  } else {
+    x3.x = fma_r(d.x, w2.x, -(d.y * w2.y));
+    x3.y = fma_r(d.x, w2.y, d.y * w2.x);
+  }
+}
+
+// LDS row of element i (2^(EL - LP) columns each).
+__device__ __forceinline__ constexpr int fft_row(int i) { return i + (i >> 4) + (i >> 6); }
+
+template <typename R> struct FftBlock;
+template <> struct FftBlock<float> { static constexpr int EL = 12; };
+template <> struct FftBlock<double> { static constexpr int EL = 11; };
+
+// The two radix-4 steps of elements i0 + h k, k = 0..15 (spans 8h and 2h), r =
+// i0 mod h.
+template <int LP, int LH, typename C>
+__device__ __forceinline__ void radix16(C (&x)[16], int r, const C* __restrict__ tw) {
+  constexpr int sh = kTwiddleLog - LP;   // w_np^j = table[j << sh]
+  constexpr int a = LP - 4 - LH;         // span 8h = 2^(LH + 3): w_{16h}^r = w_np^(r << a)
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    const int rm = r + (m << LH);
+    if (LH == 0 && m == 0) radix4<true>(x[0], x[4], x[8], x[12], x[0], x[0]);
+    else radix4<false>(x[m], x[m + 4], x[m + 8], x[m + 12], tw[rm << (a + sh)], tw[rm << (a + 1 + sh)]);
+  }
+  if (LH == 0) {
+#pragma unroll
+    for (int j = 0; j < 16; j += 4) radix4<true>(x[j], x[j + 1], x[j + 2], x[j + 3], x[0], x[0]);
+  } else {
+    const C w = tw[r << (a + 2 + sh)], w2 = tw[r << (a + 3 + sh)];
+#pragma unroll
+    for (int j = 0; j < 16; j += 4) radix4<false>(x[j], x[j + 1], x[j + 2], x[j + 3], w, w2);
+  }
+}
+
+// The last TL = 1..3 stages on contiguous groups of 2^TL elements.
+template <int LP, int TL, typename C>
+__device__ __forceinline__ void fft_tail(C* x, const C* __restrict__ tw) {
+  if constexpr (TL >= 2) {
+    constexpr int h = 1 << (TL - 2);
+    radix4<true>(x[0], x[h], x[2 * h], x[3 * h], x[0], x[0]);
+    if constexpr (TL == 3)
+      radix4<false>(x[1], x[1 + h], x[1 + 2 * h], x[1 + 3 * h], tw[1 << (kTwiddleLog - 3)], tw[1 << (kTwiddleLog - 2)]);
+  }
+  if constexpr (TL & 1) {
+#pragma unroll
+    for (int j = 0; j < (1 << TL); j += 2) {
+      const C p = x[j], q = x[j + 1];
+      x[j].x = p.x + q.x; x[j].y = p.y + q.y;
+      x[j + 1].x = p.x - q.x; x[j + 1].y = p.y - q.y;
+    }
+  }
+}
+
+template <typename R, int LP>
+__device__ __forceinline__ void fft_block(const FftGridPass& P, int64_t base, int64_t j0b, typename Cplx<R>::T* buf,
+                                          typename Cplx<R>::T* g, const typename Cplx<R>::T* __restrict__ tw,
+                                          const int64_t* __restrict__ tile_off) {
+  using C = typename Cplx<R>::T;
+  constexpr int EL = FftBlock<R>::EL, LC = EL - LP, cols = 1 << LC, TL = LP & 3;
+  const int tid = threadIdx.x;
+  const int ls = P.ls;
+  // The first pass reads elements of spreading tiles that received no point as
+  // zero (those tiles were not written); adjacent columns never straddle a tile.
+  const bool first = P.tile_base >= 0;
+  auto load = [&](int m, int c) -> C {
+    const int64_t off = ((int64_t)m << ls) + c;
+    if (first) {
+      const int64_t t = P.tile_base + ((base + off) >> kTileShift);
+      if (tile_off[t + 1] == tile_off[t]) return C{(R)0, (R)0};
+    }
+    return g[off];
+  };
+  // twiddle w_{np s}^{j0 k} and store Y[k]; the last pass: the gathered k
+  const int log2L = LP + ls;
+  auto store = [&](C v, int k, int c) {
+    if (ls > 0) {
+#pragma clang fp contract(off)
+      const unsigned ex = ((unsigned)(j0b + c) * (unsigned)k) & ((1u << log2L) - 1u);
+      R sn, cs;
+      cs_pi(ldexp_r((R)ex, 1 - log2L), sn, cs);
+      C o;
+      o.x = fma_r(v.x, cs, -(v.y * sn));
+      o.y = fma_r(v.x, sn, v.y * cs);
+      g[((int64_t)k << ls) + c] = o;
+    } else if (k <= P.khi || k >= P.klo) {
+      g[((int64_t)k << ls) + c] = v;
+    }
+  };
+  C x[16];
+  if constexpr (LP < 4) {
+    // a thread holds 2^(4 - LP) whole columns
+    constexpr int n = 1 << LP;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) x[e] = load(e & (n - 1), tid + ((e >> LP) << (EL - 4)));
+#pragma unroll
+    for (int e = 0; e < 16; e += n) fft_tail<LP, LP>(x + e, tw);
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const int i = e & (n - 1);
+      store(x[e], (int)(__brev((unsigned)i) >> (32 - LP)), tid + ((e >> LP) << (EL - 4)));
+    }
+  } else {
+    const int c = tid & (cols - 1), q = tid >> LC;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) x[k] = load(q + (k << (LP - 4)), c);
+    radix16<LP, LP - 4>(x, q, tw);
+    // the row group of the last step: brev so that the stores run over adjacent k
+    const int qb = LP > 4 ? (int)(__brev((unsigned)q) >> (36 - LP)) : 0;
+    if constexpr (LP > 4) {
+      // (rows of a step's elements: that of the first, plus constants)
+      C* b0 = buf + (fft_row(q) << LC) + c;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) b0[fft_row(k << (LP - 4)) << LC] = x[k];
+      __syncthreads();
+      if constexpr (LP > 8) {
+        // second step, h = np / 256
+        constexpr int LH = LP - 8;
+        const int r = q & ((1 << LH) - 1);
+        C* b1 = buf + ((fft_row((q >> LH) << (LH + 4)) + r) << LC) + c;
+#pragma unroll
+        for (int k = 0; k < 16; ++k) x[k] = b1[fft_row(k << LH) << LC];
+        radix16<LP, LH>(x, r, tw);
+#pragma unroll
+        for (int k = 0; k < 16; ++k) b1[fft_row(k << LH) << LC] = x[k];
+        __syncthreads();
+      }
+      const C* b2 = buf + (fft_row(16 * qb) << LC) + c;
+#pragma unroll
+      for (int e = 0; e < 16; ++e) x[e] = b2[e << LC];
+      if constexpr (TL == 0) {
+        radix16<LP, 0>(x, 0, tw);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 16; e += 1 << TL) fft_tail<LP, TL>(x + e, tw);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      // k = brev(16 qb + e)
+      const int k = (int)((__brev((unsigned)e) >> 28) << (LP - 4)) + q;
+      store(x[e], k, c);
+    }
+  }
+}
+
 template <typename R>
-__global__ __launch_bounds__(256) void k_fft_pass(const FftGridPass* __restrict__ passes, int64_t n_grids,
+__global__ __launch_bounds__(1 << (FftBlock<R>::EL - 4)) void k_fft_pass(const FftGridPass* __restrict__ passes, int64_t n_grids,
                                                   const int64_t* __restrict__ item_begin,
                                                   const typename Cplx<R>::T* __restrict__ twiddle,
                                                   typename Cplx<R>::T* __restrict__ grids,
                                                   const int64_t* __restrict__ tile_off) {
   using C = typename Cplx<R>::T;
+  constexpr int EL = FftBlock<R>::EL;
   extern __shared__ unsigned char smem_raw[];
   C* buf = reinterpret_cast<C*>(smem_raw);
   const int64_t item = blockIdx.x;
   const int64_t gi = find_segment(item_begin, n_grids, item);
   const FftGridPass P = passes[gi];
   const int64_t local_item = item - P.item_begin;
-  const int lp = P.lp, ls = P.ls, lcols = P.lcols;
-  const int np = 1 << lp, cols = 1 << lcols;
-  const int64_t s = 1LL << ls;
-  const int64_t groups_per_block = s >> lcols;
-  const int64_t blk = local_item / groups_per_block;
-  const int64_t j0b = (local_item % groups_per_block) << lcols;
-  const int64_t base = blk * ((int64_t)np << ls) + j0b;   // position of element (0, 0) in the grid
+  const int lc = EL - P.lp;   // columns per workgroup (ls >= lc)
+  const int lg = P.ls - lc;
+  const int64_t blk = local_item >> lg;
+  const int64_t j0b = (local_item & ((1LL << lg) - 1)) << lc;
+  const int64_t base = (blk << (P.lp + P.ls)) + j0b;   // position of element (0, 0) in the grid
   C* g = grids + P.grid_off + base;
-  const int total = np << lcols;
-  // load: element (m, c) -> buf[m * cols + c], eight loads in flight per
-  // thread (total is a multiple of 2048 whenever it exceeds it).  The first
-  // pass reads elements of spreading tiles that received no point as zero
-  // (those tiles were not written); a column group (cols <= 16 adjacent
-  // cells) never straddles a tile.
-  const bool first = P.tile_base >= 0;
-  auto in_empty_tile = [&](int64_t pos) -> bool {
-    const int64_t t = P.tile_base + (pos >> kTileShift);
-    return tile_off[t + 1] == tile_off[t];
-  };
-  const C zero = {(R)0, (R)0};
-  if (total >= 8 * 256) {
-    for (int e0 = threadIdx.x; e0 < total; e0 += 8 * 256) {
-      C v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int e = e0 + u * 256;
-        const int64_t off = (int64_t)(e >> lcols) * s + (e & (cols - 1));
-        v[u] = (first && in_empty_tile(base + off)) ? zero : g[off];
+  switch (P.lp) {
+#define FTP_FFT(lp) case lp: fft_block<R, lp>(P, base, j0b, buf, g, twiddle, tile_off); break;
+    FTP_FFT(1) FTP_FFT(2) FTP_FFT(3) FTP_FFT(4) FTP_FFT(5) FTP_FFT(6) FTP_FFT(7) FTP_FFT(8)
+    default:
+      if constexpr (EL == 12) {
+        if (P.lp == 9) fft_block<R, 9>(P, base, j0b, buf, g, twiddle, tile_off);
+        else fft_block<R, 12>(P, base, j0b, buf, g, twiddle, tile_off);
+      } else {
+        fft_block<R, 11>(P, base, j0b, buf, g, twiddle, tile_off);
       }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) buf[e0 + u * 256] = v[u];
-    }
-  } else {
-    for (int e = threadIdx.x; e < total; e += 256) {
-      const int m = e >> lcols, c = e & (cols - 1);
-      const int64_t off = (int64_t)m * s + c;
-      buf[e] = (first && in_empty_tile(base + off)) ? zero : g[off];
-    }
+#undef FTP_FFT
   }
-  __syncthreads();
-  // in-place radix-2 decimation in frequency; output in bit-reversed order.
-  // Pairs of stages (spans S and S/2) run as one radix-4 step per thread on
-  // x[i], x[i + S/2], x[i + S], x[i + 3S/2] (i = 2S-block base + r, r < S/2):
-  //   y0 = x0 + x2, y2 = (x0 - x2) w_{2S}^r, y1 = x1 + x3, y3 = (x1 - x3) w_{2S}^r i,
-  //   z0 = y0 + y1, z1 = (y0 - y1) w_S^r,   z2 = y2 + y3, z3 = (y2 - y3) w_S^r,
-  // exactly the two radix-2 stages (w_{2S}^{r + S/2} = w_{2S}^r i and
-  // w_S^r = (w_{2S}^r)^2 taken from the table), with one LDS round trip and one
-  // barrier instead of two; an odd stage count ends with one radix-2 stage.
-  const int tstride = kTwiddleN >> lp;   // w_np^r = w_4096^{r * 4096/np}
-  int span = np >> 1, lspan = lp - 1;
-  for (; span >= 2; span >>= 2, lspan -= 2) {
-    const int h = span >> 1;             // S/2
-    const int ng = (np >> 2) << lcols;   // radix-4 groups per step
-    for (int bi = threadIdx.x; bi < ng; bi += 256) {
-      const int c = bi & (cols - 1);
-      const int q = bi >> lcols;                 // 0 .. np/4 - 1
-      const int r = q & (h - 1);
-      const int i0 = ((q >> (lspan - 1)) << (lspan + 1)) + r;
-      C x0 = buf[i0 * cols + c], x1 = buf[(i0 + h) * cols + c];
-      C x2 = buf[(i0 + span) * cols + c], x3 = buf[(i0 + span + h) * cols + c];
-      const C w = twiddle[(r << (lp - 1 - lspan)) * tstride];        // w_{2S}^r
-      const C w2 = twiddle[(r << (lp - lspan)) * tstride];           // w_S^r
-      C y0, y1, y2, y3, d;
-      y0.x = x0.x + x2.x; y0.y = x0.y + x2.y;
-      d.x = x0.x - x2.x; d.y = x0.y - x2.y;
-      y2.x = d.x * w.x - d.y * w.y; y2.y = d.x * w.y + d.y * w.x;
-      y1.x = x1.x + x3.x; y1.y = x1.y + x3.y;
-      d.x = x1.x - x3.x; d.y = x1.y - x3.y;
-      // (d w) i
-      y3.x = -(d.x * w.y + d.y * w.x); y3.y = d.x * w.x - d.y * w.y;
-      C z0, z1, z2, z3;
-      z0.x = y0.x + y1.x; z0.y = y0.y + y1.y;
-      d.x = y0.x - y1.x; d.y = y0.y - y1.y;
-      z1.x = d.x * w2.x - d.y * w2.y; z1.y = d.x * w2.y + d.y * w2.x;
-      z2.x = y2.x + y3.x; z2.y = y2.y + y3.y;
-      d.x = y2.x - y3.x; d.y = y2.y - y3.y;
-      z3.x = d.x * w2.x - d.y * w2.y; z3.y = d.x * w2.y + d.y * w2.x;
-      buf[i0 * cols + c] = z0;
-      buf[(i0 + h) * cols + c] = z1;
-      buf[(i0 + span) * cols + c] = z2;
-      buf[(i0 + span + h) * cols + c] = z3;
-    }
-    __syncthreads();
-  }
-  for (; span >= 1; span >>= 1, --lspan) {
-    const int nb = (np >> 1) << lcols;   // butterflies per stage
-    for (int bi = threadIdx.x; bi < nb; bi += 256) {
-      const int c = bi & (cols - 1);
-      const int q = bi >> lcols;             // 0 .. np/2-1
-      const int r = q & (span - 1);
-      const int i0 = ((q >> lspan) << (lspan + 1)) + r;
-      const int i1 = i0 + span;
-      C a = buf[i0 * cols + c], b = buf[i1 * cols + c];
-      C sum, dif;
-      sum.x = a.x + b.x; sum.y = a.y + b.y;
-      dif.x = a.x - b.x; dif.y = a.y - b.y;
-      // twiddle w_{2 span}^r = w_4096^{r * 4096/(2 span)} = w_np^{r * np/(2 span)}
-      const C w = twiddle[(r << (lp - 1 - lspan)) * tstride];
-      C tw;
-      tw.x = dif.x * w.x - dif.y * w.y;
-      tw.y = dif.x * w.y + dif.y * w.x;
-      buf[i0 * cols + c] = sum;
-      buf[i1 * cols + c] = tw;
-    }
-    __syncthreads();
-  }
-  // twiddle w_{np s}^{j0 k} and store Y[k] at b np s + j0 + s k
-  const int log2L = lp + ls;
-  for (int e = threadIdx.x; e < total; e += 256) {
-    const int k = e >> lcols, c = e & (cols - 1);
-    const int kr = (int)(__brev((unsigned)k) >> (32 - lp));
-    C v = buf[kr * cols + c];
-    if (ls > 0) {
-      const int64_t j0 = j0b + c;
-      const int64_t ex = (j0 * (int64_t)k) & ((1LL << log2L) - 1);
-      R sn, cs;
-      cs_pi((R)2.0 * (R)ex / (R)(1LL << log2L), sn, cs);
-      C o;
-      o.x = v.x * cs - v.y * sn;
-      o.y = v.x * sn + v.y * cs;
-      v = o;
-    }
-    g[(int64_t)k * s + c] = v;
-  }
-  (void)lp;
 }
 
 // Explicit instantiations.
