@@ -14,7 +14,6 @@ struct LearnArgs {
   int64_t* fb_list;         // pairs the round leaves unconfirmed
   unsigned int* fb_count;
   unsigned flags;           // bit 0: forced fallback (every pair to the list); bit 1: 2H starts only
-  unsigned* queue;          // work counter (zeroed), or nullptr for grid striding
   const double2* starts;    // H <= 10: evenly spaced starts per rotation (k_start_table)
 };
 

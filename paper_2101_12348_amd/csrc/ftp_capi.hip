@@ -964,7 +964,6 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         L.fb_count = ctr;
         L.flags = ((P->opt.flags & FTP_FLAG_FORCE_FALLBACK) ? 1u : 0u) | ((P->opt.flags & FTP_FLAG_2H_STARTS) ? 2u : 0u);
         L.starts = P->starts;
-        L.queue = nullptr;   // uniform work per pair: grid striding (a queue costs more than it balances)
         // with the side stream, the Newton kernel and the side scoring launch
         // record the fork and join events themselves: the scoring of the
         // Newton-root pairs is the longest branch after the fork, so it starts

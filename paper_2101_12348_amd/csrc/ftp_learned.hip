@@ -22,7 +22,8 @@
 // eight lanes with four coefficients per lane in registers, and Newton runs on two
 // of them at a time (32 starts each, at most D).  For H = 11 a wavefront takes one
 // (k_newton_sturm, 4H starts), its Sturm sequence one coefficient per lane (the
-// degree-64 coefficient carried as a scalar; see sturm_begin).
+// degree-64 coefficient carried as a scalar; see sturm_begin); above, four whose
+// sequences run in double-double, a 16-lane row each (sturm_count_dd).
 #include <hip/hip_ext.h>
 #include "ftp_solve_common.h"
 #include "ftp_args.h"
@@ -199,108 +200,157 @@ __device__ __forceinline__ dd dd_mul(dd x, dd y) {
   e = fma(x.hi, y.lo, fma(x.lo, y.hi, e));
   return dd_quick(p, e);
 }
-__device__ __forceinline__ dd dd_div(dd x, dd y) {
+// 1 / y: the double reciprocal and one correction (y hi + lo).
+__device__ __forceinline__ dd dd_rcp(dd y) {
 #pragma clang fp contract(off)
-  // two quotient digits: q1 = x / y in double, q2 from the remainder
-  const double q1 = x.hi / y.hi;
-  const dd r = dd_add(x, dd_neg(dd_mul(dd{q1, 0.0}, y)));
-  const double q2 = r.hi / y.hi;
-  return dd_quick(q1, q2);
+  const double r = fast_rcp_d(y.hi);
+  const double e = fma(-y.lo, r, fma(-y.hi, r, 1.0));   // relative error of r, about an ulp
+  return dd_quick(r, r * e);
 }
 __device__ __forceinline__ dd dd_ldexp(dd x, int e) { return dd{ldexp(x.hi, e), ldexp(x.lo, e)}; }
-__device__ __forceinline__ dd dd_lane(dd v, int src) { return dd{lrdlane(v.hi, src), lrdlane(v.lo, src)}; }
-// v from lane - 1 (lane 0: 0), both parts
-__device__ __forceinline__ dd dd_shr1(dd v) { return dd{lane_shr1(v.hi), lane_shr1(v.lo)}; }
+// Lane `addr` / 4 of the wavefront, and the previous lane of the 16-lane row.
+__device__ __forceinline__ double row_bperm_d(int addr, double v) {
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u & 0xffffffffull));
+  const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u >> 32));
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+__device__ __forceinline__ dd dd_bperm(int addr, dd v) { return dd{row_bperm_d(addr, v.hi), row_bperm_d(addr, v.lo)}; }
+__device__ __forceinline__ dd dd_ror1(dd v) { return dd{dpp_d<0x121>(v.hi), dpp_d<0x121>(v.lo)}; }   // row_ror:1
 
-// largest |v| over the wavefront, from the doubles' high words (within a
-// factor 1 + 2^-20: enough for the chain's tests)
-__device__ __forceinline__ double wave_max_abs(double v) {
-  return from_hiword(wave_max_int(hiword(v) & 0x7fffffff));
+// Sturm chains for 64 < D < 96 in double-double, four per wavefront, one per
+// 16-lane row: coefficient c = l + 16 s of a member in register s of lane l.
+// Each remainder is the exact-arithmetic step (quotient q1 x + q0 from the two
+// leading coefficients, by the double-double reciprocal of the divisor's) and each
+// member is scaled by a power of two that brings its leading coefficient into [1,
+// 2) (exact).  The chain is trusted when every remainder's largest coefficient
+// exceeds 1e-24 of the larger of its two members' and its leading coefficient
+// 1e-24 of its largest, all finite: in double precision the spread of the Cayley
+// polynomial's coefficients at these degrees (1e-15 .. 1e-19) defeats the 1e-13
+// test of the other chains, while 106 bits leave room (a 106-bit emulation of this
+// chain trusted and matched the exact count on every polynomial tried at H =
+// 12..15, also where a double-precision chain with a relaxed test was wrong).
+//
+// Bound by vector issue: a step is ~70 instructions per register in use and ~110
+// for the quotients, maxima and tests, which the four chains share; the registers
+// in use fall with the degree.  Against one chain per wavefront with two
+// registers and two divisions per step, the Newton round at D = 76 (50 thousand
+// frequencies) 1977 -> 753 us.
+struct DdState {
+  dd at, bt, rb;      // leading coefficients of the last two members, 1 / bt
+  double mA, mB;      // their largest coefficients (high words)
+  int sp, vp;         // last member positive at +inf; sign changes so far
+  bool ok;
+};
+
+__device__ __forceinline__ double row_max_hi(int h) {
+  h = max(h, dpp_i<0xB1, 0xf>(h));
+  h = max(h, dpp_i<0x4E, 0xf>(h));
+  h = max(h, dpp_i<0x141, 0xf>(h));
+  h = max(h, dpp_i<0x140, 0xf>(h));
+  return from_hiword(h);
 }
 
-// Distinct real roots of g for 64 < D <= 127 in double-double, or -1
-// (`raw`: the count regardless of the tests).  Coefficient c = lane + 64 s of
-// a member in register s.  Each remainder is the exact-arithmetic step
-// (quotient q1 x + q0 from the two leading coefficients, by double-double
-// division) and each member is scaled by a power of two that brings its
-// leading coefficient into [1, 2) (exact).  The chain is trusted when every
-// remainder's largest coefficient exceeds 1e-24 of the larger of its two
-// members' and its leading coefficient 1e-24 of its largest, all finite: in
-// double precision the spread of the Cayley polynomial's coefficients at
-// these degrees (1e-15 .. 1e-19) defeats the 1e-13 test of the other chains,
-// while 106 bits leave room (a 106-bit emulation of this chain trusted and
-// matched the exact count on every polynomial tried at H = 12..15, also where
-// a double-precision chain with a relaxed test was wrong).  All lanes active.
-__device__ int sturm_count_dd(double g0, double g1, int D, int lane, int& raw) {
+// A (degree db + 1) becomes the next member, -rem(A, B) scaled, of degree db - 1;
+// registers 0..R - 1 hold both members (16 (R - 2) <= db - 1).
+template <int R>
+__device__ __forceinline__ void sturm_dd_step(dd (&A)[6], const dd (&B)[6], DdState& S, int db, int l, int row4) {
 #pragma clang fp contract(off)
-  const int c0 = lane, c1 = lane + 64;
-  // g and g' (exact in double-double: (c + 1) g_{c+1} is one product)
-  const double n0 = lane_shl1(g0), n1 = lane_shl1(g1);
-  const double g64 = lrdlane(g1, 0);
-  const double u0 = lane == 63 ? g64 : n0;
-  dd A[2], B[2];
-  A[0] = dd{g0, 0.0};
-  A[1] = dd{g1, 0.0};
-  {
-    const double p0 = (double)(c0 + 1) * u0, p1 = (double)(c1 + 1) * n1;
-    B[0] = c0 < D ? dd{p0, fma((double)(c0 + 1), u0, -p0)} : dd{0.0, 0.0};
-    B[1] = c1 < D ? dd{p1, fma((double)(c1 + 1), n1, -p1)} : dd{0.0, 0.0};
+  const dd q1 = dd_mul(S.at, S.rb);
+  // t = A - q1 x B (the coefficient db + 1 cancels)
+  dd prev{0.0, 0.0};
+#pragma unroll
+  for (int s = 0; s < R; ++s) {
+    const dd ro = dd_ror1(B[s]);
+    const dd sh = l == 0 ? prev : ro;
+    prev = ro;
+    A[s] = dd_add(A[s], dd_neg(dd_mul(q1, sh)));
   }
-  // scale both to leading coefficients in [1, 2) in magnitude
-  auto lead_of = [&](const dd (&X)[2], int deg) { return deg >= 64 ? dd_lane(X[1], deg - 64) : dd_lane(X[0], deg); };
-  int e;
-  {
-    dd la = lead_of(A, D);
-    frexp(la.hi, &e);
-    A[0] = dd_ldexp(A[0], 1 - e);
-    A[1] = dd_ldexp(A[1], 1 - e);
-    dd lb = lead_of(B, D - 1);
-    frexp(lb.hi, &e);
-    B[0] = dd_ldexp(B[0], 1 - e);
-    B[1] = dd_ldexp(B[1], 1 - e);
+  const dd ct = dd_bperm(row4 + ((db & 15) << 2), (R == 1 || (db >> 4) == R - 1) ? A[R - 1] : A[R > 1 ? R - 2 : 0]);
+  const dd q0 = dd_mul(ct, S.rb);
+  // rem = -(t - q0 B): coefficients below db
+  int h = 0;
+#pragma unroll
+  for (int s = 0; s < R; ++s) {
+    dd v = dd_neg(dd_add(A[s], dd_neg(dd_mul(q0, B[s]))));
+    if (s >= R - 2) {
+      const bool in = l + 16 * s < db;
+      v.hi = in ? v.hi : 0.0;
+      v.lo = in ? v.lo : 0.0;
+    }
+    A[s] = v;
+    h = max(h, hiword(v.hi) & 0x7fffffff);
   }
-  bool ok = lead_of(A, D).hi != 0.0 && isfinite(lead_of(A, D).hi) && lead_of(B, D - 1).hi != 0.0;
-  double mA = wave_max_abs(fmax(fabs(A[0].hi), fabs(A[1].hi)));
-  double mB = wave_max_abs(fmax(fabs(B[0].hi), fabs(B[1].hi)));
-  int sp = lead_of(A, D).hi > 0.0 ? 1 : 0;
-  int vp = 0;
-  {
-    const int tb = lead_of(B, D - 1).hi > 0.0 ? 1 : 0;
-    vp += tb ^ sp;
-    sp = tb;
+  const dd lead = dd_bperm(row4 + (((db - 1) & 15) << 2),
+                           (R == 1 || ((db - 1) >> 4) == R - 1) ? A[R - 1] : A[R > 1 ? R - 2 : 0]);
+  const double mr = row_max_hi(h);
+  S.ok = S.ok && isfinite(mr) && mr > 1e-24 * fmax(S.mA, S.mB) && fabs(lead.hi) > 1e-24 * mr;
+  const int tp = lead.hi > 0.0 ? 1 : 0;
+  S.vp += tp ^ S.sp;
+  S.sp = tp;
+  int e = __builtin_amdgcn_frexp_exp(lead.hi);
+  if (!(lead.hi != 0.0 && isfinite(lead.hi))) e = 0;
+#pragma unroll
+  for (int s = 0; s < R; ++s) A[s] = dd_ldexp(A[s], 1 - e);
+  S.at = S.bt;
+  S.bt = dd_ldexp(lead, 1 - e);
+  S.rb = dd_rcp(S.bt);
+  S.mA = S.mB;
+  S.mB = ldexp(mr, 1 - e);
+}
+
+template <int R>
+__device__ __forceinline__ void sturm_dd_run(dd (&A)[6], dd (&B)[6], DdState& S, int& db, int l, int row4) {
+  // two steps at a time, so that the members' roles are fixed; the registers
+  // of the first serve both
+#pragma unroll 1
+  for (; db >= 2 && db + 1 >= 16 * (R - 1); db -= 2) {
+    sturm_dd_step<R>(A, B, S, db, l, row4);
+    sturm_dd_step<R>(B, A, S, db - 1, l, row4);
   }
-  for (int db = D - 1; db >= 1; --db) {   // B has degree db, A degree db + 1
-    const bool two = db + 1 >= 64;         // (wave-uniform)
-    const dd at = lead_of(A, db + 1), bt = lead_of(B, db);
-    const dd q1 = dd_div(at, bt);
-    // t = A - q1 x B (the coefficient db + 1 cancels)
-    dd sh0 = dd_shr1(B[0]), sh1 = dd_shr1(B[1]);
-    const dd b63 = dd_lane(B[0], 63);
-    if (lane == 0) sh1 = b63;
-    dd t0 = dd_add(A[0], dd_neg(dd_mul(q1, sh0)));
-    dd t1 = two ? dd_add(A[1], dd_neg(dd_mul(q1, sh1))) : dd{0.0, 0.0};
-    const dd ct = db >= 64 ? dd_lane(t1, db - 64) : dd_lane(t0, db);
-    const dd q0 = dd_div(ct, bt);
-    // rem = -(t - q0 B): coefficients below db
-    t0 = c0 < db ? dd_neg(dd_add(t0, dd_neg(dd_mul(q0, B[0])))) : dd{0.0, 0.0};
-    t1 = (two && c1 < db) ? dd_neg(dd_add(t1, dd_neg(dd_mul(q0, B[1])))) : dd{0.0, 0.0};
-    const dd lead = db - 1 >= 64 ? dd_lane(t1, db - 65) : dd_lane(t0, db - 1);
-    const double mr = wave_max_abs(fmax(fabs(t0.hi), fabs(t1.hi)));
-    ok = ok && isfinite(mr) && mr > 1e-24 * fmax(mA, mB) && fabs(lead.hi) > 1e-24 * mr;
-    const int tp = lead.hi > 0.0 ? 1 : 0;
-    vp += tp ^ sp;
-    sp = tp;
-    frexp(lead.hi, &e);
-    if (!(lead.hi != 0.0 && isfinite(lead.hi))) e = 0;
-    A[0] = B[0];
-    A[1] = B[1];
-    B[0] = dd_ldexp(t0, 1 - e);
-    B[1] = dd_ldexp(t1, 1 - e);
-    mA = mB;
-    mB = ldexp(mr, 1 - e);
+}
+
+// Distinct real roots of the degree-D polynomial f of this lane's row (D even),
+// or -1 when a step fails its test (`raw`: the count regardless).  All lanes
+// must be active; `on` is uniform in a row.
+__device__ int sturm_count_dd(const double* f, bool on, int D, int lane, int& raw) {
+#pragma clang fp contract(off)
+  const int l = lane & 15, row4 = (lane & ~15) << 2;
+  dd A[6], B[6];
+  int hA = 0, hB = 0;
+  const double fD = on ? f[D] : 1.0, dD = (double)D * fD;
+  // scales that bring the leading coefficients into [1, 2) in magnitude
+  const int eA = 1 - __builtin_amdgcn_frexp_exp(fD), eB = 1 - __builtin_amdgcn_frexp_exp(dD);
+#pragma unroll
+  for (int s = 0; s < 6; ++s) {
+    // g and g' (exact in double-double: (c + 1) g_{c+1} is one product)
+    const int c = l + 16 * s;
+    const double g = on && c <= D ? f[c] : 0.0, g1 = on && c < D ? f[c + 1] : 0.0;
+    const double p = (double)(c + 1) * g1;
+    A[s] = dd_ldexp(dd{g, 0.0}, eA);
+    B[s] = dd_ldexp(dd{p, fma((double)(c + 1), g1, -p)}, eB);
+    hA = max(hA, hiword(A[s].hi) & 0x7fffffff);
+    hB = max(hB, hiword(B[s].hi) & 0x7fffffff);
   }
-  raw = D - 2 * vp;
-  return ok ? raw : -1;
+  DdState S;
+  S.at = dd_ldexp(dd{fD, 0.0}, eA);
+  S.bt = dd_ldexp(dd{dD, fma((double)D, fD, -dD)}, eB);
+  S.rb = dd_rcp(S.bt);
+  S.ok = S.at.hi != 0.0 && isfinite(S.at.hi) && S.bt.hi != 0.0;
+  S.mA = row_max_hi(hA);
+  S.mB = row_max_hi(hB);
+  S.sp = S.bt.hi > 0.0 ? 1 : 0;
+  S.vp = S.sp ^ (S.at.hi > 0.0 ? 1 : 0);
+  int db = D - 1;   // B has degree db, A degree db + 1
+  sturm_dd_run<6>(A, B, S, db, l, row4);
+  sturm_dd_run<5>(A, B, S, db, l, row4);
+  sturm_dd_run<4>(A, B, S, db, l, row4);
+  sturm_dd_run<3>(A, B, S, db, l, row4);
+  sturm_dd_run<2>(A, B, S, db, l, row4);
+  sturm_dd_run<1>(A, B, S, db, l, row4);
+  sturm_dd_step<1>(A, B, S, 1, l, row4);
+  raw = D - 2 * S.vp;
+  return S.ok ? raw : -1;
 }
 
 // v from lane addr / 4 (ds_bpermute, all lanes active)
@@ -839,16 +889,18 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
   }
 }
 
-// One frequency per wavefront (H = 11, D = 64): the Sturm chain of f in
-// registers (the degree-64 coefficient as a scalar), then Newton from 4H
-// starts (the 2H network seeds and 2H evenly spaced phases; all evenly spaced
-// without network), stepped on the Cayley polynomial and merged one root per
-// pass as in k_newton_sturm4, with the same stop rule.
+// Above H = 10: one frequency per wavefront at H = 11 (NC = 1, D = 64: the Sturm
+// chain of f in registers, the degree-64 coefficient as a scalar), four above (NC
+// = 4: their double-double chains run side by side), then for each of them Newton
+// from 4H starts (the 2H network seeds and 2H evenly spaced phases; all evenly
+// spaced without network), stepped on the Cayley polynomial and merged one root
+// per pass, with the stop rule of k_newton_sturm4.
 __host__ __device__ inline size_t learn_lds_bytes(int H) {
   const int D = 6 * H - 2;
   return (size_t)(2 * (newton_top(D) + 2)) * sizeof(double);   // f and its reversal
 }
 
+template <int NC>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_newton_sturm(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
   const int lane = threadIdx.x & 63;
@@ -857,117 +909,132 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const RecLayout RL(H);
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long iters_acc = 0, roots_acc = 0, fb_acc = 0;
-  for (int64_t w = first_item(L.queue, lane); w < L.np; w = next_item(L.queue, lane, w)) {
-    double* R = L.rec + w * (int64_t)RL.stride;
-    const int st = (int)R[RL.meta + M_STATUS];
-    if (st == ST_BAD_LC || st == ST_CONSTANT) continue;
-    if (L.flags & 1u) {   // forced fallback
-      if (lane == 0) {
-        const unsigned slot = atomicAdd(L.fb_count, 1u);
-        L.fb_list[slot] = w;
-        R[RL.meta + M_FALLBACK] = 1.0;
-        R[RL.meta + M_WARM] = 0.0;
-        R[RL.meta + M_COUNT] = -1.0;
-      }
-      ++fb_acc;
-      continue;
-    }
-    for (int c = lane; c <= DP; c += 64) {
-      const double fc = c <= D ? R[RL.f + c] : 0.0;
-      sml[c] = fc;
-      sml[FS + (c <= D ? D - c : c)] = fc;
-    }
-    const double gv = lane <= D ? R[RL.f + lane] : 0.0;
-    const double gv1 = lane + 64 <= D ? R[RL.f + 64 + lane] : 0.0;
-    const double gtop = R[RL.f + D];
-    lwave_sync();
-    // Sturm count first: an ill-determined count (or fewer than the two real
+  for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
+    // Sturm counts first: an ill-determined count (or fewer than the two real
     // roots every non-constant P has) sends the frequency on without Newton
-    int raw;
-    int cnt = D > 64 ? sturm_count_dd(gv, gv1, D, lane, raw) : sturm_count_line_reg(gv, gtop, D, lane, raw);
-    if (cnt < 2) cnt = -1;
-    const double phi0 = R[RL.meta + M_PHI0];
-    double u = 0.0;
-    int sg = 1;
-    bool conv = false, live = cnt >= 0 && lane < NS;
-    int its = 0;
-    double prev_step = 1.0;
-    if (live) {
-      const bool seeded = L.seeds_out && lane < S;
-      double bc = 1.0, bs = 0.0, ang;
-      if (seeded) {
-        const float* o = L.seeds_out + w * 2 * S;
-        bc = (double)o[2 * lane];
-        bs = (double)o[2 * lane + 1];
-        ang = -(R[RL.meta + M_CANON] + phi0);
+    const int row = NC > 1 ? lane >> 4 : 0;
+    bool mine = w0 + row < L.np;
+    double* Rr = L.rec + (w0 + (mine ? row : 0)) * (int64_t)RL.stride;
+    const int st = (int)Rr[RL.meta + M_STATUS];
+    mine = mine && st != ST_BAD_LC && st != ST_CONSTANT;
+    if (__ballot(mine) == 0ull) continue;
+    int cnts = -1, raw;
+    if (!(L.flags & 1u)) {
+      if constexpr (NC > 1) {
+        cnts = sturm_count_dd(Rr + RL.f, mine, D, lane, raw);
       } else {
-        ang = (L.seeds_out ? (lane - S + 0.5) * (kTwoPi / (NS - S)) : (lane + 0.5) * (kTwoPi / NS)) - phi0;
-      }
-      double s1, c1;
-      sincos_small(ang, s1, c1);
-      u_from_dir(fma(bc, c1, -bs * s1), fma(bc, s1, bs * c1), u, sg);
-    }
-    bool done = cnt < 0;
-    unsigned long long um = 0ull, merged = 0ull, U = 0ull;
-    for (int it = 1; it <= 12 && !done; ++it) {
-      if (live && !conv) {
-        bool ok;
-        const double sc = newton_u_step(sg > 0 ? sml : sml + FS, DP, K, u, sg, ok);
-        if (!ok) {
-          live = false;
-        } else {
-          ++its;
-          if (newton_settled(sc, prev_step)) conv = true;
-        }
-      }
-      if (it >= 2) {
-        const unsigned long long cm = __ballot(conv);
-        // fewer converged lanes than the count cannot reach it (the last
-        // check always runs: its roots seed the fallback)
-        if (__popcll(cm) < cnt && it < 12) continue;
-        const double key = sg > 0 ? u : copysign(2.0, u) - u;
-        for (unsigned long long pend = cm & ~merged; pend;) {
-          const int jj = __builtin_ctzll(pend);
-          const double kj = lrdlane(key, jj), uj = lrdlane(u, jj);
-          const double tol = 0.5e-8 * fma(uj, uj, 1.0);
-          const unsigned long long bit = 1ull << jj;
-          const unsigned long long same = __ballot(fabs(key - kj) < tol) & cm;
-          const unsigned long long upto = (bit << 1) - 1ull;
-          U &= upto | ~same;
-          U = (same & (bit - 1ull)) ? (U & ~bit) : (U | bit);
-          pend &= ~(same | bit);
-        }
-        merged = cm;
-        um = U;
-        if (__popcll(um) == cnt) {
-          done = true;
-          live = false;
-        }
+        const double gv = lane <= D ? Rr[RL.f + lane] : 0.0;
+        cnts = sturm_count_line_reg(gv, Rr[RL.f + D], D, lane, raw);
       }
     }
-    iters_acc += (unsigned long long)wave_sum((double)(lane < NS ? its : 0));
-    const double thw = theta_from_u(phi0, u, sg);
-    const int nu = __popcll(um);
-    const bool uniq = (um >> lane) & 1ull;
-    if (cnt >= 0 && cnt == nu) {
-      double* cand = R + RL.cand;
-      for (int c = lane; c < D; c += 64) cand[c] = __longlong_as_double(0x7ff8000000000000ll);
+    if (cnts < 2) cnts = -1;
+    if (!mine) cnts = -2;
+#pragma unroll 1
+    for (int p = 0; p < NC; ++p) {
+      const int cnt = __builtin_amdgcn_readlane(cnts, 16 * p);
+      if (cnt == -2) continue;
+      const int64_t w = w0 + p;
+      double* R = L.rec + w * (int64_t)RL.stride;
+      if (L.flags & 1u) {   // forced fallback
+        if (lane == 0) {
+          const unsigned slot = atomicAdd(L.fb_count, 1u);
+          L.fb_list[slot] = w;
+          R[RL.meta + M_FALLBACK] = 1.0;
+          R[RL.meta + M_WARM] = 0.0;
+          R[RL.meta + M_COUNT] = -1.0;
+        }
+        ++fb_acc;
+        continue;
+      }
+      for (int c = lane; c <= DP; c += 64) {
+        const double fc = c <= D ? R[RL.f + c] : 0.0;
+        sml[c] = fc;
+        sml[FS + (c <= D ? D - c : c)] = fc;
+      }
       lwave_sync();
-      if (uniq) cand[__popcll(um & below)] = thw;
-      roots_acc += (unsigned long long)nu;
-    } else {
-      // the distinct roots Newton did find start the Aberth iteration
-      if (uniq) R[RL.cand + __popcll(um & below)] = thw;
-      if (lane == 0) {
-        R[RL.meta + M_WARM] = (double)nu;
-        R[RL.meta + M_COUNT] = (double)cnt;
-        R[RL.meta + M_FALLBACK] = 1.0;
-        const unsigned slot = atomicAdd(L.fb_count, 1u);
-        L.fb_list[slot] = w;
+      const double phi0 = R[RL.meta + M_PHI0];
+      double u = 0.0;
+      int sg = 1;
+      bool conv = false, live = cnt >= 0 && lane < NS;
+      int its = 0;
+      double prev_step = 1.0;
+      if (live) {
+        const bool seeded = L.seeds_out && lane < S;
+        double bc = 1.0, bs = 0.0, ang;
+        if (seeded) {
+          const float* o = L.seeds_out + w * 2 * S;
+          bc = (double)o[2 * lane];
+          bs = (double)o[2 * lane + 1];
+          ang = -(R[RL.meta + M_CANON] + phi0);
+        } else {
+          ang = (L.seeds_out ? (lane - S + 0.5) * (kTwoPi / (NS - S)) : (lane + 0.5) * (kTwoPi / NS)) - phi0;
+        }
+        double s1, c1;
+        sincos_small(ang, s1, c1);
+        u_from_dir(fma(bc, c1, -bs * s1), fma(bc, s1, bs * c1), u, sg);
       }
-      ++fb_acc;
+      bool done = cnt < 0;
+      unsigned long long um = 0ull, merged = 0ull, U = 0ull;
+      for (int it = 1; it <= 12 && !done; ++it) {
+        if (live && !conv) {
+          bool ok;
+          const double sc = newton_u_step(sg > 0 ? sml : sml + FS, DP, K, u, sg, ok);
+          if (!ok) {
+            live = false;
+          } else {
+            ++its;
+            if (newton_settled(sc, prev_step)) conv = true;
+          }
+        }
+        if (it >= 2) {
+          const unsigned long long cm = __ballot(conv);
+          // fewer converged lanes than the count cannot reach it (the last
+          // check always runs: its roots seed the fallback)
+          if (__popcll(cm) < cnt && it < 12) continue;
+          const double key = sg > 0 ? u : copysign(2.0, u) - u;
+          for (unsigned long long pend = cm & ~merged; pend;) {
+            const int jj = __builtin_ctzll(pend);
+            const double kj = lrdlane(key, jj), uj = lrdlane(u, jj);
+            const double tol = 0.5e-8 * fma(uj, uj, 1.0);
+            const unsigned long long bit = 1ull << jj;
+            const unsigned long long same = __ballot(fabs(key - kj) < tol) & cm;
+            const unsigned long long upto = (bit << 1) - 1ull;
+            U &= upto | ~same;
+            U = (same & (bit - 1ull)) ? (U & ~bit) : (U | bit);
+            pend &= ~(same | bit);
+          }
+          merged = cm;
+          um = U;
+          if (__popcll(um) == cnt) {
+            done = true;
+            live = false;
+          }
+        }
+      }
+      iters_acc += (unsigned long long)wave_sum((double)(lane < NS ? its : 0));
+      const double thw = theta_from_u(phi0, u, sg);
+      const int nu = __popcll(um);
+      const bool uniq = (um >> lane) & 1ull;
+      if (cnt >= 0 && cnt == nu) {
+        double* cand = R + RL.cand;
+        for (int c = lane; c < D; c += 64) cand[c] = __longlong_as_double(0x7ff8000000000000ll);
+        lwave_sync();
+        if (uniq) cand[__popcll(um & below)] = thw;
+        roots_acc += (unsigned long long)nu;
+      } else {
+        // the distinct roots Newton did find start the Aberth iteration
+        if (uniq) R[RL.cand + __popcll(um & below)] = thw;
+        if (lane == 0) {
+          R[RL.meta + M_WARM] = (double)nu;
+          R[RL.meta + M_COUNT] = (double)cnt;
+          R[RL.meta + M_FALLBACK] = 1.0;
+          const unsigned slot = atomicAdd(L.fb_count, 1u);
+          L.fb_list[slot] = w;
+        }
+        ++fb_acc;
+      }
+      lwave_sync();
     }
-    lwave_sync();
   }
   if (lane == 0 && a.counters) {
     SolveCounters* c = counter_slot(a.counters);
@@ -990,7 +1057,7 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
   const int lane = threadIdx.x & 63;
   const int D = 6 * H - 2;
   const RecLayout RL(H);
-  const int G = D < 64 ? sturm_group(D) : 64;
+  const int G = D < 64 ? sturm_group(D) : (D > 64 ? 16 : 64);
   const int per = 64 / G;
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < np; w0 += per * (int64_t)gridDim.x) {
     int cnt;
@@ -1005,12 +1072,17 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
       cnt = G == 8 ? sturm_count_groups<8>(C, gtop, D, lane, raw) : sturm_count_groups<16>(C, gtop, D, lane, raw);
       if (cnt < 0) cnt = -1000 - raw;
       cnt = __shfl(cnt, (lane * G) & 63);   // pair `lane` of the group to lane `lane`
+    } else if (D > 64) {
+      const int row = lane >> 4;
+      const bool in = w0 + row < np;
+      int raw;
+      cnt = sturm_count_dd(rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f, in, D, lane, raw);
+      if (cnt < 0) cnt = -1000 - raw;
+      cnt = __shfl(cnt, (lane * 16) & 63);
     } else {
       const double* RA = rec + w0 * (int64_t)RL.stride;
-      const double gv = RA[RL.f + lane];
-      const double gv1 = lane + 64 <= D ? RA[RL.f + 64 + lane] : 0.0;
       int raw;
-      cnt = D > 64 ? sturm_count_dd(gv, gv1, D, lane, raw) : sturm_count_line_reg(gv, RA[RL.f + D], D, lane, raw);
+      cnt = sturm_count_line_reg(RA[RL.f + lane], RA[RL.f + D], D, lane, raw);
       if (cnt < 0) cnt = -1000 - raw;
     }
     if (lane < per && w0 + lane < np) {
@@ -1189,8 +1261,12 @@ hipError_t launch_newton_sturm(const SolveArgs& a, const LearnArgs& L, int waves
     FTP_NEWTON(6) FTP_NEWTON(7) FTP_NEWTON(8) FTP_NEWTON(9) FTP_NEWTON(10)
 #undef FTP_NEWTON
     default:
-      hipExtLaunchKernelGGL(k_newton_sturm, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr, done, 0,
-                            a, L);
+      if (a.H == 11)
+        hipExtLaunchKernelGGL(k_newton_sturm<1>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
+                              done, 0, a, L);
+      else
+        hipExtLaunchKernelGGL(k_newton_sturm<4>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
+                              done, 0, a, L);
   }
   return hipGetLastError();
 }
