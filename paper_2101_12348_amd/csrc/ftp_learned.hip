@@ -442,6 +442,7 @@ __device__ __forceinline__ double with_sign(double v, int signbit) {
 template <int G, int R, int RQ>
 __device__ __forceinline__ void sturm_rows_step(double (&A)[4], const double (&B)[4], SturmSigns& S, SturmTests<G>& T,
                                                 int db, int l, int gb4) {
+#pragma clang fp contract(off)
   constexpr int RL = (RQ + R - 1) % R;
   const int lq = db / R, ll = (db - 1) / R;   // (R a power of two)
   const double ab = from_hiword(S.ab ^ kHi1);
@@ -498,6 +499,9 @@ __device__ __forceinline__ void sturm_repack(double (&X)[4], int l, int gb4) {
 // must be active.
 template <int G>
 __device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double gtop, int D, int lane, int& raw) {
+  // (a chain that ends near the thresholds of its tests turns on its last bits: no
+  // contraction, which known signs and degrees would open or close)
+#pragma clang fp contract(off)
   const int l = lane & (G - 1), gb4 = (lane & ~(G - 1)) << 2;
   double A[4], B[4];
   SturmSigns S;
@@ -505,7 +509,7 @@ __device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double g
   bool ok;
   {
     const double ag = fabs(gtop), sgn = gtop > 0.0 ? 1.0 : -1.0;
-    const double sa = fast_rcp_d(ag + 1e-300), sb = fast_rcp_d(D * ag + 1e-300);
+    const double sa = fast_rcp_d(ag + 1e-300), sb = fast_rcp_d(fma((double)D, ag, 1e-300));
     ok = ag > 0.0 && ag < INFINITY;
     int hA = 0, hB = 0;
     const double up = dpp_d<0x101>(C[0]);   // row_shl:1: coefficient 4 (l + 1) (used up to coefficient D)
