@@ -1356,19 +1356,23 @@ int plan_create_impl(ftp_plan** out, int n_band, int H, const double* c, const d
     return FTP_E_HIP;
   }
   const int D = 6 * H - 2;
-  if (D < 64) {
-    std::vector<double> ct = cayley_table(D);
+  {
+    std::vector<double> ct;
+    if (D < 64) ct = cayley_table(D);
     append_products(ct, H, al.data());
     // (then the first round's starts: 32 iterates for each of sixteen rotations)
-    const size_t nt_starts = sizeof(double2) * 16 * 32;
+    const size_t nt_starts = D < 64 ? sizeof(double2) * 16 * 32 : 0;
     if ((rc = P->ctab.ensure(sizeof(double) * ct.size() + nt_starts))) {
       delete P;
       return rc;
     }
-    P->starts = reinterpret_cast<double2*>(P->ctab.as<double>() + ct.size());
-    if (launch_start_table(P->starts, H, (P->opt.flags & FTP_FLAG_2H_STARTS) != 0, nullptr) != hipSuccess ||
-        hipStreamSynchronize(nullptr) != hipSuccess ||
-        hipMemcpy(P->ctab.p, ct.data(), sizeof(double) * ct.size(), hipMemcpyHostToDevice) != hipSuccess) {
+    bool ok = hipMemcpy(P->ctab.p, ct.data(), sizeof(double) * ct.size(), hipMemcpyHostToDevice) == hipSuccess;
+    if (ok && D < 64) {
+      P->starts = reinterpret_cast<double2*>(P->ctab.as<double>() + ct.size());
+      ok = launch_start_table(P->starts, H, (P->opt.flags & FTP_FLAG_2H_STARTS) != 0, nullptr) == hipSuccess &&
+           hipStreamSynchronize(nullptr) == hipSuccess;
+    }
+    if (!ok) {
       g_last_error = "plan setup copy failed";
       delete P;
       return FTP_E_HIP;

@@ -31,14 +31,6 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// Value of v in lane `src` (src must be wave-uniform).
-__device__ __forceinline__ double rdlane(double v, int src) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(unsigned)(u & 0xffffffffull), src);
-  const int hi = __builtin_amdgcn_readlane((int)(unsigned)(u >> 32), src);
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
-}
-
 // f_c = sum_j rc[j] T[c][j], j = 0..K, over row c of the Cayley table (rows of
 // cayley_row(K) doubles, 16-byte aligned like rc), in two sums, even and odd j.
 __device__ __forceinline__ double cayley_dot(const double* rc, const double* row, int K) {
@@ -58,38 +50,7 @@ __device__ __forceinline__ double cayley_dot(const double* rc, const double* row
 
 // ------------------------------------------------------------- assemble
 
-__host__ __device__ inline size_t asm_lds_bytes(int H, int nb) {
-  const int K = 3 * H - 1, D = 2 * K;
-  return (size_t)(2 * ((3 * H + 1) + (2 * H + 1) + (H + 1) + (K + 1) + 4 * (D + 1) + H)) * sizeof(double) +
-         (size_t)nb * (3 * H + (2 * H + 1) + H + 1) * sizeof(double2);
-}
-
-// W: per-pair work arrays; hb, vb: Horner buffers; shared phase: Zb (band
-// sums, nb x 3H), T (template products, nb x (2H + 1)), alb (templates,
-// nb x H), wsb (the bands' weight shares, nb).
-struct AsmLayout { FreqWork W; double2* hb[2]; double2* vb[2]; double2* Zb; double2* T; double2* alb; double2* wsb; };
-
-__device__ __forceinline__ AsmLayout asm_layout(double* sm, int H, int nb) {
-  const int K = 3 * H - 1, D = 2 * K;
-  AsmLayout s;
-  double2* q = reinterpret_cast<double2*>(sm);
-  s.W.Z = q; q += 3 * H + 1;
-  s.W.mu = q; q += 2 * H + 1;
-  s.W.eta = q; q += H + 1;
-  s.W.r = q; q += K + 1;
-  s.hb[0] = q; q += D + 1;
-  s.hb[1] = q; q += D + 1;
-  s.vb[0] = q; q += D + 1;
-  s.vb[1] = q; q += D + 1;
-  s.W.al = q; q += H;
-  s.Zb = q; q += nb * 3 * H;
-  s.T = q; q += nb * (2 * H + 1);
-  s.alb = q; q += nb * H;
-  s.wsb = q;
-  return s;
-}
-
-// Compact per-frequency working set of k_assemble2 (single band, D < 64):
+// Per-frequency working set of k_assemble:
 // Z, mu, eta, r and a scratch of 8H + 2 complex values (assemble_r's MM and YM
 // coefficient rows; later the rotated 2 rho_j, two rows of cayley_row(K)).
 __host__ __device__ inline int asm2_doubles(int H) {
@@ -106,29 +67,32 @@ __device__ __forceinline__ FreqWork asm2_layout(double* sm, int H, double2*& scr
   scr = q;
   return W;
 }
-// Waves per workgroup of k_assemble2: they share one LDS copy of the Cayley
+// Waves per workgroup of k_assemble: they share one LDS copy of the Cayley
 // table (14 KB at H = 10) and of the template's products, which the loops read
 // with LDS latency instead of the L2's.
 constexpr int kAsmWaves = 4;
-// Lanes per frequency of k_assemble2: sixteen where 3H and 2H + 1 fit them.
+// Lanes per frequency of k_assemble: sixteen where 3H and 2H + 1 fit them.
 __host__ __device__ inline constexpr int asm_group(int H) { return H <= 5 ? 16 : 32; }
+// Doubles of the Cayley table in LDS (none above H = 10, whose f comes by Horner).
+__host__ __device__ inline int cayley_doubles(int H) {
+  const int K = 3 * H - 1;
+  return 2 * K < 64 ? (2 * K + 1) * cayley_row(K) : 0;
+}
 __host__ __device__ inline int asm2_table_doubles(int H) {
-  const int K = 3 * H - 1, D = 2 * K;
-  return (D + 1) * cayley_row(K) + 2 * template_products(H) + 2 * H;
+  return cayley_doubles(H) + 2 * template_products(H) + 2 * H;
 }
 // nb > 0 (shared-phase bands): the Cayley table, then per band the 2H + 1
 // template products, the template and the weight share; per frequency the
 // bands' sums as well.
 __host__ __device__ inline int asm2_band_doubles(int H, int nb) {
-  const int K = 3 * H - 1;
-  return (2 * K + 1) * cayley_row(K) + 2 * nb * (3 * H + 2);
+  return cayley_doubles(H) + 2 * nb * (3 * H + 2);
 }
-__host__ __device__ inline size_t asm2_lds_bytes(int H, int nb) {
+__host__ __device__ inline size_t asm2_lds_bytes(int H, int nb, int waves) {
   const int tab = nb ? asm2_band_doubles(H, nb) : asm2_table_doubles(H);
-  return ((size_t)tab + (size_t)kAsmWaves * (64 / asm_group(H)) * (asm2_doubles(H) + nb * 6 * H)) * sizeof(double);
+  return ((size_t)tab + (size_t)waves * (64 / asm_group(H)) * (asm2_doubles(H) + nb * 6 * H)) * sizeof(double);
 }
 
-// mu_e, e = 0..2H, of MM from the sums (see assemble_poly), on a group of nl
+// mu_e, e = 0..2H, of MM from the sums, on a group of nl
 // lanes, lane per e.  The pairs (n, m) of e are run in one loop: n + m = e first,
 // then n - m = e (m = |e - n|; conjugating Z_m turns the first form into the
 // second), with the template's factors alpha_n alpha_m and 2 alpha_n conj(alpha_m)
@@ -179,7 +143,7 @@ __device__ __forceinline__ void assemble_mu(const FreqWork& W, int H, int lane, 
 //   mu_e = sum_b conj(Z^b_e) T^b_e - C_e,
 // T^b_e = sum_{n+m=e} alpha^b_n alpha^b_m + 2 sum_{n-m=e} alpha^b_n conj(alpha^b_m)
 // (T^b_0 = 2 sum_n |alpha^b_n|^2) the band's sum of M^2, and C_e the same
-// products of B (Mbar^2).  One band reduces to assemble_poly.  W.Z[1..H]
+// products of B (Mbar^2).  One band reduces to assemble_mu.  W.Z[1..H]
 // receive conj(B_n), which the scoring uses with unit alpha for Mbar.
 struct BandTables { const double2 *Zb, *T, *alb, *wsb; };
 __device__ __forceinline__ void band_tables(double2* alb, double2* wsb, double2* T, const SolveArgs& a, int tid, int nt) {
@@ -236,184 +200,6 @@ __device__ __forceinline__ void assemble_shared(const BandTables& S, const FreqW
   wave_sync();
 }
 
-// Load the 3H sums of pair pidx (frequency index j of lightcurve L) into W.Z.
-template <typename R>
-__device__ __forceinline__ void load_sums(const SolveArgs& a, const LcInfo& L, int64_t pidx, int64_t j,
-                                          const FreqWork& W, int lane) {
-  const int H = a.H;
-  if (lane == 0) W.Z[0] = make_double2(1.0, 0.0);
-  if (a.sums_in) {
-    for (int q = lane; q < 3 * H; q += 64) {
-      const double* s = a.sums_in + (pidx * 3 * H + q) * 2;
-      double2 v = make_double2(s[0], s[1]);
-      if (q >= 2 * H) v = cscale(v, L.inv_sqrt_yy);
-      W.Z[q + 1] = v;
-    }
-  } else {
-    const typename Cplx<R>::T* grids = reinterpret_cast<const typename Cplx<R>::T*>(a.grids);
-    for (int q = lane; q < 3 * H; q += 64) {
-      const int g = q < 2 * H ? 0 : 1;
-      const int k = g == 0 ? q + 1 : q - 2 * H + 1;
-      W.Z[q + 1] = gather_mode<R>(L, g, (int64_t)k * j, grids);
-    }
-  }
-  wave_sync();
-}
-
-// Sums -> polynomial record for pairs [p0, p0 + np) of the chunk.
-// At least four waves per SIMD (at most 128 VGPRs): the kernel is bound by
-// VALU issue and latency, and the register count otherwise drifts just above 128.
-template <typename R>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_assemble(SolveArgs a, double* rec, int64_t p0, int64_t np) {
-  extern __shared__ double sma[];
-  const int lane = wave_lane();
-  if (a.clear8 && blockIdx.x == 0 && lane < 8) a.clear8[lane] = 0u;
-  const int H = a.H, K = 3 * H - 1, D = 2 * K;
-  const RecLayout RL(H);
-  const int nb = a.n_band;
-  AsmLayout S = asm_layout(sma, H, nb);
-  const FreqWork& W = S.W;
-  if (nb == 0) {
-    for (int q = lane; q < H; q += 64) S.W.al[q] = a.alpha[q];
-  } else {
-    band_tables(S.alb, S.wsb, S.T, a, lane, 64);
-  }
-  wave_sync();
-  // e^{2 pi i m / 16}, m = lane mod 16: the rotation phases d phi0 are
-  // multiples of 2 pi / 16, read from here by lane index
-  double tab_c, tab_s;
-  sincos(kTwoPi * (lane & 15) / 16.0, &tab_s, &tab_c);
-  for (int64_t w = blockIdx.x; w < np; w += gridDim.x) {
-    const int64_t pidx = p0 + w;
-    double* Rr = rec + w * (int64_t)RL.stride;
-    const int64_t lc = pair_lc(a, pidx);
-    const LcInfo& L = a.lcs[lc];
-    const int64_t j = pidx - a.freq_off[lc] + 1;
-    if (L.status != 0) {
-      if (lane == 0) {
-        Rr[RL.meta + M_STATUS] = (double)ST_BAD_LC;
-        Rr[RL.meta + M_LC] = (double)lc;
-        Rr[RL.meta + M_FALLBACK] = 0.0;
-        Rr[RL.meta + M_WARM] = 0.0;
-      }
-      continue;
-    }
-    const double ref = ref_cycles(j, L.df, L.tref);
-    if (nb == 0) {
-      load_sums<R>(a, L, pidx, j, W, lane);
-      assemble_poly(W, H, lane, S.hb[0]);
-    } else {
-      // every band's sums of this frequency (grids of lightcurves 0..nb-1)
-      const typename Cplx<R>::T* grids = reinterpret_cast<const typename Cplx<R>::T*>(a.grids);
-      for (int q = lane; q < nb * 3 * H; q += 64) {
-        const int b = q / (3 * H), qq = q % (3 * H);
-        const int g = qq < 2 * H ? 0 : 1;
-        const int k = g == 0 ? qq + 1 : qq - 2 * H + 1;
-        S.Zb[q] = gather_mode<R>(a.lcs[b], g, (int64_t)k * j, grids);
-      }
-      wave_sync();
-      assemble_shared(BandTables{S.Zb, S.T, S.alb, S.wsb}, W, nb, H, lane, 64);
-      assemble_r(W, H, lane, S.hb[0]);
-    }
-    double rmax = 0.0, mumax = 0.0, etamax = 0.0;
-    // (largest squared magnitudes, one square root each: sqrt is monotone and
-    // correctly rounded, so this is the largest magnitude)
-    for (int d = lane; d <= K; d += 64) rmax = fmax(rmax, cabs2(W.r[d]));
-    for (int e = lane; e <= 2 * H; e += 64) mumax = fmax(mumax, cabs2(W.mu[e]));
-    for (int k = lane; k <= H; k += 64) etamax = fmax(etamax, cabs2(W.eta[k]));
-    rmax = sqrt(rmax);
-    mumax = sqrt(mumax);
-    etamax = sqrt(etamax);
-    // maxima from the doubles' high words (within 2^-20): the threshold
-    // below only separates R = 0 from rounding noise
-    rmax = wave_max_abs_hi(rmax);
-    mumax = wave_max_abs_hi(mumax);
-    etamax = wave_max_abs_hi(etamax);
-    const double rscale = mumax * etamax * (6.0 * H) * (2.0 * H + 1.0);
-    const bool constant = !(rmax > 64.0 * kEps * rscale);
-    double phi0 = 0.0;
-    if (!constant) {
-      double Rv = -1.0;
-      if (lane < 16) Rv = fabs(eval_R_value(W, H, kTwoPi * lane / 16.0 + kPi));
-      const double rm = wave_max(Rv);
-      const unsigned long long mask = __ballot(lane < 16 && Rv == rm);
-      const int k0 = __ffsll((long long)mask) - 1;
-      phi0 = kTwoPi * k0 / 16.0;
-      // f(x) = sum_j rho_{j-K} u^j v^{2K-j}, u = 1 + i x, v = 1 - i x,
-      // rho_d = r_d e^{i d phi0}; homogeneous Horner h_l = u h_{l-1} + rho_{K-l} v^l
-      const double cK = rdlane(tab_c, (K * k0) & 15), sK = rdlane(tab_s, (K * k0) & 15);
-      if (D < 64) {
-        // f_c = sum_j (rho_{j-K}.x or .y) T[j][c] with the Cayley-map table
-        // (coefficient c of u^j v^(D-j), u = 1 + i x, v = 1 - i x, divided by
-        // i^c), whose terms j and D - j are equal (the table keeps rows j <=
-        // K): f_c = sum_{j<K} 2 rho'_j T[j][c] + rho'_K T[K][c].  Lane j forms
-        // 2 rho_{j-K} (rho_0 once), lane c the dot product of column c.
-        double* rx = reinterpret_cast<double*>(S.hb[0]);
-        double* ry = rx + cayley_row(K);
-        {
-          const int d = lane - K;
-          const double ec = __shfl(tab_c, (d * k0) & 15), es = __shfl(tab_s, (d * k0) & 15);
-          if (lane <= K) {
-            const double2 rho = cmul(cconj(W.r[-d]), make_double2(ec, es));
-            const double wgt = lane < K ? 2.0 : 1.0;
-            rx[lane] = wgt * rho.x;
-            ry[lane] = wgt * rho.y;
-          }
-        }
-        wave_sync();
-        if (lane <= D) {
-          const double* rc = (lane & 1) ? ry : rx;
-          Rr[RL.f + lane] = cayley_dot(rc, a.ctab + lane * cayley_row(K), K);
-        }
-      } else {
-        for (int c = lane; c <= D; c += 64) {
-          S.hb[0][c] = c == 0 ? cmul(W.r[K], make_double2(cK, sK)) : make_double2(0.0, 0.0);
-          S.vb[0][c] = c == 0 ? make_double2(1.0, 0.0) : make_double2(0.0, 0.0);
-        }
-        wave_sync();
-        for (int l = 1; l <= D; ++l) {
-          const int d = K - l;
-          const double2 rd = d >= 0 ? W.r[d] : cconj(W.r[-d]);
-          const int m = (d * k0) & 15;
-          const double2 rho = cmul(rd, make_double2(rdlane(tab_c, m), rdlane(tab_s, m)));
-          const double2* hsrc = (l & 1) ? S.hb[0] : S.hb[1];
-          const double2* vsrc = (l & 1) ? S.vb[0] : S.vb[1];
-          double2* hdst = (l & 1) ? S.hb[1] : S.hb[0];
-          double2* vdst = (l & 1) ? S.vb[1] : S.vb[0];
-          for (int c = lane; c <= D; c += 64) {
-            const double2 vprev = c > 0 ? vsrc[c - 1] : make_double2(0.0, 0.0);
-            const double2 hprev = c > 0 ? hsrc[c - 1] : make_double2(0.0, 0.0);
-            const double2 vnew = make_double2(vsrc[c].x + vprev.y, vsrc[c].y - vprev.x);
-            const double2 hnew = make_double2(hsrc[c].x - hprev.y, hsrc[c].y + hprev.x);
-            vdst[c] = vnew;
-            hdst[c] = cadd(hnew, cmul(rho, vnew));
-          }
-          wave_sync();
-        }
-        const double2* hfin = (D & 1) ? S.hb[1] : S.hb[0];
-        for (int c = lane; c <= D; c += 64) Rr[RL.f + c] = hfin[c].x;
-      }
-    }
-    for (int d = lane; d <= K; d += 64) { Rr[RL.r + 2 * d] = W.r[d].x; Rr[RL.r + 2 * d + 1] = W.r[d].y; }
-    for (int e = lane; e <= 2 * H; e += 64) { Rr[RL.mu + 2 * e] = W.mu[e].x; Rr[RL.mu + 2 * e + 1] = W.mu[e].y; }
-    for (int k = lane; k < H; k += 64) {
-      Rr[RL.eta + 2 * k] = W.eta[k + 1].x;
-      Rr[RL.eta + 2 * k + 1] = W.eta[k + 1].y;
-      Rr[RL.zw + 2 * k] = W.Z[k + 1].x;
-      Rr[RL.zw + 2 * k + 1] = W.Z[k + 1].y;
-    }
-    if (lane == 0) {
-      Rr[RL.meta + M_PHI0] = phi0;
-      Rr[RL.meta + M_REF] = ref;
-      Rr[RL.meta + M_STATUS] = constant ? (double)ST_CONSTANT : (double)ST_OK;
-      Rr[RL.meta + M_LC] = (double)lc;
-      Rr[RL.meta + M_FALLBACK] = 0.0;
-      Rr[RL.meta + M_WARM] = 0.0;
-    }
-    wave_sync();
-  }
-}
-
 // Maximum over a group of GL lanes (16 or 32), in every lane of it: of an int,
 // and of a double.
 template <int GL>
@@ -444,7 +230,56 @@ __device__ __forceinline__ int abs2_hi(double2 z) {
   return (int)((unsigned long long)__double_as_longlong(cabs2(z)) >> 32) & 0x7fffffff;
 }
 
-// Several frequencies per wavefront (D < 64; sums from the grids, given, or of
+// Above H = 10 the products of the Cayley table would not be exact; f(x) = sum_j
+// rho_{j-K} u^j v^(D-j), u = 1 + i x, v = 1 - i x, comes by homogeneous Horner, h <-
+// u h + rho_{K-l} v^l.  With the powers of i taken out (h_c = i^c g_c, v^l's
+// coefficient c = i^c V_c) both recurrences are real shifts: g_c += g_{c-1},
+// V_c -= V_{c-1}, then g_c += rho V_c.  Lane hl of 32 holds c = 3 hl..3 hl + 2 (D <
+// 95, so the next group's first lane receives V = 0 by itself).  Against 64 lanes
+// exchanging h and v through LDS for one frequency: the assembly of 50 thousand
+// frequencies at H = 13 806 -> 203 us.
+__device__ __forceinline__ void f_by_horner(const FreqWork& W, double2* rho, int K, int D, int hl, int k0, double tab_c,
+                                            double tab_s, bool write, double* f) {
+#pragma clang fp contract(off)
+  for (int l0 = 0; l0 <= D; l0 += 32) {
+    const int l = l0 + hl, d = K - l;
+    const double ec = __shfl(tab_c, (d * k0) & 15), es = __shfl(tab_s, (d * k0) & 15);
+    if (l <= D) {
+      const double2 r = W.r[d < 0 ? -d : d], rd = make_double2(r.x, d < 0 ? -r.y : r.y);
+      rho[l] = make_double2(fma(rd.x, ec, -(rd.y * es)), fma(rd.y, ec, rd.x * es));
+    }
+  }
+  wave_sync();
+  const double2 r0 = rho[0];
+  double v0 = hl == 0 ? 1.0 : 0.0, v1 = 0.0, v2 = 0.0;
+  double x0 = hl == 0 ? r0.x : 0.0, x1 = 0.0, x2 = 0.0, y0 = hl == 0 ? r0.y : 0.0, y1 = 0.0, y2 = 0.0;
+#pragma unroll 2
+  for (int l = 1; l <= D; ++l) {
+    const double2 r = rho[l];
+    const double xs = lane_shr1(x2), ys = lane_shr1(y2), vp = lane_shr1(v2);
+    const double xp = hl == 0 ? 0.0 : xs, yp = hl == 0 ? 0.0 : ys;
+    v2 = v2 - v1;
+    v1 = v1 - v0;
+    v0 = v0 - vp;
+    x2 = (x2 + x1) + r.x * v2;
+    x1 = (x1 + x0) + r.x * v1;
+    x0 = (x0 + xp) + r.x * v0;
+    y2 = (y2 + y1) + r.y * v2;
+    y1 = (y1 + y0) + r.y * v1;
+    y0 = (y0 + yp) + r.y * v0;
+  }
+  // f_c = Re(i^c g_c)
+  const double gx[3] = {x0, x1, x2}, gy[3] = {y0, y1, y2};
+#pragma unroll
+  for (int s = 0; s < 3; ++s) {
+    const int c = 3 * hl + s;
+    const double v = (c & 1) ? gy[s] : gx[s];
+    if (write && c <= D) f[c] = ((c + 1) & 2) ? -v : v;
+  }
+  wave_sync();
+}
+
+// Several frequencies per wavefront (sums from the grids, given, or of
 // shared-phase bands), one per group of GL lanes with its own LDS working set: two of 32 lanes,
 // or four of 16 where the template has at most five harmonics.  The assembly's
 // per-frequency loops have 3H, 2H + 1, K + 1 or 16 lanes of work, which a group
@@ -466,7 +301,7 @@ __device__ __forceinline__ int abs2_hi(double2 z) {
 // HT: H, or 0 to take it from the arguments.  MODE: the sums' source.
 enum { kFromGrids = 0, kFromSums = 1, kFromBands = 2 };
 template <typename R, int GL, int HT, int MODE>
-__global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_assemble2(SolveArgs a, double* rec,
+__global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(4))) void k_assemble(SolveArgs a, double* rec,
                                                                                           int64_t p0, int64_t np) {
   extern __shared__ double sma[];
   constexpr int NG = 64 / GL;
@@ -474,12 +309,13 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
   if (a.clear8 && blockIdx.x == 0 && threadIdx.x < 8) a.clear8[threadIdx.x] = 0u;
   const int H = HT ? HT : a.H, K = 3 * H - 1, D = 2 * K;
   const RecLayout RL(H);
+  const int nwv = MODE == kFromBands ? blockDim.x >> 6 : kAsmWaves, nt = 64 * nwv;
   const int nb = MODE == kFromBands ? a.n_band : 0;
   // the Cayley table, the template's products and squares (or the bands'),
   // shared by the workgroup's waves
-  const int LR = cayley_row(K), nct = (D + 1) * LR;
+  const int LR = cayley_row(K), nct = cayley_doubles(H);
   const int ntab = MODE == kFromBands ? asm2_band_doubles(H, nb) : asm2_table_doubles(H);
-  for (int i = threadIdx.x; i < (MODE == kFromBands ? nct : ntab); i += 64 * kAsmWaves) sma[i] = a.ctab[i];
+  for (int i = threadIdx.x; i < (MODE == kFromBands ? nct : ntab); i += nt) sma[i] = a.ctab[i];
   const double* ctab = sma;
   const double2* prod = reinterpret_cast<const double2*>(sma + nct);
   const double* pn = sma + nct + 2 * template_products(H);
@@ -489,7 +325,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
   double2* const Zb = reinterpret_cast<double2*>(work + asm2_doubles(H));
   double2* const bt = reinterpret_cast<double2*>(sma + nct);
   const BandTables B{Zb, bt, bt + nb * (2 * H + 1), bt + nb * (3 * H + 1)};
-  if (MODE == kFromBands) band_tables(bt + nb * (2 * H + 1), bt + nb * (3 * H + 1), bt, a, threadIdx.x, 64 * kAsmWaves);
+  if (MODE == kFromBands) band_tables(bt + nb * (2 * H + 1), bt + nb * (3 * H + 1), bt, a, threadIdx.x, nt);
   __syncthreads();
   double tab_c, tab_s;
   sincos(kTwoPi * (lane & 15) / 16.0, &tab_s, &tab_c);
@@ -500,7 +336,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
   // MM, YM of order one: the squared threshold of the constant test below
   const double ctol = 64.0 * kEps * (6.0 * H) * (2.0 * H + 1.0), ctol2 = ctol * ctol;
   const typename Cplx<R>::T* grids = reinterpret_cast<const typename Cplx<R>::T*>(a.grids);
-  const int64_t gw = (int64_t)blockIdx.x * kAsmWaves + wv, nw = (int64_t)gridDim.x * kAsmWaves;
+  const int64_t gw = (int64_t)blockIdx.x * nwv + wv, nw = (int64_t)gridDim.x * nwv;
   for (int64_t w0 = NG * gw; w0 < np; w0 += NG * nw) {
     const bool has = w0 + g < np;                    // an empty group repeats the first
     const int64_t w = has ? w0 + g : w0;
@@ -572,28 +408,32 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
     const unsigned hm = (unsigned)(mask >> (lane & ~(GL - 1))) & 0xffffu;
     const int k0 = hm ? __ffs(hm) - 1 : 0;
     const double phi0 = constant ? 0.0 : kTwoPi * k0 / 16.0;
-    // 2 rho_j = 2 r_{j-K} e^{i (j-K) phi0}, j = 0..K - 1, and rho_K (every lane
-    // takes part in the table reads), then the dot products over j <= K (the
-    // terms j and D - j are equal)
-    double* rx = reinterpret_cast<double*>(scr);
-    double* ry = rx + LR;
-    for (int jx = hl; jx < ((K + GL) & ~(GL - 1)); jx += GL) {
-#pragma clang fp contract(off)
-      const int d = jx - K;
-      const int m = (d * k0) & 15;
-      const double ec = __shfl(tab_c, m), es = __shfl(tab_s, m);
-      if (jx <= K) {
-        const double2 rd = W.r[-d];
-        const double wgt = jx < K ? 2.0 : 1.0;
-        rx[jx] = wgt * fma(rd.x, ec, rd.y * es);
-        ry[jx] = wgt * fma(rd.x, es, -(rd.y * ec));
-      }
-    }
-    wave_sync();
     const bool write = has && !bad;
-    for (int c = hl; c <= D; c += GL) {
-      const double fc = cayley_dot((c & 1) ? ry : rx, ctab + c * LR, K);
-      if (write && !constant) Rr[RL.f + c] = fc;
+    if (HT >= 11 || (HT == 0 && D >= 64)) {
+      f_by_horner(W, scr, K, D, hl, k0, tab_c, tab_s, write && !constant, Rr + RL.f);
+    } else {
+      // 2 rho_j = 2 r_{j-K} e^{i (j-K) phi0}, j = 0..K - 1, and rho_K (every lane
+      // takes part in the table reads), then the dot products over j <= K (the
+      // terms j and D - j are equal)
+      double* rx = reinterpret_cast<double*>(scr);
+      double* ry = rx + LR;
+      for (int jx = hl; jx < ((K + GL) & ~(GL - 1)); jx += GL) {
+#pragma clang fp contract(off)
+        const int d = jx - K;
+        const int m = (d * k0) & 15;
+        const double ec = __shfl(tab_c, m), es = __shfl(tab_s, m);
+        if (jx <= K) {
+          const double2 rd = W.r[-d];
+          const double wgt = jx < K ? 2.0 : 1.0;
+          rx[jx] = wgt * fma(rd.x, ec, rd.y * es);
+          ry[jx] = wgt * fma(rd.x, es, -(rd.y * ec));
+        }
+      }
+      wave_sync();
+      for (int c = hl; c <= D; c += GL) {
+        const double fc = cayley_dot((c & 1) ? ry : rx, ctab + c * LR, K);
+        if (write && !constant) Rr[RL.f + c] = fc;
+      }
     }
     if (write) {
       double2* r2 = reinterpret_cast<double2*>(Rr);
@@ -1157,44 +997,39 @@ __global__ void k_export_stats(const LcInfo* lcs, double* out) {
 // ------------------------------------------------------------ launchers
 
 template <typename R>
-static void launch_assemble2(const SolveArgs& a, double* rec, int64_t p0, int64_t np, unsigned wg, hipStream_t st) {
-  const dim3 grid(wg), block(64 * kAsmWaves);
-  const size_t lds = asm2_lds_bytes(a.H, a.n_band);
+static void launch_assemble_r(const SolveArgs& a, double* rec, int64_t p0, int64_t np, unsigned wg, int nw,
+                             hipStream_t st) {
+  const dim3 grid(wg), block(64 * nw);
+  const size_t lds = asm2_lds_bytes(a.H, a.n_band, nw);
   const bool g16 = asm_group(a.H) == 16;
   if (a.n_band) {
-    if (g16) hipLaunchKernelGGL((k_assemble2<R, 16, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
-    else hipLaunchKernelGGL((k_assemble2<R, 32, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
+    if (g16) hipLaunchKernelGGL((k_assemble<R, 16, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
+    else hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
     return;
   }
   if (a.sums_in) {
-    if (g16) hipLaunchKernelGGL((k_assemble2<double, 16, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
-    else hipLaunchKernelGGL((k_assemble2<double, 32, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
+    if (g16) hipLaunchKernelGGL((k_assemble<double, 16, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
+    else hipLaunchKernelGGL((k_assemble<double, 32, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
     return;
   }
   switch (a.H) {
-#define FTP_ASM(h) case h: hipLaunchKernelGGL((k_assemble2<R, asm_group(h), h, kFromGrids>), grid, block, lds, st, a, rec, p0, np); break;
+#define FTP_ASM(h) case h: hipLaunchKernelGGL((k_assemble<R, asm_group(h), h, kFromGrids>), grid, block, lds, st, a, rec, p0, np); break;
     FTP_ASM(1) FTP_ASM(2) FTP_ASM(3) FTP_ASM(4) FTP_ASM(5)
     FTP_ASM(6) FTP_ASM(7) FTP_ASM(8) FTP_ASM(9) FTP_ASM(10)
 #undef FTP_ASM
+    default: hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromGrids>), grid, block, lds, st, a, rec, p0, np);
   }
 }
 
 hipError_t launch_assemble(int precision, const SolveArgs& a, double* rec, int64_t p0, int64_t np, int waves,
                            hipStream_t st) {
-  if (6 * a.H - 2 < 64 && asm2_lds_bytes(a.H, a.n_band) <= ((size_t)64 << 10)) {
-    // several frequencies per wavefront, kAsmWaves wavefronts per workgroup
-    // (many bands of many harmonics do not fit its LDS: one per wavefront)
-    const int per = 64 / asm_group(a.H);
-    const int64_t w2 = std::max<int64_t>(1, std::min<int64_t>(waves, (np + per - 1) / per));
-    if (precision == 1) launch_assemble2<double>(a, rec, p0, np, (unsigned)((w2 + kAsmWaves - 1) / kAsmWaves), st);
-    else launch_assemble2<float>(a, rec, p0, np, (unsigned)((w2 + kAsmWaves - 1) / kAsmWaves), st);
-    return hipGetLastError();
-  }
-  const size_t lds = asm_lds_bytes(a.H, a.n_band);
-  if (precision == 1)
-    hipLaunchKernelGGL(k_assemble<double>, dim3((unsigned)waves), dim3(64), lds, st, a, rec, p0, np);
-  else
-    hipLaunchKernelGGL(k_assemble<float>, dim3((unsigned)waves), dim3(64), lds, st, a, rec, p0, np);
+  // several frequencies per wavefront, kAsmWaves wavefronts per workgroup (one where
+  // many bands of many harmonics would not fit its LDS: at most 44 KB)
+  const int per = 64 / asm_group(a.H);
+  const int nw = asm2_lds_bytes(a.H, a.n_band, kAsmWaves) <= ((size_t)64 << 10) ? kAsmWaves : 1;
+  const int64_t w2 = std::max<int64_t>(1, std::min<int64_t>(waves, (np + per - 1) / per));
+  if (precision == 1) launch_assemble_r<double>(a, rec, p0, np, (unsigned)((w2 + nw - 1) / nw), nw, st);
+  else launch_assemble_r<float>(a, rec, p0, np, (unsigned)((w2 + nw - 1) / nw), nw, st);
   return hipGetLastError();
 }
 

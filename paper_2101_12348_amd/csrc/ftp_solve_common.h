@@ -17,7 +17,7 @@ struct SolveArgs {
   const void* grids;             // float2 or double2 grids
   const double* sums_in;         // optional: per pair 3H complex sums (see gather)
   const double2* alpha;          // template alpha_n, n = 1..H (shared phase: n_band x H, band-major)
-  const double* ctab;            // D < 64: Cayley-map table, rows c = 0..D of cayley_row(K) doubles (see k_assemble),
+  const double* ctab;            // D < 64: the Cayley-map table, rows c = 0..D of cayley_row(K) doubles (see k_assemble);
                                  // then the template's products (template_products, complex) and |alpha_n|^2, n = 1..H
   int n_band;                    // 0: single band; > 0: shared-phase bands (lcs[0..n_band))
   int newton_cands;              // candidates of M_FALLBACK == 0 pairs are Newton-converged roots
@@ -133,6 +133,10 @@ __device__ __forceinline__ int64_t pair_lc(const SolveArgs& a, int64_t x) {
   return find_seg(a.freq_off, a.n_lc, x);
 }
 
+// (DPP moves without an `old` value, so that each folds into its v_max; lanes
+// of rows a row mask leaves out hold unspecified values.)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, ROWS, 0xf, true); }
 // Wavefront reductions of doubles: DPP moves inside each row of 16 lanes
 // (quad_perm [1,0,3,2], quad_perm [2,3,0,1], row_half_mirror, row_mirror), then
 // the four row results are combined through readlane.  Every lane returns the
@@ -164,29 +168,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += dpp_d<0x141>(v);
   v += dpp_d<0x140>(v);
   return (lane_d(v, 0) + lane_d(v, 16)) + (lane_d(v, 32) + lane_d(v, 48));
-}
-
-// max |v| over the wavefront from the high words (sign cleared) of the
-// doubles: the high word of |v| orders like |v|, so this is the maximum with
-// its low word cleared (relative error below 2^-20, never above the maximum).
-// Row stages: quad_perm [1,0,3,2], [2,3,0,1], row_half_mirror, row_mirror
-// (every lane of a row ends with the row maximum); then row_bcast:15 into rows
-// 1 and 3 and row_bcast:31 into rows 2 and 3 leave the maximum in lane 63.
-// (DPP moves without an `old` value, so that each folds into its v_max; lanes
-// of rows a row mask leaves out hold unspecified values, which do not reach
-// lane 63.)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_i(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, ROWS, 0xf, true); }
-__device__ __forceinline__ double wave_max_abs_hi(double v) {
-  int h = (int)((unsigned long long)__double_as_longlong(v) >> 32) & 0x7fffffff;
-  h = max(h, dpp_i<0xB1, 0xf>(h));
-  h = max(h, dpp_i<0x4E, 0xf>(h));
-  h = max(h, dpp_i<0x141, 0xf>(h));
-  h = max(h, dpp_i<0x140, 0xf>(h));
-  h = max(h, dpp_i<0x142, 0xa>(h));
-  h = max(h, dpp_i<0x143, 0xc>(h));
-  h = __builtin_amdgcn_readlane(h, 63);
-  return __longlong_as_double((long long)((unsigned long long)(unsigned)h << 32));
 }
 
 // Exact per-half maximum of doubles: row stages of wave_max, then
@@ -298,49 +279,15 @@ struct FreqWork {
   double2* al;   // alpha_n at al[n-1]
 };
 
-// Assemble mu, eta, r from the sums (all lanes of one wave participate).
+// mu, eta and r from the sums (all lanes of one wave participate; `lane` counts within
+// a group of `nl` lanes working on one frequency).
 //   MM(psi) = sum_{n,m} a_n a_m conj(Z_{n+m} - Z_n Z_m) psi^{n+m}
 //           + 2 a_n conj(a_m) conj(Z_{n-m} - Z_n conj(Z_m)) psi^{n-m} + c.c.
 // (the CC~, CS~, SS~ terms of Section 2 written with Z_k = C_k + i S_k),
 //   YM(psi) = sum_k a_k conj(Zy_k) psi^k + c.c.   (YC~_k = conj(Zy_k)),
 //   R(theta) = 2 MM dYM/dtheta - YM dMM/dtheta = sum_d r_d psi^d,
 //   r_d = i sum_k (3k - d) mu_{d-k} eta_k   (Eq. finalpoly with p = -i psi^K R).
-__device__ __forceinline__ void assemble_r(const FreqWork& W, int H, int lane, double2* scr, int nl = 64);
-
-// `scr`: LDS scratch of 8H + 2 complex values for assemble_r.  `lane` counts
-// within a group of `nl` lanes working on one frequency (64: the wavefront; 32:
-// a half-wave, two frequencies per wavefront); every lane of the wavefront
-// calls this.
-__device__ __forceinline__ void assemble_poly(const FreqWork& W, int H, int lane, double2* scr, int nl = 64) {
-  for (int e = lane; e <= 2 * H; e += nl) {
-    double2 acc = make_double2(0.0, 0.0);
-    if (e == 0) {
-      double s = 0.0;
-      for (int n = 1; n <= H; ++n) s += cabs2(W.al[n - 1]) * (1.0 - cabs2(W.Z[n]));
-      acc.x = 2.0 * s;
-    } else {
-      const int nlo = e - H > 1 ? e - H : 1;
-      const int nhi = e - 1 < H ? e - 1 : H;
-      for (int n = nlo; n <= nhi; ++n) {
-        const int m = e - n;
-        double2 t = csub(W.Z[e], cmul(W.Z[n], W.Z[m]));
-        acc = cadd(acc, cmul(cmul(W.al[n - 1], W.al[m - 1]), cconj(t)));
-      }
-      for (int n = e + 1; n <= H; ++n) {
-        const int m = n - e;
-        double2 t = csub(W.Z[e], cmul(W.Z[n], cconj(W.Z[m])));
-        acc = cadd(acc, cscale(cmul(cmul(W.al[n - 1], cconj(W.al[m - 1])), cconj(t)), 2.0));
-      }
-    }
-    W.mu[e] = acc;
-  }
-  for (int k = lane; k <= H; k += nl) {
-    W.eta[k] = k == 0 ? make_double2(0.0, 0.0) : cmul(W.al[k - 1], cconj(W.Z[2 * H + k]));
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); __builtin_amdgcn_wave_barrier();
-  assemble_r(W, H, lane, scr, nl);
-}
-
+//
 // r_d, d = 0..K, of R(theta) = 2 MM dYM/dtheta - YM dMM/dtheta from the trig
 // coefficients mu_e of MM and eta_k of YM (Eq. finalpoly as a trig polynomial).
 // The coefficients are first laid out over their full index ranges (mu_e for
@@ -596,17 +543,6 @@ __device__ __forceinline__ Cand eval_candidate(const FreqWork& W, int H, double 
   double sn, cs;
   sincos_small(theta, sn, cs);
   return eval_candidate_psi(W, H, make_double2(cs, sn));
-}
-
-// R(theta) alone (Horner in psi).
-__device__ __forceinline__ double eval_R_value(const FreqWork& W, int H, double theta) {
-  const int K = 3 * H - 1;
-  double sn, cs;
-  sincos_small(theta, sn, cs);
-  const double2 psi = make_double2(cs, sn);
-  double2 q = W.r[K];
-  for (int d = K - 1; d >= 1; --d) q = cfma(q, psi, W.r[d]);
-  return W.r[0].x + 2.0 * (q.x * psi.x - q.y * psi.y);
 }
 
 // R(theta) and dR/dtheta from r_d.
