@@ -662,9 +662,10 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
 // slots at six wavefronts per SIMD), so H is a template parameter: strides, loop
 // counts and LDS offsets are immediates, which fits six wavefronts without
 // spills (with H an argument 271 -> 144 MB read and 553 -> 285 MB written at H = 10
-// were spills).  That, the merge of both halves per pass, the tabulated starts
-// and phases left to the scoring: H = 10, 300 thousand frequencies 985 -> 890 us;
-// H = 6, 250 thousand 575 -> 495 us; H = 4, 4.2 million 5.4 -> 4.7 ms.
+// were spills).  That, the merge of both halves per pass (its scalar half
+// shortened in a second step, 6 %), the tabulated starts and phases left to the
+// scoring: H = 10, 300 thousand frequencies 985 -> 830 us; H = 6, 250 thousand 575
+// -> 478 us; H = 4, 4.2 million 5.4 -> 4.3 ms.
 // Starts of the first round for each frequency.
 __host__ __device__ inline constexpr int first_starts(int H, bool equal) {
   return equal ? 2 * H : (6 * H - 2 < 32 ? 6 * H - 2 : 32);
@@ -749,42 +750,39 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
     }
     if (it >= 2) {   // merges are incremental, so every iteration from the second checks
       const unsigned long long cm = __ballot(conv);
-      const bool needA = !doneA && __popcll(cm & lo32) >= cA;
-      const bool needB = !doneB && __popcll(cm >> 32) >= cB;
-      if (!needA && !needB && it < 12) continue;
-      // distinct converged roots of each half: a converged lane is unique
-      // unless a lower converged lane of its half lies within 1e-8 rad.
+      // (each half on its own count alone: what it settles, and so the lane that
+      // stands for a root, does not depend on the other's)
+      const bool needA = !doneA && (__popcll(cm & lo32) >= cA || it == 12);
+      const bool needB = !doneB && (__popcll(cm >> 32) >= cB || it == 12);
+      if (!needA && !needB) continue;
+      const unsigned long long need = (needA ? lo32 : 0ull) | (needB ? ~lo32 : 0ull);
+      // distinct converged roots of each half: converged lanes of one root lie
+      // within 1e-8 rad of each other.
       // Compared on key = u (sg > 0) or sign(u) 2 - u (sg < 0), which
       // increases with theta - phi0 over (-pi, pi) and moves by |du| where
       // theta moves by 2 |du| / (1 + u^2) (the cut at theta - phi0 = pi
       // sits where R is largest, far from any root).  Converged lanes no
       // longer move, so each check settles only the lanes converged since
-      // the last: one pass takes the lowest pending lane jj of each half and
-      // marks every converged lane of the half within the tolerance of jj; jj
-      // is unique if none of them is lower, and the higher ones (also roots
-      // settled earlier) are not.  (Both halves per pass, the roots
-      // broadcast through LDS: against one half per pass through scalar
-      // registers it takes half the passes and a quarter of the vector
-      // instructions.)
+      // the last: one pass takes the lowest pending lane of each half, counts it
+      // as a new root unless a root settled before lies within the tolerance, and
+      // settles every converged lane of the half that does.  (Both halves per
+      // pass, the keys broadcast through LDS: against one half per pass
+      // through scalar registers, with the lowest lane kept as each root's, it
+      // takes half the passes and a quarter of the vector instructions.)
       const double key = sg > 0 ? u : copysign(2.0, u) - u;
       const double tol = 0.5e-8 * fma(u, u, 1.0);
-      for (unsigned long long pend = cm & ~merged; pend;) {
+      for (unsigned long long pend = cm & ~merged & need; pend;) {
         const unsigned pA = (unsigned)pend, pB = (unsigned)(pend >> 32);
         const unsigned bA = pA & (0u - pA), bB = pB & (0u - pB);   // 0: none pending
         const int jA = __builtin_ctz(pA | 0x80000000u), jB = __builtin_ctz(pB | 0x80000000u);
-        const int src = (half ? 32 + jB : jA) << 2;
-        const double kj = bperm_d(src, key), tj = bperm_d(src, tol);
-        const unsigned long long sm = __ballot(fabs(key - kj) < tj) & cm;
-        const unsigned sA = bA ? (unsigned)sm : 0u, sB = bB ? (unsigned)(sm >> 32) : 0u;
-        unsigned uA = (unsigned)U, uB = (unsigned)(U >> 32);
-        uA = (uA & ~sA) | (uA & (bA - 1u));   // lanes above jj within the tolerance are not unique
-        uB = (uB & ~sB) | (uB & (bB - 1u));
-        uA = (sA & (bA - 1u)) ? uA & ~bA : uA | bA;
-        uB = (sB & (bB - 1u)) ? uB & ~bB : uB | bB;
-        U = uA | ((unsigned long long)uB << 32);
+        const double kj = bperm_d((half ? 32 + jB : jA) << 2, key);
+        const unsigned long long same = __ballot(fabs(key - kj) < tol) & cm;
+        const unsigned sA = (unsigned)same, sB = (unsigned)(same >> 32);
+        const unsigned uA = (unsigned)U, uB = (unsigned)(U >> 32);
+        U |= (sA & uA ? 0u : bA) | ((unsigned long long)(sB & uB ? 0u : bB) << 32);
         pend &= ~((sA | bA) | ((unsigned long long)(sB | bB) << 32));
       }
-      merged = cm;
+      merged |= cm & need;
       um = U;
       if (__popcll(um & lo32) == cA) doneA = true;
       if (__popcll(um >> 32) == cB) doneB = true;
