@@ -420,7 +420,7 @@ __global__ __launch_bounds__(64) void k_features2(double* rec, int H, int64_t np
 
 // ------------------------------------------------------- fused inference
 
-// The four layers of the network for kFRows (128 or 32) pairs per workgroup
+// The four layers of the network for kFRows pairs per workgroup, every pair of a round
 // (four waves), with the activations kept in LDS between layers: the output of
 // a layer is written over its input (after every wave has read it) and is the
 // A operand of the next.  Per layer, wave w computes all kFRows rows of the
@@ -436,22 +436,14 @@ __global__ __launch_bounds__(64) void k_features2(double* rec, int H, int64_t np
 // bit for bit.  Requirements (checked on the host): width a multiple of 32 up
 // to 256, kp[0] up to 256, d_out up to 64.
 
-// kFRows: pairs per workgroup, 128 when the network runs on every pair of a
-// round (each workgroup's weight reads serve more rows), 32 on a device list
-// (the first round's leftovers, a few thousand pairs: more workgroups, each
-// with a shorter chain of tiles; measured 14 us faster there).
+constexpr int kFRows = 128;           // pairs per workgroup
 constexpr int kActLd = 256 + 8;      // LDS row of one pair's activations (bf16)
 constexpr int kOutLd = 64 + 4;       // LDS row of one pair's outputs (FP32, d_out <= 64)
 
-template <int kFRows>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_mlp_fused(FusedMlpArgs a) {
   constexpr int kFRT = kFRows / 16;    // row tiles
   __shared__ __align__(16) uint16_t act[kFRows * kActLd];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  if (a.np_dev) {
-    const int64_t n = (int64_t)*a.np_dev;
-    if (n < a.np) a.np = n;
-  }
   // tiles of 128 pairs, strided over the grid (the same for every thread of
   // the workgroup, so the barriers below are reached by all or none)
   for (int64_t row0 = (int64_t)blockIdx.x * kFRows; row0 < a.np; row0 += (int64_t)gridDim.x * kFRows) {
@@ -638,6 +630,75 @@ hipError_t launch_f32_to_bf16(const float* x, uint16_t* y, int64_t n, hipStream_
   return hipGetLastError();
 }
 
+// The same network on a device list (the first round's leftovers, tens to a few
+// thousand pairs): 32 pairs per workgroup of sixteen waves, each on one 16-column
+// tile of a layer, the next layer's weights on their way while one is
+// computed.  Bound by latency: one fetch of the first layer's weights, then four
+// short layers.  (With four waves per 32 pairs, each streaming four tiles' weights
+// three slices ahead: 33 us for 33 pairs, 37 us for 4200; now 15 and 18.)
+// Same operands, K order, bias, ReLU and bf16 rounding: bit for bit the same.
+__global__ __launch_bounds__(64 * kTileWaves) void k_mlp_list(FusedMlpArgs a) {
+  __shared__ __align__(16) uint16_t act[2][32 * kTileLd];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t np = min((int64_t)*a.np_dev, a.np);
+  const int n = 16 * wave + (lane & 15);
+  // the wave's weights (rows padded to whole K slices) and bias of layer l
+  auto load = [&](int l, bf16x8_t (&f)[8], float& bias) {
+    if (16 * wave >= a.nout[l]) return;
+    const int K = a.kp[l], nc = min(n, a.nout[l] - 1);
+    const uint16_t* row = a.wi + a.oWi[l] + (int64_t)nc * K + 8 * (lane >> 4);
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      if (32 * s < K) f[s] = *reinterpret_cast<const bf16x8_t*>(row + 32 * s);
+    bias = a.w32[a.ob[l] + nc];
+  };
+  const int nout = a.nout[3];
+  float* of = reinterpret_cast<float*>(act[0]);
+  for (int64_t row0 = 32 * (int64_t)blockIdx.x; row0 < np; row0 += 32 * (int64_t)gridDim.x) {
+    bf16x8_t f[8], fn[8];
+    float bias = 0.f, bn = 0.f;
+    load(0, f, bias);
+    {
+      // features (rows of X, stride kp[0]; zero rows past the end): kp[0] <= 256
+      // takes at most one 16-byte load per thread
+      const int c8 = a.kp[0] >> 3, i = tid / c8, c = (tid - i * c8) * 8;
+      if (i < 32) {
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (row0 + i < np) v = *reinterpret_cast<const uint4*>(a.X + (row0 + i) * a.kp[0] + c);
+        *reinterpret_cast<uint4*>(&act[0][i * kTileLd + c]) = v;
+      }
+    }
+    __syncthreads();
+    // (one copy of the layer's code: the tier's launch fetches it cold)
+#pragma unroll 1
+    for (int l = 0; l < 4; ++l) {
+      if (l < 3) load(l + 1, fn, bn);
+      if (16 * wave < a.nout[l]) {
+        f32x4_t acc[2];
+        tile_mfma(act[l & 1], a.kp[l] >> 5, f, lane, acc);
+        const int r = 4 * (lane >> 4);
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float x = acc[i][v] + bias;
+            if (l < 3) act[(l + 1) & 1][(r + 16 * i + v) * kTileLd + n] = bf16_rne(fmaxf(x, 0.f));
+            else if (n < nout) of[(r + 16 * i + v) * kTileOutLd + n] = x;
+          }
+      }
+      __syncthreads();
+      bias = bn;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) f[s] = fn[s];
+    }
+    for (int q = tid; q < 32 * nout; q += 64 * kTileWaves) {
+      const int r = q / nout, c = q - r * nout;
+      if (row0 + r < np) a.out[(row0 + r) * nout + c] = of[r * kTileOutLd + c];
+    }
+    __syncthreads();   // the outputs have left the LDS
+  }
+}
+
 bool mlp_fused_ok(const int* nin, const int* nout) {
   if (((nin[0] + 31) & ~31) > 256 || nout[3] < 1 || nout[3] > 64) return false;
   for (int l = 0; l < 3; ++l)
@@ -650,13 +711,13 @@ bool mlp_fused_ok(const int* nin, const int* nout) {
 // `done` (nullable): an event the launch records at the kernel's end.
 hipError_t launch_mlp_fused(const FusedMlpArgs& fa, hipStream_t st, int max_blocks, hipEvent_t done) {
   if (fa.np <= 0) return done ? hipEventRecord(done, st) : hipSuccess;
-  const int rows = fa.np_dev ? 32 : 128;
+  const int rows = fa.np_dev ? 32 : kFRows;
   int64_t blocks = (fa.np + rows - 1) / rows;
   if (max_blocks > 0 && blocks > max_blocks) blocks = max_blocks;
   if (fa.np_dev)
-    hipExtLaunchKernelGGL(k_mlp_fused<32>, dim3((unsigned)blocks), dim3(256), 0, st, nullptr, done, 0, fa);
+    hipExtLaunchKernelGGL(k_mlp_list, dim3((unsigned)blocks), dim3(64 * kTileWaves), 0, st, nullptr, done, 0, fa);
   else
-    hipExtLaunchKernelGGL(k_mlp_fused<128>, dim3((unsigned)blocks), dim3(256), 0, st, nullptr, done, 0, fa);
+    hipExtLaunchKernelGGL(k_mlp_fused, dim3((unsigned)blocks), dim3(256), 0, st, nullptr, done, 0, fa);
   return hipGetLastError();
 }
 

@@ -75,3 +75,24 @@ def test_shared_phase_band_tables(H, n_band):
     ref = O.shared_phase_periodogram(bands, tmpls, df, n_f)
     # the stationary power: a root error of 1e-5 rad changes it by 1e-10; sums to 1e-10
     assert np.max(np.abs(out["power"].cpu().numpy() - ref["power"])) <= 1e-9
+
+
+@pytest.mark.parametrize("H,width,n_f", [(1, 32, 40), (3, 96, 700), (6, 256, 700), (10, 256, 700), (10, 32, 40)])
+def test_network_on_the_list_equals_layer_by_layer(H, width, n_f):
+    import paper_2101_12348_amd as F
+
+    # few starts leave a ragged list to the network (a third of the frequencies
+    # and more); the fused layers and one GEMM per layer seed the same second round
+    rng = np.random.default_rng(H + width)
+    tmpl, lc = tiny_case(50 + H, n_obs=200, H=H, n_f=n_f, baseline=60.0, cadence="nightly")
+    n = F.mlp_param_count(2 * (6 * H - 1), width, 4 * H)
+    w = (rng.normal(size=n) / np.sqrt(width)).astype(np.float32)
+    outs = []
+    for fused in (1, 0):
+        plan = F.Plan(tmpl.c, tmpl.s, precision=F.FTP_FP64, solver=F.FTP_SOLVER_LEARNED, flags=F.FTP_FLAG_2H_STARTS)
+        plan.set_tuning(mlp_fused=fused)
+        plan.load_mlp(w, width)
+        outs.append({k: v.cpu().numpy() for k, v in plan.periodogram(lc.t, lc.y, lc.sigma, lc.df, n_f).items()})
+        assert H == 1 or plan.stats()["n_fallback"] > 0
+    for k in outs[0]:
+        assert np.array_equal(outs[0][k], outs[1][k]), k
