@@ -233,6 +233,8 @@ __global__ __launch_bounds__(64 * 8) void k_aberth_split(AberthArgs A) {
   const int64_t n = (int64_t)(*A.count);
   constexpr double u = 1.1102230246251565e-16;
   unsigned long long its_acc = 0, qr_acc = 0;
+  // (places of no root: zeros, made visible by the first barrier below)
+  if (wv == 0) zs[0][lane] = zs[1][lane] = make_double2(0.0, 0.0);
   for (int64_t i = blockIdx.x; i < n; i += gridDim.x) {
     const int64_t w = A.list[i];
     double* R = A.rec + w * (int64_t)RL.stride;
@@ -313,17 +315,24 @@ __global__ __launch_bounds__(64 * 8) void k_aberth_split(AberthArgs A) {
         pr = qr;
         ab = ab * ay + fabs(cc);
       }
-      // the roots' sum (j = root and j >= D skipped)
+      // the roots' sum (j = root and j >= D, zeros here, skipped), eight reciprocals
+      // side by side
       double sr = 0.0, si = 0.0;
+      double2 e[8];
+      double inv[8];
 #pragma unroll
       for (int k = 0; k < 8; ++k) {
-        if (8 * k >= D) break;
+        const double2 zj = zc[8 * k + q];
+        e[k] = make_double2(zr - zj.x, zi - zj.y);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) inv[k] = fast_rcp_d(e[k].x * e[k].x + e[k].y * e[k].y);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
         const int j = 8 * k + q;
-        const double2 zj = zc[j];
-        const double er = zr - zj.x, ei = zi - zj.y;
-        const double inv = (j == root || j >= D) ? 0.0 : fast_rcp_d(er * er + ei * ei);
-        sr += er * inv;
-        si -= ei * inv;
+        const double iv = (j == root || j >= D) ? 0.0 : inv[k];
+        sr += e[k].x * iv;
+        si -= e[k].y * iv;
       }
       const double2 p = make_double2(pr, pi);
       const double2 v = cmul(xq, p);

@@ -73,13 +73,31 @@ __device__ __forceinline__ int64_t find_segment(const int64_t* off, int64_t n, i
 
 // Block-wide sums of v[0..NS) and minima of v[NS..NS+NM) in a fixed order
 // (wave shuffles, then the waves in turn); every thread receives the result.
+// The double of lane ^ O in a butterfly from 32 down: within a 16-lane row by DPP
+// (a rotation by 4 after the rotation by 8 meets lane ^ 4 or its equal lane ^ 12),
+// which a chain of nine values waits for a sixth as long as for an LDS permute.
+template <int O>
+__device__ __forceinline__ double butterfly(double v) {
+  if constexpr (O >= 16) return __shfl_xor(v, O);
+  constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4E : 0xB1;
+  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
+  const int lo = __builtin_amdgcn_mov_dpp((int)(unsigned)(u & 0xffffffffull), ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), ctrl, 0xf, 0xf, true);
+  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
+}
+template <int NS, int NM, int O>
+__device__ __forceinline__ void butterfly_all(double* v) {
+#pragma unroll
+  for (int q = 0; q < NS; ++q) v[q] += butterfly<O>(v[q]);
+#pragma unroll
+  for (int q = NS; q < NS + NM; ++q) v[q] = fmin(v[q], butterfly<O>(v[q]));
+  if constexpr (O > 1) butterfly_all<NS, NM, O / 2>(v);
+}
+
 template <int NS, int NM>
 __device__ __forceinline__ void block_reduce(double* v) {
   constexpr int N = NS + NM, NW = kStatThreads / 64;
-  for (int o = 32; o > 0; o >>= 1) {
-    for (int q = 0; q < NS; ++q) v[q] += __shfl_xor(v[q], o);
-    for (int q = NS; q < N; ++q) v[q] = fmin(v[q], __shfl_xor(v[q], o));
-  }
+  butterfly_all<NS, NM, 32>(v);
   __shared__ double sh[NW][N];
   const int wid = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0)
@@ -365,33 +383,44 @@ __global__ __launch_bounds__(256) void k_prep_points(const LcInfo* __restrict__ 
 }
 
 // Exclusive scan of 32-bit counts into 64-bit offsets, one workgroup for up
-// to kScanSingleMax counts: thread k scans a contiguous run of
-// ceil(n / 1024) counts; the run totals are scanned across the workgroup.
-// out[n] and *total receive the sum.
+// to kScanSingleMax counts: thread k takes a contiguous run of ceil(n / 1024) <= 16
+// counts, loaded together; the run totals are scanned across the wavefronts and
+// then the workgroup.  out[n] and *total receive the sum.  Bound by latency: one
+// round trip for the counts, one for the offsets.  (A loop of loads, repeated for
+// the output, and a scan of ten barriers took 13-17 us at 5000-12000 counts, now
+// 9-12; chunks of 64 per wavefront, coalesced, with a scan each: 10-13.)
 __global__ __launch_bounds__(1024) void k_scan_single(const unsigned int* __restrict__ in, int64_t n,
                                                       int64_t* __restrict__ out, int64_t* __restrict__ total) {
-  __shared__ int64_t sh[1024];
-  const int tid = threadIdx.x;
-  const int64_t per = (n + 1023) / 1024;
-  const int64_t b = tid * per, e = b + per < n ? b + per : n;
+  __shared__ int64_t sh[16];
+  const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, nn = (int)n;
+  const int per = (nn + 1023) / 1024, b = tid * per;
+  unsigned v[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) v[k] = (k < per && b + k < nn) ? in[b + k] : 0u;
   int64_t s = 0;
-  for (int64_t k = b; k < e; ++k) s += in[k];
-  sh[tid] = s;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += v[k];
+  int64_t run = s;   // inclusive over the wavefront
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const int64_t a = __shfl_up(run, o);
+    run += lane >= o ? a : 0;
+  }
+  if (lane == 63) sh[wv] = run;
   __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    const int64_t a = tid >= o ? sh[tid - o] : 0;
-    __syncthreads();
-    sh[tid] += a;
-    __syncthreads();
-  }
-  int64_t run = sh[tid] - s;
-  for (int64_t k = b; k < e; ++k) {
-    out[k] = run;
-    run += in[k];
-  }
+  int64_t before = 0;
+#pragma unroll
+  for (int w = 0; w < 16; ++w) before += w < wv ? sh[w] : 0;
+  run += before;
   if (tid == 1023) {
-    out[n] = sh[1023];
-    *total = sh[1023];
+    out[n] = run;
+    *total = run;
+  }
+  run -= s;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    if (k < per && b + k < nn) out[b + k] = run;
+    run += v[k];
   }
 }
 
