@@ -17,10 +17,9 @@
 //   * if they do, the Newton roots are the candidate set; otherwise the
 //     frequency goes to the Aberth iteration (then, if that does not
 //     converge, to the companion-matrix solve) through device work lists.
-// For H <= 10 a wavefront takes four frequencies, for H <= 5 eight
-// (k_newton_sturm4): their Sturm sequences run one per group of sixteen or
-// eight lanes with four coefficients per lane in registers, and Newton runs on two
-// of them at a time (32 starts each, at most D).  For H = 11 a wavefront takes one
+// For H <= 10 a wavefront takes eight frequencies, or four (k_newton_sturm4): their
+// Sturm sequences run one per group of eight or sixteen lanes with up to eight
+// coefficients per lane in registers, and Newton runs on two of them at a time (32 starts each, at most D).  For H = 11 a wavefront takes one
 // (k_newton_sturm, 4H starts), its Sturm sequence one coefficient per lane (the
 // degree-64 coefficient carried as a scalar; see sturm_begin); above, four whose
 // sequences run in double-double, a 16-lane row each (sturm_count_dd).
@@ -361,11 +360,11 @@ __device__ __forceinline__ double bperm_d(int addr, double v) {
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
-// Sturm chains, one per group of G lanes (16: four per wavefront, D < 64; 8:
-// eight, D < 32).  Lane l of a group holds R consecutive coefficients R l .. R l
+// Sturm chains, one per group of G lanes (8: eight per wavefront; 16: four), D <
+// 64.  Lane l of a group holds R consecutive coefficients R l .. R l
 // + R - 1 of each member in registers, so the shift by one power of x moves one
-// register between lanes (DPP row_shr:1) and the rest by name; R falls from 4 to
-// 2 and 1 as the members' degree falls below 2 G and G (sturm_repack).  The two
+// register between lanes (DPP row_shr:1) and the rest by name; R falls from 8
+// or 4 to 2 and 1 as the members' degree falls (sturm_repack).  The two
 // coefficients a step needs from its own chain (the quotient's and the new
 // leading one) come by ds_bpermute.  Per coefficient the arithmetic is that of
 // sturm_begin / sturm_step (scaled members with leading coefficient +-1,
@@ -375,8 +374,8 @@ __device__ __forceinline__ double bperm_d(int addr, double v) {
 // The tests of the steps (sturm_step_ok, as margins) are taken G steps at a
 // time: lane j of a group keeps step j's two high words (largest coefficient,
 // leading coefficient with its sign), and sturm_flush forms the margins and sign
-// changes of all of them at once.  A step is 35 vector instructions at R = 4
-// (22 at R = 1) for 64 / G chains; with the coefficients strided over the lanes
+// changes of all of them at once.  A step is ~52 vector instructions at R = 8,
+// 35 at R = 4 and 22 at R = 1 for 64 / G chains; with the coefficients strided over the lanes
 // and the tests in every step it was 66 (36) for four.
 template <int G>
 struct SturmTests {
@@ -439,8 +438,8 @@ __device__ __forceinline__ double with_sign(double v, int signbit) {
 
 // One step: from A (older, degree db + 1) and B (degree db), A becomes the
 // new member.  RQ = db % R.
-template <int G, int R, int RQ>
-__device__ __forceinline__ void sturm_rows_step(double (&A)[4], const double (&B)[4], SturmSigns& S, SturmTests<G>& T,
+template <int G, int R, int RQ, int N>
+__device__ __forceinline__ void sturm_rows_step(double (&A)[N], const double (&B)[N], SturmSigns& S, SturmTests<G>& T,
                                                 int db, int l, int gb4) {
 #pragma clang fp contract(off)
   constexpr int RL = (RQ + R - 1) % R;
@@ -482,8 +481,8 @@ __device__ __forceinline__ void sturm_rows_step(double (&A)[4], const double (&B
 }
 
 // R to R / 2 coefficients per lane.
-template <int R>
-__device__ __forceinline__ void sturm_repack(double (&X)[4], int l, int gb4) {
+template <int R, int N>
+__device__ __forceinline__ void sturm_repack(double (&X)[N], int l, int gb4) {
   const int src = gb4 + ((l >> 1) << 2);
   const bool odd = l & 1;
 #pragma unroll
@@ -494,16 +493,16 @@ __device__ __forceinline__ void sturm_repack(double (&X)[4], int l, int gb4) {
 }
 
 // Distinct real roots of the degree-D polynomial of this lane's group (D even,
-// D + 1 <= 4 G; C[r] = coefficient 4 l + r, zero above D; gtop = coefficient D),
-// or -1 when a step fails its test (`raw`: the count regardless).  All lanes
-// must be active.
-template <int G>
-__device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double gtop, int D, int lane, int& raw) {
+// D + 1 <= RM G, RM = 4 or 8; C[r] = coefficient RM l + r, zero above D; gtop =
+// coefficient D), or -1 when a step fails its test (`raw`: the count regardless).
+// All lanes must be active.
+template <int G, int RM>
+__device__ __forceinline__ int sturm_count_groups(const double (&C)[RM], double gtop, int D, int lane, int& raw) {
   // (a chain that ends near the thresholds of its tests turns on its last bits: no
   // contraction, which known signs and degrees would open or close)
 #pragma clang fp contract(off)
   const int l = lane & (G - 1), gb4 = (lane & ~(G - 1)) << 2;
-  double A[4], B[4];
+  double A[RM], B[RM];
   SturmSigns S;
   SturmTests<G> T;
   bool ok;
@@ -512,11 +511,11 @@ __device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double g
     const double sa = fast_rcp_d(ag + 1e-300), sb = fast_rcp_d(fma((double)D, ag, 1e-300));
     ok = ag > 0.0 && ag < INFINITY;
     int hA = 0, hB = 0;
-    const double up = dpp_d<0x101>(C[0]);   // row_shl:1: coefficient 4 (l + 1) (used up to coefficient D)
+    const double up = dpp_d<0x101>(C[0]);   // row_shl:1: coefficient RM (l + 1) (used up to coefficient D)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = 4 * l + r;
-      const double g1 = r < 3 ? C[r < 3 ? r + 1 : 3] : up;   // coefficient k + 1
+    for (int r = 0; r < RM; ++r) {
+      const int k = RM * l + r;
+      const double g1 = r < RM - 1 ? C[r < RM - 1 ? r + 1 : RM - 1] : up;   // coefficient k + 1
       const double dv = k < D ? (k + 1) * g1 : 0.0;
       A[r] = k == D ? sgn : C[r] * sa;
       B[r] = k == D - 1 ? sgn : dv * sb;
@@ -532,6 +531,40 @@ __device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double g
     S.ab = 0;
   }
   int db = D - 1;   // degree of the newer member (odd)
+  if constexpr (RM == 8) {
+    if (db > 4 * G - 5) {
+      // to a multiple of eight coefficients, then whole rounds of them
+      const int q = db & 7;
+      if (q == 5) {
+        sturm_rows_step<G, 8, 5>(A, B, S, T, db, l, gb4);
+        sturm_rows_step<G, 8, 4>(B, A, S, T, db - 1, l, gb4);
+        db -= 2;
+      }
+      if (q == 5 || q == 3) {
+        sturm_rows_step<G, 8, 3>(A, B, S, T, db, l, gb4);
+        sturm_rows_step<G, 8, 2>(B, A, S, T, db - 1, l, gb4);
+        db -= 2;
+      }
+      if (q != 7) {
+        sturm_rows_step<G, 8, 1>(A, B, S, T, db, l, gb4);
+        sturm_rows_step<G, 8, 0>(B, A, S, T, db - 1, l, gb4);
+        db -= 2;
+      }
+#pragma unroll 1
+      for (; db > 4 * G - 5; db -= 8) {
+        sturm_rows_step<G, 8, 7>(A, B, S, T, db, l, gb4);
+        sturm_rows_step<G, 8, 6>(B, A, S, T, db - 1, l, gb4);
+        sturm_rows_step<G, 8, 5>(A, B, S, T, db - 2, l, gb4);
+        sturm_rows_step<G, 8, 4>(B, A, S, T, db - 3, l, gb4);
+        sturm_rows_step<G, 8, 3>(A, B, S, T, db - 4, l, gb4);
+        sturm_rows_step<G, 8, 2>(B, A, S, T, db - 5, l, gb4);
+        sturm_rows_step<G, 8, 1>(A, B, S, T, db - 6, l, gb4);
+        sturm_rows_step<G, 8, 0>(B, A, S, T, db - 7, l, gb4);
+      }
+    }
+    sturm_repack<8>(A, l, gb4);
+    sturm_repack<8>(B, l, gb4);
+  }
   if (db > 2 * G - 5) {
     if ((db & 3) == 1) {
       sturm_rows_step<G, 4, 1>(A, B, S, T, db, l, gb4);
@@ -568,13 +601,15 @@ __device__ __forceinline__ int sturm_count_groups(const double (&C)[4], double g
   return ok ? raw : -1;
 }
 
-// Lanes per Sturm chain at degree D < 64.
-__host__ __device__ inline constexpr int sturm_group(int D) { return D < 32 ? 8 : 16; }
+// Coefficients per lane at first of a Sturm chain on G lanes, D < 64 (eight lanes
+// throughout, or sixteen above degree 31).
+__host__ __device__ inline constexpr int sturm_coefs(int D, int G) { return D < 4 * G ? 4 : 8; }
 
-// C[r] = coefficient 4 l + r of f (zero above D), l the lane's index in its group.
-__device__ __forceinline__ void load_coefficients(const double* f, bool on, int D, int l, double (&C)[4]) {
+// C[r] = coefficient R l + r of f (zero above D), l the lane's index in its group.
+template <int R>
+__device__ __forceinline__ void load_coefficients(const double* f, bool on, int D, int l, double (&C)[R]) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r) C[r] = (on && 4 * l + r <= D) ? f[4 * l + r] : 0.0;
+  for (int r = 0; r < R; ++r) C[r] = (on && R * l + r <= D) ? f[R * l + r] : 0.0;
 }
 
 // Newton on R(theta) carried out on the Cayley polynomial.  With x = tan((theta
@@ -648,7 +683,7 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
   return c;
 }
 
-// Four (H = 6..10) or eight (H <= 5) frequencies per wavefront, consecutive ones
+// Eight frequencies per wavefront (four where there are few and H > 5), consecutive ones
 // of the list.  Their Sturm chains run side by side, a group of lanes each
 // (sturm_count_groups); then Newton runs on two of them at a time, lanes
 // 0..31 for the first and 32..63 for the second, each half with min(32, D)
@@ -663,9 +698,10 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
 // counts and LDS offsets are immediates, which fits six wavefronts without
 // spills (with H an argument 271 -> 144 MB read and 553 -> 285 MB written at H = 10
 // were spills).  That, the merge of both halves per pass (its scalar half
-// shortened in a second step, 6 %), the tabulated starts and phases left to the
-// scoring: H = 10, 300 thousand frequencies 985 -> 830 us; H = 6, 250 thousand 575
-// -> 478 us; H = 4, 4.2 million 5.4 -> 4.3 ms.
+// shortened in a second step, 6 %), the tabulated starts, phases left to the
+// scoring and eight lanes per Sturm chain also above degree 31 (10 %): H = 10, 300
+// thousand frequencies 985 -> 775 us; H = 6, 250 thousand 575 -> 420 us; H = 4, 4.2
+// million 5.4 -> 4.3 ms.
 // Starts of the first round for each frequency.
 __host__ __device__ inline constexpr int first_starts(int H, bool equal) {
   return equal ? 2 * H : (6 * H - 2 < 32 ? 6 * H - 2 : 32);
@@ -829,16 +865,18 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
 // OCC: resident wavefronts per SIMD the register allocation is made for (5: up
 // to 96 VGPRs, 6: up to 80, a spill or two at H = 6); which is faster depends on the
 // workload and the grid, so the launch shape picks it (below 5 takes the former).
-template <int H, int OCC>
+template <int H, int OCC, int G>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
-  constexpr int D = 6 * H - 2, G = sturm_group(D);
+  constexpr int D = 6 * H - 2, RM = sturm_coefs(D, G);
   constexpr int NC = 64 / G;   // frequencies per wavefront
-  constexpr int DP = newton_top(D), FS = DP + 2;   // f and its reversal for each frequency, 16-byte aligned
+  constexpr int DP = newton_top(D), FS = DP + 2;   // f and its reversal of the two at hand, 16-byte aligned
   const int lane = threadIdx.x & 63, row = lane / G, l = lane & (G - 1);
   const RecLayout RL(H);
   NewtonAcc acc{0, 0, 0};
-  for (int k = D + 1 + l; k <= DP; k += G) sml[2 * FS * row + k] = sml[2 * FS * row + FS + k] = 0.0;
+  const int half = lane >> 5, hl = lane & 31;
+  double* fh = sml + 2 * FS * half;
+  for (int k = D + 1 + hl; k <= DP; k += 32) fh[k] = fh[FS + k] = 0.0;
   for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
     // this group's frequency (inactive: past the end, rejected lightcurve, or P
     // constant in theta_2)
@@ -859,28 +897,33 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
       acc.fb += (unsigned long long)(__popcll(act) / G);
       continue;
     }
-    // coefficients to registers, f and its reversal to LDS for Newton
     const double* f = Rr + RL.f;
-    double C[4];
+    double C[RM];
     load_coefficients(f, mine, D, l, C);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int k = 4 * l + r;
-      if (mine && k <= D) {
-        sml[2 * FS * row + k] = C[r];
-        sml[2 * FS * row + FS + D - k] = C[r];
-      }
-    }
     const double gtop = mine ? f[D] : 0.0;
-    lwave_sync();
     int raw;
     int cnt = sturm_count_groups<G>(C, gtop, D, lane, raw);
     if (cnt < 2) cnt = -1;
     if (!mine) cnt = -2;
+    // Newton two frequencies at a time; each half's coefficients come again, from
+    // the cache, ahead of its turn (all eight pairs of rows would take 8 KB of LDS)
+    auto fetch = [&](int p, double& v0, double& v1) {
+      const int64_t w = w0 + 2 * p + half;
+      const double* fw = L.rec + (w < L.np ? w : w0) * (int64_t)RL.stride + RL.f;
+      v0 = fw[hl < D ? hl : D];
+      v1 = D >= 32 ? fw[hl + 32 < D ? hl + 32 : D] : 0.0;
+    };
+    double v0, v1;
+    fetch(0, v0, v1);
 #pragma unroll 1
-    for (int p = 0; p < NC / 2; ++p)
+    for (int p = 0; p < NC / 2; ++p) {
+      if (hl <= D) fh[hl] = fh[FS + D - hl] = v0;
+      if (D >= 32 && hl + 32 <= D) fh[hl + 32] = fh[FS + D - 32 - hl] = v1;
+      lwave_sync();
+      if (p + 1 < NC / 2) fetch(p + 1, v0, v1);
       newton_pair<H>(L, RL, w0 + 2 * p, __builtin_amdgcn_readlane(cnt, 2 * p * G),
-                  __builtin_amdgcn_readlane(cnt, (2 * p + 1) * G), sml + 4 * FS * p, lane, acc);
+                     __builtin_amdgcn_readlane(cnt, (2 * p + 1) * G), sml, lane, acc);
+    }
   }
   const unsigned long long iters = (unsigned long long)wave_sum((double)acc.iters);
   if (lane == 0 && a.counters) {
@@ -1059,7 +1102,7 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
   const int lane = threadIdx.x & 63;
   const int D = 6 * H - 2;
   const RecLayout RL(H);
-  const int G = D < 64 ? sturm_group(D) : (D > 64 ? 16 : 64);
+  const int G = D < 64 ? 8 : (D > 64 ? 16 : 64);
   const int per = 64 / G;
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < np; w0 += per * (int64_t)gridDim.x) {
     int cnt;
@@ -1067,11 +1110,17 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
       const int row = lane / G, l = lane & (G - 1);
       const bool in = w0 + row < np;
       const double* f = rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f;
-      double C[4];
-      load_coefficients(f, in, D, l, C);
       int raw;
       const double gtop = in ? f[D] : 0.0;
-      cnt = G == 8 ? sturm_count_groups<8>(C, gtop, D, lane, raw) : sturm_count_groups<16>(C, gtop, D, lane, raw);
+      if (sturm_coefs(D, 8) == 4) {
+        double C[4];
+        load_coefficients(f, in, D, l, C);
+        cnt = sturm_count_groups<8>(C, gtop, D, lane, raw);
+      } else {
+        double C[8];
+        load_coefficients(f, in, D, l, C);
+        cnt = sturm_count_groups<8>(C, gtop, D, lane, raw);
+      }
       if (cnt < 0) cnt = -1000 - raw;
       cnt = __shfl(cnt, (lane * G) & 63);   // pair `lane` of the group to lane `lane`
     } else if (D > 64) {
@@ -1241,13 +1290,28 @@ hipError_t launch_newton_retry(const RetryArgs& A, int waves, hipStream_t st) {
 
 bool newton_four_per_wave(int H) { return 6 * H - 2 < 64; }
 
+template <int H, int G>
+static void launch_newton_g(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+  const size_t lds = (size_t)4 * (newton_top(6 * H - 2) + 2) * sizeof(double);   // f and its reversal of two frequencies
+  const dim3 grid((unsigned)waves), block(64);
+  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6, G>), grid, block, lds, st, nullptr, done, 0, a, L);
+  else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5, G>), grid, block, lds, st, nullptr, done, 0, a, L);
+}
+
+// Eight lanes per Sturm chain, so eight frequencies per wavefront, where that leaves
+// the device two rounds of resident wavefronts; with fewer frequencies four per
+// wavefront (sixteen lanes) fill it more evenly, except up to degree 31, where
+// eight lanes are also the shorter chain.  Measured with 8 / 16 lanes, whole
+// periodograms: H = 6 311 / 305 us at 50 thousand frequencies, 475 / 473 at 100, 755 /
+// 810 at 200; H = 10 418 / 405, 655 / 675 and 1140 / 1170.
+constexpr int64_t kEightLanesFrom = 100000;
+
 template <int H>
 static void launch_newton_h(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
-  constexpr int D = 6 * H - 2, NC = 64 / sturm_group(D);
-  const size_t lds = (size_t)NC * 2 * (newton_top(D) + 2) * sizeof(double);   // f and its reversal per frequency
-  const dim3 grid((unsigned)waves), block(64);
-  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6>), grid, block, lds, st, nullptr, done, 0, a, L);
-  else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5>), grid, block, lds, st, nullptr, done, 0, a, L);
+  if constexpr (6 * H - 2 >= 32) {
+    if (L.np < kEightLanesFrom) return launch_newton_g<H, 16>(a, L, waves, occ, st, done);
+  }
+  launch_newton_g<H, 8>(a, L, waves, occ, st, done);
 }
 
 hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st) {

@@ -96,3 +96,18 @@ def test_network_on_the_list_equals_layer_by_layer(H, width, n_f):
         assert H == 1 or plan.stats()["n_fallback"] > 0
     for k in outs[0]:
         assert np.array_equal(outs[0][k], outs[1][k]), k
+
+
+@pytest.mark.parametrize("H", [6, 7, 8, 9, 10])
+def test_eight_chains_per_wavefront_where_there_are_many(H):
+    import paper_2101_12348_amd as F
+
+    # either side of 100 thousand frequencies, the last wavefront partly filled
+    for n_f in (99997, 100003):
+        tmpl, lc = tiny_case(30 + H, n_obs=200, H=H, n_f=n_f, baseline=2000.0, cadence="nightly")
+        args = (lc.t, lc.y, lc.sigma, lc.df, n_f)
+        uni, plain = (F.Plan(tmpl.c, tmpl.s, precision=F.FTP_FP64, solver=s).periodogram(*args)
+                      for s in (F.FTP_SOLVER_UNIFORM, F.FTP_SOLVER_PLAIN))
+        # the power is stationary at the root: a root error of 1e-5 rad changes it by 1e-10
+        assert float((uni["power"] - plain["power"]).abs().max()) <= 1e-10
+        assert int((uni["status"] & 7).max()) == 0
