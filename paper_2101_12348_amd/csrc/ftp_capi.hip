@@ -882,9 +882,11 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
   auto root_ev = [&]() -> hipEvent_t { return B.timing ? next_root_event(P) : nullptr; };
   auto learn_ev = [&]() -> hipEvent_t { return B.timing ? next_learn_event(P) : nullptr; };
   const ftp_tuning& T = P->tune;
-  // scoring of the Newton-root pairs four per wavefront, on the side stream
+  // scoring of the Newton-root pairs on the side stream, beside the fallback tiers
+  // (above H = 10 beside the companion solve of a few: 145 of 2810 us at H = 13, 50
+  // thousand frequencies)
   const bool overlap_score =
-      !dataset && (solver == FTP_SOLVER_LEARNED || solver == FTP_SOLVER_UNIFORM) && 6 * P->H - 2 < 64;
+      !dataset && (solver == FTP_SOLVER_LEARNED || solver == FTP_SOLVER_UNIFORM);
   // learned solver with a fusable network: features in rows of dinp bf16
   // (zero padded), then one kernel for the four layers
   const bool fused = solver == FTP_SOLVER_LEARNED && P->tune.mlp_fused && P->net.dense &&

@@ -297,7 +297,7 @@ __device__ __forceinline__ void f_by_horner(const FreqWork& W, double2* rho, int
 // offsets unroll; 10-14 % of the time).  Large H = 10 lightcurve (300 thousand
 // frequencies) 575 -> 402 us; a batch round at H = 4 (4.2 million), sixteen lanes
 // per frequency instead of 32 as well, 3.87 -> 1.65 ms; three bands at H = 6 (50
-// thousand frequencies), one per wavefront before, 184 -> 104 us.
+// thousand frequencies), one per wavefront before, 184 -> 84 us.
 // HT: H, or 0 to take it from the arguments.  MODE: the sums' source.
 enum { kFromGrids = 0, kFromSums = 1, kFromBands = 2 };
 template <typename R, int GL, int HT, int MODE>
@@ -595,6 +595,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     const int64_t pidx = p0 + w;
     const double* Rr = rec + w * (int64_t)RL.stride;
     const int st = (int)Rr[RL.meta + M_STATUS];
+    if (a.newton_cands == 2 && Rr[RL.meta + M_FALLBACK] != 0.0) continue;   // the fallback list's scoring takes it
     const int64_t lc = (int64_t)Rr[RL.meta + M_LC];
     const LcInfo& L = a.lcs[lc];
     if (st == ST_BAD_LC) {
@@ -1002,22 +1003,23 @@ static void launch_assemble_r(const SolveArgs& a, double* rec, int64_t p0, int64
   const dim3 grid(wg), block(64 * nw);
   const size_t lds = asm2_lds_bytes(a.H, a.n_band, nw);
   const bool g16 = asm_group(a.H) == 16;
-  if (a.n_band) {
-    if (g16) hipLaunchKernelGGL((k_assemble<R, 16, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
-    else hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
-    return;
-  }
   if (a.sums_in) {
     if (g16) hipLaunchKernelGGL((k_assemble<double, 16, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
     else hipLaunchKernelGGL((k_assemble<double, 32, 0, kFromSums>), grid, block, lds, st, a, rec, p0, np);
     return;
   }
   switch (a.H) {
-#define FTP_ASM(h) case h: hipLaunchKernelGGL((k_assemble<R, asm_group(h), h, kFromGrids>), grid, block, lds, st, a, rec, p0, np); break;
+#define FTP_ASM(h)                                                                                                  \
+  case h:                                                                                                           \
+    if (a.n_band) hipLaunchKernelGGL((k_assemble<R, asm_group(h), h, kFromBands>), grid, block, lds, st, a, rec, p0, np); \
+    else hipLaunchKernelGGL((k_assemble<R, asm_group(h), h, kFromGrids>), grid, block, lds, st, a, rec, p0, np);     \
+    break;
     FTP_ASM(1) FTP_ASM(2) FTP_ASM(3) FTP_ASM(4) FTP_ASM(5)
     FTP_ASM(6) FTP_ASM(7) FTP_ASM(8) FTP_ASM(9) FTP_ASM(10)
 #undef FTP_ASM
-    default: hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromGrids>), grid, block, lds, st, a, rec, p0, np);
+    default:   // (H as an argument costs 3 % here, where f's recurrence dominates)
+      if (a.n_band) hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromBands>), grid, block, lds, st, a, rec, p0, np);
+      else hipLaunchKernelGGL((k_assemble<R, 32, 0, kFromGrids>), grid, block, lds, st, a, rec, p0, np);
   }
 }
 
@@ -1044,10 +1046,23 @@ hipError_t launch_score(const SolveArgs& a, const double* rec, int64_t p0, int64
   return hipGetLastError();
 }
 
-// Newton-candidate pairs four per wavefront (see k_score4, H <= 10); `done`
-// (nullable): an event the launch itself records at the kernel's end.
-hipError_t launch_score_newton(const SolveArgs& a, const double* rec, int64_t p0, int64_t np, int waves, hipStream_t st,
+// Newton-candidate pairs, four per wavefront (see k_score4), one above H = 10 (the
+// pairs the fallback tiers work on beside it are skipped); `done` (nullable): an
+// event the launch itself records at the kernel's end.
+hipError_t launch_score_newton(const SolveArgs& a0, const double* rec, int64_t p0, int64_t np, int waves, hipStream_t st,
                          hipEvent_t done) {
+  SolveArgs a = a0;
+  a.newton_cands = 2;
+  if (a.H > 10) {
+    const dim3 g((unsigned)waves);
+    if (a.H == 11)
+      hipExtLaunchKernelGGL(k_score<1>, g, dim3(64), score_lds_bytes(a.H), st, nullptr, done, 0, a, rec, p0, np,
+                            (const int64_t*)nullptr, (const unsigned*)nullptr);
+    else
+      hipExtLaunchKernelGGL(k_score<2>, g, dim3(64), score_lds_bytes(a.H), st, nullptr, done, 0, a, rec, p0, np,
+                            (const int64_t*)nullptr, (const unsigned*)nullptr);
+    return hipGetLastError();
+  }
   // consecutive frequencies per wavefront: more amortise the finish, fewer fill
   // the chip (twice over at four wavefronts per SIMD)
   const int w = std::max(1, std::min(waves, 8192));

@@ -20,7 +20,7 @@ struct SolveArgs {
   const double* ctab;            // D < 64: the Cayley-map table, rows c = 0..D of cayley_row(K) doubles (see k_assemble);
                                  // then the template's products (template_products, complex) and |alpha_n|^2, n = 1..H
   int n_band;                    // 0: single band; > 0: shared-phase bands (lcs[0..n_band))
-  int newton_cands;              // candidates of M_FALLBACK == 0 pairs are Newton-converged roots
+  int newton_cands;              // candidates of M_FALLBACK == 0 pairs are Newton-converged roots (2: score only these)
   int H;
   int flags;
   double mm_tau;                 // degenerate if MM <= mm_tau * sum|alpha|^2 at every candidate
