@@ -410,8 +410,12 @@ struct ftp_plan {
   std::string arch = "unknown";
   size_t grid_budget = (size_t)8 << 30;   // bytes of NFFT grids per chunk
   // device buffers
-  DevBuf alpha, twiddle32, twiddle64, ctab;
-  double2* starts = nullptr;   // in ctab, D < 64 (k_start_table)
+  // one allocation and copy: twiddles, templates, the solve's tables (SolveArgs::ctab)
+  // and, D < 64, the first round's starts (k_start_table)
+  DevBuf tables;
+  double2 *twiddle64 = nullptr, *alpha = nullptr, *starts = nullptr;
+  float2* twiddle32 = nullptr;
+  double* ctab = nullptr;
   DevBuf pw, py, tile_count, tile_off, cursor, block_sums,
       total, bucket, grids, fft_tab, fft_items, counters, stats_out, rec;
   DevBuf stat_part, stat_ticket;   // statistics kernel: partials per workgroup, ticket per lightcurve
@@ -650,7 +654,7 @@ int run_nfft(ftp_plan* P, int64_t n_lc, int64_t n_pts, int64_t n_grid, int64_t n
                      sigma, P->stat_part.as<double>(), P->stat_ticket.as<unsigned>(), P->tile_count.as<unsigned>(),
                      P->cursor.as<unsigned>(), n_tiles);
   if (shared_bands > 0)
-    hipLaunchKernelGGL(k_sp_combine, dim3(1), dim3(64), 0, st, dl, shared_bands, P->alpha.as<double2>(), P->H);
+    hipLaunchKernelGGL(k_sp_combine, dim3(1), dim3(64), 0, st, dl, shared_bands, P->alpha, P->H);
   const unsigned pblocks = (unsigned)((n_pts + 255) / 256);
   hipLaunchKernelGGL(k_prep_points<R>, dim3(pblocks), dim3(256), 0, st, dl, n_lc,
                      P->d_obs_off, n_pts, t, y, sigma, P->pw.as<PointRec<R>>(),
@@ -675,7 +679,7 @@ int run_nfft(ftp_plan* P, int64_t n_lc, int64_t n_pts, int64_t n_grid, int64_t n
                      P->tile_off.as<int64_t>(), P->bucket.as<int>(), P->grids.as<C>());
   hipEvent_t s1 = next_nfft_event(P);
   if (s1) HIP_TRY(hipEventRecord(s1, st));
-  const C* tw = reinterpret_cast<const C*>(P->opt.precision == FTP_FP64 ? P->twiddle64.p : P->twiddle32.p);
+  const C* tw = reinterpret_cast<const C*>(P->opt.precision == FTP_FP64 ? (const void*)P->twiddle64 : (const void*)P->twiddle32);
   int64_t item_base = 0;
   for (size_t r = 0; r < P->fft_round_n.size(); ++r) {
     const int el = fft_block_log2(P->opt.precision);
@@ -1078,8 +1082,8 @@ SolveArgs base_args(ftp_plan* P, int64_t n_lc, int64_t n_pairs) {
   a.lc_block = n_lc > 1 ? P->d_lcb : nullptr;
   a.total = n_pairs;
   a.grids = P->grids.p;
-  a.alpha = P->alpha.as<double2>();
-  a.ctab = P->ctab.as<double>();
+  a.alpha = P->alpha;
+  a.ctab = P->ctab;
   a.H = P->H;
   a.flags = (int)P->opt.flags;
   a.mm_tau = P->opt.precision == FTP_FP64 ? 1e-9 : 1e-5;
@@ -1334,51 +1338,49 @@ int plan_create_impl(ftp_plan** out, int n_band, int H, const double* c, const d
   }
   std::vector<double2> al(nt * H);
   for (int n = 0; n < nt * H; ++n) al[n] = make_double2(0.5 * c[n], 0.5 * s[n]);
-  std::vector<float2> tw32(kTwiddleN);
-  std::vector<double2> tw64(kTwiddleN);
-  for (int k = 0; k < kTwiddleN; ++k) {
-    const long double ang = 2.0L * 3.141592653589793238462643383279502884L * (long double)k / (long double)kTwiddleN;
-    tw64[k] = make_double2((double)cosl(ang), (double)sinl(ang));
-    tw32[k] = make_float2((float)tw64[k].x, (float)tw64[k].y);
+  const int D = 6 * H - 2;
+  std::vector<double> ct;
+  if (D < 64) ct = cayley_table(D);
+  append_products(ct, H, al.data());
+  // twiddle64, twiddle32, alpha, ctab, starts
+  const size_t o32 = sizeof(double2) * kTwiddleN, oal = o32 + sizeof(float2) * kTwiddleN,
+               oct = oal + sizeof(double2) * al.size(), ost = oct + ((sizeof(double) * ct.size() + 15) & ~(size_t)15);
+  std::vector<unsigned char> tab(ost);
+  {
+    double2* t64 = reinterpret_cast<double2*>(tab.data());
+    float2* t32 = reinterpret_cast<float2*>(tab.data() + o32);
+    for (int k = 0; k < kTwiddleN; ++k) {
+      const long double ang = 2.0L * 3.141592653589793238462643383279502884L * (long double)k / (long double)kTwiddleN;
+      t64[k] = make_double2((double)cosl(ang), (double)sinl(ang));
+      t32[k] = make_float2((float)t64[k].x, (float)t64[k].y);
+    }
+    std::memcpy(tab.data() + oal, al.data(), sizeof(double2) * al.size());
+    std::memcpy(tab.data() + oct, ct.data(), sizeof(double) * ct.size());
   }
-  if ((rc = P->alpha.ensure(sizeof(double2) * nt * H)) || (rc = P->twiddle32.ensure(sizeof(float2) * kTwiddleN)) ||
-      (rc = P->twiddle64.ensure(sizeof(double2) * kTwiddleN)) || (rc = P->counters.ensure(sizeof(SolveCounters) * kCounterSlots))) {
+  if ((rc = P->tables.ensure(ost + (D < 64 ? sizeof(double2) * 16 * 32 : 0))) ||
+      (rc = P->counters.ensure(sizeof(SolveCounters) * kCounterSlots))) {
     delete P;
     return rc;
   }
-  if (hipMemcpy(P->alpha.p, al.data(), sizeof(double2) * nt * H, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(P->twiddle32.p, tw32.data(), sizeof(float2) * kTwiddleN, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(P->twiddle64.p, tw64.data(), sizeof(double2) * kTwiddleN, hipMemcpyHostToDevice) != hipSuccess ||
+  {
+    unsigned char* d = P->tables.as<unsigned char>();
+    P->twiddle64 = reinterpret_cast<double2*>(d);
+    P->twiddle32 = reinterpret_cast<float2*>(d + o32);
+    P->alpha = reinterpret_cast<double2*>(d + oal);
+    P->ctab = reinterpret_cast<double*>(d + oct);
+    if (D < 64) P->starts = reinterpret_cast<double2*>(d + ost);
+  }
+  // (the starts before the copy, which waits for them)
+  if ((P->starts && launch_start_table(P->starts, H, (P->opt.flags & FTP_FLAG_2H_STARTS) != 0, nullptr) != hipSuccess) ||
       hipMemset(P->counters.p, 0, sizeof(SolveCounters) * kCounterSlots) != hipSuccess ||
+      hipMemcpy(P->tables.p, tab.data(), tab.size(), hipMemcpyHostToDevice) != hipSuccess ||
+      hipStreamSynchronize(nullptr) != hipSuccess ||
       hipEventCreateWithFlags(&P->upload_done, hipEventDisableTiming) != hipSuccess ||
       hipStreamCreateWithFlags(&P->side, hipStreamNonBlocking) != hipSuccess ||
       hipEventCreate(&P->fork_ev) != hipSuccess || hipEventCreate(&P->join_ev) != hipSuccess) {
     g_last_error = "plan setup copy failed";
     delete P;
     return FTP_E_HIP;
-  }
-  const int D = 6 * H - 2;
-  {
-    std::vector<double> ct;
-    if (D < 64) ct = cayley_table(D);
-    append_products(ct, H, al.data());
-    // (then the first round's starts: 32 iterates for each of sixteen rotations)
-    const size_t nt_starts = D < 64 ? sizeof(double2) * 16 * 32 : 0;
-    if ((rc = P->ctab.ensure(sizeof(double) * ct.size() + nt_starts))) {
-      delete P;
-      return rc;
-    }
-    bool ok = hipMemcpy(P->ctab.p, ct.data(), sizeof(double) * ct.size(), hipMemcpyHostToDevice) == hipSuccess;
-    if (ok && D < 64) {
-      P->starts = reinterpret_cast<double2*>(P->ctab.as<double>() + ct.size());
-      ok = launch_start_table(P->starts, H, (P->opt.flags & FTP_FLAG_2H_STARTS) != 0, nullptr) == hipSuccess &&
-           hipStreamSynchronize(nullptr) == hipSuccess;
-    }
-    if (!ok) {
-      g_last_error = "plan setup copy failed";
-      delete P;
-      return FTP_E_HIP;
-    }
   }
   *out = P;
   return FTP_OK;
@@ -1406,7 +1408,7 @@ int ftp_plan_create_bands(ftp_plan** out, int n_band, int H, const double* c, co
 int ftp_plan_destroy(ftp_plan* P) {
   if (!P) return FTP_E_NULL;
   (void)hipDeviceSynchronize();
-  DevBuf* bufs[] = {&P->alpha, &P->twiddle32, &P->twiddle64, &P->ctab, &P->d_stage,
+  DevBuf* bufs[] = {&P->tables, &P->d_stage,
                     &P->pw, &P->py, &P->tile_count, &P->tile_off, &P->cursor,
                     &P->block_sums, &P->total, &P->bucket, &P->grids,
                     &P->counters, &P->stats_out, &P->rec, &P->stat_part, &P->stat_ticket, &P->xfeat, &P->seeds, &P->fb_list,
