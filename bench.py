@@ -370,8 +370,8 @@ SINGLE_WORKLOADS = {
                              "oversample 5, f_max=10/day"),
 }
 
-# kernels behind each stage for H <= 10 (four frequencies per wavefront in the
-# Newton + Sturm kernel; the one-frequency k_newton_sturm serves H >= 11)
+# kernels behind each stage for H <= 10 (four or eight frequencies per wavefront
+# in the Newton + Sturm kernel; k_newton_sturm serves H >= 11)
 KERNEL_NAMES = {"plain_qr": "k_qr (companion QR, FP64 vector)",
                 "fallback_qr": "k_qr on the Aberth tier's leftovers (FP64 vector)",
                 "newton_sturm": "k_newton_sturm4 (FP64 vector)",
@@ -389,7 +389,8 @@ def nfft_bytes(H: int, n_f: int, n_obs: int, span: float, R: float = 2.0, msp: i
     within span n + 2 msp of the reference time, in whole 2048-cell tiles, and
     reads two 16-byte point records per observation; the first FFT pass reads
     those cells (the others are known zeros) and writes the whole grid, each
-    later pass reads and writes the whole grid."""
+    later pass reads and writes the whole grid, except that the last writes only
+    the gathered modes."""
     import math
     n_w = 1 << max(12, math.ceil(math.log2(R * (2 * H * n_f + 1))))
     n_y = 1 << max(12, math.ceil(math.log2(R * (H * n_f + 1))))
@@ -397,7 +398,8 @@ def nfft_bytes(H: int, n_f: int, n_obs: int, span: float, R: float = 2.0, msp: i
     passes = lambda n: 1 + max(0, math.ceil((int(math.log2(n)) - last) / 9))
     touched = lambda n: min(n, 2048 * (math.ceil((span * n + 2 * msp) / 2048) + 1))
     spread = 8 * (touched(n_w) + touched(n_y)) + 32 * n_obs
-    fft = sum(8 * (touched(n) + n) + 16 * n * (passes(n) - 1) for n in (n_w, n_y))
+    fft = sum(8 * (touched(n) + n) + 16 * n * (passes(n) - 1) - 8 * (n - m)
+              for n, m in ((n_w, 2 * H * n_f + 1), (n_y, H * n_f + 1)))
     return spread, fft, n_w, n_y
 
 
