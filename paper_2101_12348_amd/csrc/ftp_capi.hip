@@ -161,7 +161,7 @@ struct MlpNet {
   DevBuf h[3], outf, dout_f, dout_b, dz_f, dz_b[3];
   // training: transposed weights of layers 1..3, partial sums of the weight and
   // bias gradients
-  DevBuf wt[3], wpart, bpart;
+  DevBuf wpart, bpart;
   TransposedWeights twt{};
   int64_t cap_batch = 0;
   int64_t step = 0;
@@ -205,7 +205,7 @@ struct MlpNet {
   static int wgrad_splits(int64_t B) { return (int)std::min<int64_t>(32, (B + 255) / 256); }
   void release() {
     DevBuf* bs[] = {&winf, &w32, &wbf, &grad, &am, &av, &loss, &h[0], &h[1], &h[2], &outf, &dout_f, &dout_b,
-                    &dz_f, &dz_b[0], &dz_b[1], &dz_b[2], &wt[0], &wt[1], &wt[2], &wpart, &bpart};
+                    &dz_f, &dz_b[0], &dz_b[1], &dz_b[2], &wpart, &bpart};
     for (DevBuf* b : bs) b->release();
   }
 };
@@ -218,35 +218,36 @@ uint16_t host_f2bf(float x) {
   return (uint16_t)(u >> 16);
 }
 
-// Copies FP32 parameters (host) into the net and refreshes the bf16 copies.
-int mlp_set_weights(MlpNet* N, const float* w) {
+// Copies FP32 parameters (host) into the net and refreshes the bf16 copies: the
+// parameters in order and, for a network to be trained, the transposed
+// weights (see TransposedWeights) behind them, in one allocation and one copy
+// (with three more of each a creation took 0.47 ms instead of 0.38).
+int mlp_set_weights(MlpNet* N, const float* w, bool train = false) {
   int rc;
-  if ((rc = N->w32.ensure(sizeof(float) * N->n_params))) return rc;
-  if ((rc = N->wbf.ensure(sizeof(uint16_t) * N->n_params))) return rc;
-  std::vector<uint16_t> b(N->n_params);
-  for (int64_t i = 0; i < N->n_params; ++i) b[i] = host_f2bf(w[i]);
-  HIP_TRY(hipMemcpy(N->w32.p, w, sizeof(float) * N->n_params, hipMemcpyHostToDevice));
-  HIP_TRY(hipMemcpy(N->wbf.p, b.data(), sizeof(uint16_t) * N->n_params, hipMemcpyHostToDevice));
-  return FTP_OK;
-}
-
-// Transposed bf16 weights of a network to be trained (see TransposedWeights).
-int mlp_set_transposed(MlpNet* N, const float* w) {
-  if (!mlp_fused_ok(N->nin, N->nout)) return FTP_OK;
   TransposedWeights& T = N->twt;
+  const bool tr = train && mlp_fused_ok(N->nin, N->nout);
+  int64_t at[3], n = N->n_params;
   T.nin = N->width;
-  for (int l = 0; l < 3; ++l) {
+  for (int l = 0; l < 3 && tr; ++l) {
     T.oW[l] = N->oW[l + 1];
     T.nout[l] = N->nout[l + 1];
     T.ld[l] = (T.nout[l] + 31) & ~31;
-    std::vector<uint16_t> t((size_t)T.nin * T.ld[l], 0);
-    for (int o = 0; o < T.nout[l]; ++o)
-      for (int k = 0; k < T.nin; ++k) t[(size_t)k * T.ld[l] + o] = host_f2bf(w[T.oW[l] + (int64_t)o * T.nin + k]);
-    int rc;
-    if ((rc = N->wt[l].ensure(sizeof(uint16_t) * t.size()))) return rc;
-    HIP_TRY(hipMemcpy(N->wt[l].p, t.data(), sizeof(uint16_t) * t.size(), hipMemcpyHostToDevice));
-    T.p[l] = N->wt[l].as<uint16_t>();
+    at[l] = (n + 63) & ~(int64_t)63;
+    n = at[l] + (int64_t)T.nin * T.ld[l];
   }
+  if ((rc = N->w32.ensure(sizeof(float) * N->n_params))) return rc;
+  if ((rc = N->wbf.ensure(sizeof(uint16_t) * n))) return rc;
+  std::vector<uint16_t> b(n, 0);
+  for (int64_t i = 0; i < N->n_params; ++i) b[i] = host_f2bf(w[i]);
+  for (int l = 0; l < 3 && tr; ++l) {
+    // (32 columns at a time: the lines being written stay in the cache)
+    for (int k0 = 0; k0 < T.nin; k0 += 32)
+      for (int o = 0; o < T.nout[l]; ++o)
+        for (int k = k0; k < k0 + 32; ++k) b[at[l] + (int64_t)k * T.ld[l] + o] = b[T.oW[l] + (int64_t)o * T.nin + k];
+    T.p[l] = N->wbf.as<uint16_t>() + at[l];
+  }
+  HIP_TRY(hipMemcpy(N->w32.p, w, sizeof(float) * N->n_params, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(N->wbf.p, b.data(), sizeof(uint16_t) * n, hipMemcpyHostToDevice));
   return FTP_OK;
 }
 
@@ -1802,8 +1803,7 @@ int ftp_mlp_create(ftp_mlp** out, int d_in, int width, int d_out, const float* w
       }
     }
   }
-  int rc = mlp_set_weights(&N, w.data());
-  if (!rc) rc = mlp_set_transposed(&N, w.data());
+  int rc = mlp_set_weights(&N, w.data(), true);
   if (!rc) rc = N.am.ensure(sizeof(float) * N.n_params);
   if (!rc) rc = N.av.ensure(sizeof(float) * N.n_params);
   if (!rc) rc = N.grad.ensure(sizeof(float) * N.n_params);
