@@ -892,6 +892,11 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
   // thousand frequencies)
   const bool overlap_score =
       !dataset && (solver == FTP_SOLVER_LEARNED || solver == FTP_SOLVER_UNIFORM);
+  // In a graph capture an event that a kernel launch records is no node of the
+  // graph, so the side stream would not join it: the same kernels in line.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  const bool side = overlap_score &&
+                    !(st && hipStreamIsCapturing(st, &capture) == hipSuccess && capture != hipStreamCaptureStatusNone);
   // learned solver with a fusable network: features in rows of dinp bf16
   // (zero padded), then one kernel for the four layers
   const bool fused = solver == FTP_SOLVER_LEARNED && P->tune.mlp_fused && P->net.dense &&
@@ -979,7 +984,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         // the second round instead, so that the network's large workgroups
         // and the round do not wait for CU room behind the scoring's
         // wavefronts (measured: learned -15 us, uniform +11 us that way)
-        HIP_TRY(launch_newton_sturm(a, L, w_nt, T.newton_occ, st, (overlap_score && !net_list) ? P->fork_ev : nullptr));
+        HIP_TRY(launch_newton_sturm(a, L, w_nt, T.newton_occ, st, (side && !net_list) ? P->fork_ev : nullptr));
       }
       hipEvent_t rb = learn_ev();
       if (rb) HIP_TRY(hipEventRecord(rb, st));
@@ -994,8 +999,8 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
       auto fork_score = [&]() -> int {
         SolveArgs as = a;
         as.newton_cands = true;
-        HIP_TRY(hipStreamWaitEvent(P->side, P->fork_ev, 0));
-        HIP_TRY(launch_score_newton(as, rec, p0, np, w_sc, P->side, P->join_ev));
+        if (side) HIP_TRY(hipStreamWaitEvent(P->side, P->fork_ev, 0));
+        HIP_TRY(launch_score_newton(as, rec, p0, np, w_sc, side ? P->side : st, side ? P->join_ev : nullptr));
         return FTP_OK;
       };
       if (solver != FTP_SOLVER_ABERTH && overlap_score && !net_list) {
@@ -1018,7 +1023,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         HIP_TRY(launch_newton_retry(RA, (int)grid_waves(P, 64, np), st));
       }
       if (solver != FTP_SOLVER_ABERTH && overlap_score && net_list) {
-        HIP_TRY(hipEventRecord(P->fork_ev, st));
+        if (side) HIP_TRY(hipEventRecord(P->fork_ev, st));
         if ((rc = fork_score())) return rc;
       }
       hipEvent_t rt = learn_ev();
@@ -1066,7 +1071,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         // chunk's assembly rewrites the records)
         HIP_TRY(launch_score(as, rec, p0, np, std::min(w_sc, (int)grid_waves(P, 16, np)), st,
                              B.fb_list, ctr));
-        HIP_TRY(hipStreamWaitEvent(st, P->join_ev, 0));
+        if (side) HIP_TRY(hipStreamWaitEvent(st, P->join_ev, 0));
       } else {
         HIP_TRY(launch_score(as, rec, p0, np, w_sc, st));
       }
