@@ -45,7 +45,10 @@ __device__ __forceinline__ float half_sum(float v, int lane) {
 // Chamfer loss on the circle of one sample (see k_chamfer) on a half-wave: lane
 // k holds seed (ou, ov); the roots' directions are computed a root per lane and
 // read back from LDS (dir, 32 of them, this half-wave's own).  (gu, gv)
-// receives dL/d(u, v) of the lane's seed; returns L.
+// receives dL/d(u, v) of the lane's seed; returns L.  As in k_chamfer, a root
+// that no seed is within 3.4e38 of (seeds not finite) counts as nearest to seed
+// 0, so the gradients of a network that has diverged are not finite either, and
+// the terms are divided before they are added, so that none overflows early.
 __device__ __forceinline__ float chamfer_half(float ou, float ov, int Kseeds, const float* roots, int n, float lam,
                                               int lane, float2* dir, float& gu, float& gv) {
   const int hl = lane & 31, hb = lane & 32;
@@ -53,11 +56,12 @@ __device__ __forceinline__ float chamfer_half(float ou, float ov, int Kseeds, co
   float L = 0.f, best = 3.4e38f, bu = 0.f, bv = 0.f;
   gu = gv = 0.f;
   // x / n by the correctly rounded reciprocal and one residual step
-  // (Markstein: the correctly rounded quotient)
+  // (Markstein: the correctly rounded quotient); the residual of an infinite x is
+  // NaN, which the maximum drops
   const float fn = (float)(n > 0 ? n : 1), rn = 1.f / fn;
   auto over_n = [&](float x) {
     const float q = x * rn;
-    return fmaf(fmaf(-q, fn, x), rn, q);
+    return fmaf(fmaxf(fmaf(-q, fn, x), -3.4e38f), rn, q);
   };
   // (both halves run as many roots as the longer of the two samples has)
   const int nmax = max(n, __shfl_xor(n, 32));
@@ -77,8 +81,8 @@ __device__ __forceinline__ float chamfer_half(float ou, float ov, int Kseeds, co
       const float db = half_min(on ? d2 : 3.4e38f, lane);
       const unsigned hit = (unsigned)(__ballot(on && d2 == db) >> hb);
       if (has) {
-        L += db;
-        const bool mine = hit && hl == __ffs(hit) - 1;
+        L = fmaf(db, rn, L);
+        const bool mine = hl == __ffs(hit ? hit : 1u) - 1;
         gu += mine ? over_n(2.f * du) : 0.f;
         gv += mine ? over_n(2.f * dv) : 0.f;
         // nearest root of the seed
@@ -92,9 +96,9 @@ __device__ __forceinline__ float chamfer_half(float ou, float ov, int Kseeds, co
     __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
     __builtin_amdgcn_wave_barrier();
   }
-  const float back = half_sum(on ? best : 0.f, lane);
+  const float back = half_sum(on ? lam * best / Kseeds : 0.f, lane);
   if (n > 0) {
-    L = L / n + lam * back / Kseeds;
+    L += back;
     gu += lam * 2.f * bu / Kseeds;
     gv += lam * 2.f * bv / Kseeds;
   }

@@ -1,0 +1,60 @@
+"""Loss and gradients of a network whose outputs are not finite or nearly
+overflow: the row-tile kernel (width 256) and one GEMM per layer (width 48).
+Zero weights, so every output is its bias of the last layer."""
+import numpy as np
+import pytest
+
+from oracle import mlp_oracle as MO
+
+pytestmark = pytest.mark.gpu
+
+B, DIN, DOUT, R = 40, 22, 8, 12
+
+
+def _run(width, b4, lam=0.5):
+    import torch
+    import paper_2101_12348_amd as F
+
+    rng = np.random.default_rng(5)
+    w = np.zeros(F.mlp_param_count(DIN, width, DOUT), dtype=np.float32)
+    w[-DOUT:] = b4
+    net = F.Mlp(DIN, width, DOUT, weights=w)
+    X = torch.as_tensor(rng.standard_normal((B, DIN)).astype(np.float32), device="cuda").to(torch.bfloat16)
+    roots = rng.uniform(0, 2 * np.pi, (B, R)).astype(np.float32)
+    nroots = np.full(B, R, dtype=np.int32)
+    loss, grads = net.loss_grad(X, torch.as_tensor(roots, device="cuda"), torch.as_tensor(nroots, device="cuda"),
+                                lam=lam)
+    return loss.cpu().numpy(), grads.cpu().numpy()[-DOUT:], roots, nroots
+
+
+@pytest.mark.parametrize("width", [256, 48])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+def test_gradients_of_outputs_that_are_not_finite_are_not_finite(width, value):
+    loss, g, _, _ = _run(width, np.full(DOUT, value, dtype=np.float32))
+    assert np.all(~np.isfinite(g[:2]))         # seed 0 stands for the nearest
+    assert np.all((g[2:] == 0) | np.isnan(g[2:]))
+    assert np.all(loss >= 3.4e38 * 0.99)
+
+
+@pytest.mark.parametrize("width", [256, 48])
+def test_some_seeds_not_finite(width):
+    b4 = np.array([0.5, 0.5, np.nan, 0.1, 0.3, np.inf, -0.7, 0.2], dtype=np.float32)
+    loss, g, roots, nroots = _run(width, b4)
+    # every root has a nearest finite seed; the other two enter the loss with 3.4e38 lam / K each
+    keep = np.array([0, 1, 6, 7])
+    _, d = MO.chamfer_loss(np.tile(b4[keep], (B, 1)).astype(np.float64), roots.astype(np.float64), nroots, lam=0.0)
+    _, d1 = MO.chamfer_loss(np.tile(b4[keep], (B, 1)).astype(np.float64), roots.astype(np.float64), nroots, lam=1.0)
+    # (lam counts all four seeds, the oracle's call two)
+    ref = np.sum(d + 0.25 * (d1 - d), axis=0)
+    assert np.all(g[2:6] == 0)
+    assert np.max(np.abs(g[keep] - ref)) <= 1e-5
+    assert np.max(np.abs(loss / (2 * 0.5 * 3.4e38 / 4) - 1)) <= 1e-6
+
+
+@pytest.mark.parametrize("width", [256, 48])
+def test_terms_do_not_overflow_before_they_are_divided(width):
+    b4 = np.full(DOUT, 5e18, dtype=np.float32)   # squared distances of 5e37, twelve roots
+    loss, g, roots, nroots = _run(width, b4)
+    L, d = MO.chamfer_loss(np.tile(b4, (B, 1)).astype(np.float64), roots.astype(np.float64), nroots, lam=0.5)
+    assert np.max(np.abs(loss / L - 1)) <= 1e-5
+    assert np.max(np.abs(g / np.sum(d, axis=0) - 1)) <= 1e-4
