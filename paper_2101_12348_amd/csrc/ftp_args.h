@@ -74,6 +74,7 @@ struct TransposedWeights {
 struct TrainArgs {
   const uint16_t* X;        // B x din bf16
   int64_t B;
+  int64_t tile0;            // first tile of the launch (filled in by the launcher)
   int din, width, dout;
   const uint16_t* w;        // bf16 weights, layer l at w + oW[l]
   const float* w32;         // FP32 parameters (biases at w32 + ob[l])

@@ -68,7 +68,7 @@ hipError_t launch_gemm(const GemmArgs& g, hipStream_t st);
 hipError_t launch_dense(const uint16_t* A, int64_t lda, const uint16_t* W, int ldw, const float* bias, int64_t M,
                         int N, int Kp, int relu, uint16_t* Yb, float* Yf, int64_t ldy, hipStream_t st);
 hipError_t launch_col_part(const float* G, int64_t M, int N, int64_t ld, float* part, int ld_part, hipStream_t st);
-hipError_t launch_train_rows(const TrainArgs& a, hipStream_t st);
+hipError_t launch_train_rows(TrainArgs a, hipStream_t st);
 hipError_t launch_wgrad(WgradArgs a, float* grad, hipStream_t st);
 hipError_t launch_chamfer(const float* out, int64_t B, int Kseeds, const float* roots, const int* nroots, int R,
                           float lam, float* loss_b, float* dout, uint16_t* dout_bf, hipStream_t st);

@@ -4,6 +4,8 @@
 // with the activations in LDS (k_train_rows); the weight gradients are one
 // split-K launch for the four layers (k_wgrad), and one launch adds the
 // partial sums of weights and biases in a fixed order (k_grad_reduce).
+#include <algorithm>
+
 #include "ftp_args.h"
 #include "ftp_mlp_tile.h"
 #include "ftp_solve_common.h"
@@ -133,9 +135,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_train_rows(TrainArgs a) {
   __shared__ float2 dir[kTileRows][32];                             // directions of the roots
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int mrow = lane & 15, n = 16 * wave + mrow;   // this lane's column of a layer
-  const int64_t row0 = (int64_t)blockIdx.x * kTileRows;
+  const int64_t tile = a.tile0 + blockIdx.x, row0 = tile * kTileRows;
   const int W = a.width;
-  float* part = a.bias_part + (int64_t)blockIdx.x * (3 * W + a.dout);
+  float* part = a.bias_part + tile * (3 * W + a.dout);
   bf16x8_t f0[8], f1[8];
   tile_load_b(a.w + a.oW[0], a.din, a.din, W, n, lane, f0);
   // rows of X, zero-padded to whole K slices and past the batch
@@ -416,14 +418,23 @@ __global__ __launch_bounds__(256) void k_grad_reduce(WgradArgs a, float* grad) {
   if (lane == 0) grad[a.ob[l] + c] = s;
 }
 
-hipError_t launch_train_rows(const TrainArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(k_train_rows, dim3((unsigned)((a.B + kTileRows - 1) / kTileRows)), dim3(64 * kTileWaves), 0, st, a);
+// Tiles of a launch: a grid of 2^32 threads and more is cut short without an
+// error, so larger batches take several launches.
+constexpr int64_t kLaunchTiles = 1 << 21;
+
+hipError_t launch_train_rows(TrainArgs a, hipStream_t st) {
+  const int64_t tiles = (a.B + kTileRows - 1) / kTileRows;
+  for (a.tile0 = 0; a.tile0 < tiles; a.tile0 += kLaunchTiles)
+    hipLaunchKernelGGL(k_train_rows, dim3((unsigned)std::min(kLaunchTiles, tiles - a.tile0)), dim3(64 * kTileWaves), 0,
+                       st, a);
   return hipGetLastError();
 }
 
 hipError_t launch_col_part(const float* G, int64_t M, int N, int64_t ld, float* part, int ld_part, hipStream_t st) {
-  hipLaunchKernelGGL(k_col_part, dim3((unsigned)((M + kTileRows - 1) / kTileRows), (unsigned)((N + 255) / 256)),
-                     dim3(256), 0, st, G, M, N, ld, part, ld_part);
+  const int64_t tiles = (M + kTileRows - 1) / kTileRows;
+  for (int64_t t = 0; t < tiles; t += kLaunchTiles)
+    hipLaunchKernelGGL(k_col_part, dim3((unsigned)std::min(kLaunchTiles, tiles - t), (unsigned)((N + 255) / 256)),
+                       dim3(256), 0, st, G + t * kTileRows * ld, M - t * kTileRows, N, ld, part + t * ld_part, ld_part);
   return hipGetLastError();
 }
 
