@@ -15,6 +15,7 @@ struct LearnArgs {
   unsigned int* fb_count;
   unsigned flags;           // bit 0: forced fallback (every pair to the list); bit 1: 2H starts only
   const double2* starts;    // H <= 10: evenly spaced starts per rotation (k_start_table)
+  int per;                  // H <= 5 and H >= 12: frequencies per wavefront (newton_per)
 };
 
 // Second Newton round over the first round's list (k_newton_retry).

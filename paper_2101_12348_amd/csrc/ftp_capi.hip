@@ -84,7 +84,7 @@ hipError_t launch_labels(const double* rec, int H, int64_t np, float* roots, int
 hipError_t launch_root_counts(const double* rec, int H, int64_t np, int* sturm, int* real, int waves,
                               hipStream_t st);
 bool newton_four_per_wave(int H);
-hipError_t launch_newton_sturm(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st,
+hipError_t launch_newton_sturm(const SolveArgs& a, LearnArgs L, int waves, int occ, int n_cu, hipStream_t st,
                                hipEvent_t done = nullptr);
 hipError_t launch_aberth(const AberthArgs& A, int waves, hipStream_t st);
 bool mlp_fused_ok(const int* nin, const int* nout);
@@ -984,7 +984,7 @@ int run_solve_with(ftp_plan* P, const SolveArgs& a0, int64_t n_pairs, const Solv
         // the second round instead, so that the network's large workgroups
         // and the round do not wait for CU room behind the scoring's
         // wavefronts (measured: learned -15 us, uniform +11 us that way)
-        HIP_TRY(launch_newton_sturm(a, L, w_nt, T.newton_occ, st, (side && !net_list) ? P->fork_ev : nullptr));
+        HIP_TRY(launch_newton_sturm(a, L, w_nt, T.newton_occ, P->n_cu, st, (side && !net_list) ? P->fork_ev : nullptr));
       }
       hipEvent_t rb = learn_ev();
       if (rb) HIP_TRY(hipEventRecord(rb, st));

@@ -683,8 +683,8 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
   return c;
 }
 
-// Eight frequencies per wavefront (four where there are few and H > 5), consecutive ones
-// of the list.  Their Sturm chains run side by side, a group of lanes each
+// Eight frequencies per wavefront (where there are few, four for H > 5 and down to two
+// for H <= 5, newton_per), consecutive ones of the list.  Their Sturm chains run side by side, a group of lanes each
 // (sturm_count_groups); then Newton runs on two of them at a time, lanes
 // 0..31 for the first and 32..63 for the second, each half with min(32, D)
 // starts: the 2H network seeds and min(32, D) - 2H evenly spaced phases (all
@@ -871,7 +871,6 @@ template <int H, int OCC, int G>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
   constexpr int D = 6 * H - 2, RM = sturm_coefs(D, G);
-  constexpr int NC = 64 / G;   // frequencies per wavefront
   constexpr int DP = newton_top(D), FS = DP + 2;   // f and its reversal of the two at hand, 16-byte aligned
   const int lane = threadIdx.x & 63, row = lane / G, l = lane & (G - 1);
   const RecLayout RL(H);
@@ -879,10 +878,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
   const int half = lane >> 5, hl = lane & 31;
   double* fh = sml + 2 * FS * half;
   for (int k = D + 1 + hl; k <= DP; k += 32) fh[k] = fh[FS + k] = 0.0;
-  for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
-    // this group's frequency (inactive: past the end, rejected lightcurve, or P
-    // constant in theta_2)
-    bool mine = w0 + row < L.np;
+  const int per = D < 32 ? L.per : 64 / G;   // frequencies per wavefront, even
+  for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < L.np; w0 += per * (int64_t)gridDim.x) {
+    // this group's frequency (inactive: no turn, past the end, rejected lightcurve,
+    // or P constant in theta_2)
+    bool mine = row < per && w0 + row < L.np;
     double* Rr = L.rec + (w0 + (mine ? row : 0)) * (int64_t)RL.stride;
     const int st = (int)Rr[RL.meta + M_STATUS];
     mine = mine && st != ST_BAD_LC && st != ST_CONSTANT;
@@ -918,11 +918,11 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
     double v0, v1;
     fetch(0, v0, v1);
 #pragma unroll 1
-    for (int p = 0; p < NC / 2; ++p) {
+    for (int p = 0; p < per / 2; ++p) {
       if (hl <= D) fh[hl] = fh[FS + D - hl] = v0;
       if (D >= 32 && hl + 32 <= D) fh[hl + 32] = fh[FS + D - 32 - hl] = v1;
       lwave_sync();
-      if (p + 1 < NC / 2) fetch(p + 1, v0, v1);
+      if (p + 1 < per / 2) fetch(p + 1, v0, v1);
       newton_pair<H>(L, RL, w0 + 2 * p, __builtin_amdgcn_readlane(cnt, 2 * p * G),
                      __builtin_amdgcn_readlane(cnt, (2 * p + 1) * G), sml, lane, acc);
     }
@@ -937,8 +937,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
 }
 
 // Above H = 10: one frequency per wavefront at H = 11 (NC = 1, D = 64: the Sturm
-// chain of f in registers, the degree-64 coefficient as a scalar), four above (NC
-// = 4: their double-double chains run side by side), then for each of them Newton
+// chain of f in registers, the degree-64 coefficient as a scalar), up to four above
+// (NC = 4: their double-double chains run side by side), then for each of them Newton
 // from 4H starts (the 2H network seeds and 2H evenly spaced phases; all evenly
 // spaced without network), stepped on the Cayley polynomial and merged one root
 // per pass, with the stop rule of k_newton_sturm4.
@@ -956,11 +956,12 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const RecLayout RL(H);
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long iters_acc = 0, roots_acc = 0, fb_acc = 0;
-  for (int64_t w0 = NC * (int64_t)blockIdx.x; w0 < L.np; w0 += NC * (int64_t)gridDim.x) {
+  const int per = NC > 1 ? L.per : 1;
+  for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < L.np; w0 += per * (int64_t)gridDim.x) {
     // Sturm counts first: an ill-determined count (or fewer than the two real
     // roots every non-constant P has) sends the frequency on without Newton
     const int row = NC > 1 ? lane >> 4 : 0;
-    bool mine = w0 + row < L.np;
+    bool mine = row < per && w0 + row < L.np;
     double* Rr = L.rec + (w0 + (mine ? row : 0)) * (int64_t)RL.stride;
     const int st = (int)Rr[RL.meta + M_STATUS];
     mine = mine && st != ST_BAD_LC && st != ST_CONSTANT;
@@ -977,7 +978,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
     if (cnts < 2) cnts = -1;
     if (!mine) cnts = -2;
 #pragma unroll 1
-    for (int p = 0; p < NC; ++p) {
+    for (int p = 0; p < per; ++p) {
       const int cnt = __builtin_amdgcn_readlane(cnts, 16 * p);
       if (cnt == -2) continue;
       const int64_t w = w0 + p;
@@ -1292,10 +1293,27 @@ hipError_t launch_newton_retry(const RetryArgs& A, int waves, hipStream_t st) {
 
 bool newton_four_per_wave(int H) { return 6 * H - 2 < 64; }
 
+// Frequencies per wavefront of the first round: nc (a group of lanes each), fewer
+// where that would leave less than `waves` wavefronts: their Newton iterations follow
+// one another in a wavefront, so that few frequencies in few wavefronts wait for
+// each other on an idle device.  A multiple of `step`, the frequencies Newton takes
+// at once.  Measured on given sums, 2 / 4 / 8 per wavefront: H = 5 71 / 76 / 82 us at
+// 100 frequencies, 91 / 97 / 106 at 4000, 104 / 104 / 111 at 8000, 128 / 121 / 126 at
+// 16000.  H = 12, 1 / 2 / 3 / 4 per wavefront: 124 / 133 / 139 / 149 us at 100, 133 /
+// 139 / 149 / 155 at 1000, 164 / 142 / 151 / 160 at 2000, 242 / 191 / 204 / 179 at 4000.
+// So the line lies at eight wavefronts per compute unit up to H = 5 and at four above
+// H = 11.
+static int newton_per(int64_t np, int nc, int step, int64_t waves) {
+  const int64_t per = (np + waves - 1) / waves;
+  return (int)std::min<int64_t>(nc, (per + step - 1) / step * step);
+}
+
 template <int H, int G>
-static void launch_newton_g(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+static void launch_newton_g(const SolveArgs& a, LearnArgs L, int waves, int occ, int n_cu, hipStream_t st,
+                            hipEvent_t done) {
   const size_t lds = (size_t)4 * (newton_top(6 * H - 2) + 2) * sizeof(double);   // f and its reversal of two frequencies
   const dim3 grid((unsigned)waves), block(64);
+  if (6 * H - 2 < 32) L.per = newton_per(L.np, 64 / G, 2, 8 * (int64_t)n_cu);
   if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6, G>), grid, block, lds, st, nullptr, done, 0, a, L);
   else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5, G>), grid, block, lds, st, nullptr, done, 0, a, L);
 }
@@ -1309,11 +1327,12 @@ static void launch_newton_g(const SolveArgs& a, const LearnArgs& L, int waves, i
 constexpr int64_t kEightLanesFrom = 100000;
 
 template <int H>
-static void launch_newton_h(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+static void launch_newton_h(const SolveArgs& a, const LearnArgs& L, int waves, int occ, int n_cu, hipStream_t st,
+                            hipEvent_t done) {
   if constexpr (6 * H - 2 >= 32) {
-    if (L.np < kEightLanesFrom) return launch_newton_g<H, 16>(a, L, waves, occ, st, done);
+    if (L.np < kEightLanesFrom) return launch_newton_g<H, 16>(a, L, waves, occ, n_cu, st, done);
   }
-  launch_newton_g<H, 8>(a, L, waves, occ, st, done);
+  launch_newton_g<H, 8>(a, L, waves, occ, n_cu, st, done);
 }
 
 hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st) {
@@ -1321,20 +1340,22 @@ hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_newton_sturm(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st,
+hipError_t launch_newton_sturm(const SolveArgs& a, LearnArgs L, int waves, int occ, int n_cu, hipStream_t st,
                                hipEvent_t done) {
   switch (a.H) {
-#define FTP_NEWTON(h) case h: launch_newton_h<h>(a, L, waves, occ, st, done); break;
+#define FTP_NEWTON(h) case h: launch_newton_h<h>(a, L, waves, occ, n_cu, st, done); break;
     FTP_NEWTON(1) FTP_NEWTON(2) FTP_NEWTON(3) FTP_NEWTON(4) FTP_NEWTON(5)
     FTP_NEWTON(6) FTP_NEWTON(7) FTP_NEWTON(8) FTP_NEWTON(9) FTP_NEWTON(10)
 #undef FTP_NEWTON
     default:
-      if (a.H == 11)
+      if (a.H == 11) {
         hipExtLaunchKernelGGL(k_newton_sturm<1>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
                               done, 0, a, L);
-      else
+      } else {
+        L.per = newton_per(L.np, 4, 1, 4 * (int64_t)n_cu);
         hipExtLaunchKernelGGL(k_newton_sturm<4>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
                               done, 0, a, L);
+      }
   }
   return hipGetLastError();
 }
