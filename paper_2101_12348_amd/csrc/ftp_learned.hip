@@ -1092,53 +1092,52 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   }
 }
 
+// Lanes per Sturm chain up to H = 10: eight, so eight frequencies per wavefront, where
+// that leaves the device two rounds of resident wavefronts; with fewer frequencies
+// sixteen (four per wavefront) fill it more evenly, except up to degree 31, where
+// eight lanes are also the shorter chain.  Measured with 8 / 16 lanes, whole
+// periodograms: H = 6 311 / 305 us at 50 thousand frequencies, 475 / 473 at 100, 755 /
+// 810 at 200; H = 10 418 / 405, 655 / 675 and 1140 / 1170.
+constexpr int64_t kEightLanesFrom = 100000;
+__host__ constexpr int sturm_lanes(int H, int64_t np) { return 6 * H - 2 < 32 || np >= kEightLanesFrom ? 8 : 16; }
+
 // Root counts of a record chunk (diagnostic of the count the learned and
 // uniform solvers trust): per pair, the Sturm count of the Cayley polynomial
-// f by the device code the Newton kernels use (sturm_count_groups, four pairs
-// per wavefront, for H <= 10; sturm_count_line_reg for H = 11,
-// sturm_count_dd above), -1000 - n when the
-// chain fails its test (n: the count it reached regardless), -2 for an
+// f by the device code the Newton kernels use on such a chunk
+// (sturm_count_groups for H <= 10, with G = sturm_lanes lanes per pair;
+// sturm_count_line_reg, G = 64, for H = 11; sturm_count_dd, DD, above), -1000 - n
+// when the chain fails its test (n: the count it reached regardless), -2 for an
 // inactive pair; and the number of real
 // eigenvalues the companion QR (run before this kernel) marked in M_REAL_LO,
 // M_REAL_HI and M_REAL_X (-1 when the QR did not converge).
+template <int G, bool DD>
 __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, int64_t np, int* sturm, int* real) {
-  const int lane = threadIdx.x & 63;
+  constexpr int per = 64 / G;
+  const int lane = threadIdx.x & 63, row = lane / G, l = lane & (G - 1);
   const int D = 6 * H - 2;
   const RecLayout RL(H);
-  const int G = D < 64 ? 8 : (D > 64 ? 16 : 64);
-  const int per = 64 / G;
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < np; w0 += per * (int64_t)gridDim.x) {
-    int cnt;
-    if (D < 64) {
-      const int row = lane / G, l = lane & (G - 1);
-      const bool in = w0 + row < np;
-      const double* f = rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f;
-      int raw;
+    const bool in = w0 + row < np;
+    const double* f = rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f;
+    int cnt, raw;
+    if constexpr (DD) {
+      cnt = sturm_count_dd(f, in, D, lane, raw);
+    } else if constexpr (G == 64) {
+      cnt = sturm_count_line_reg(f[lane], f[D], D, lane, raw);
+    } else {
       const double gtop = in ? f[D] : 0.0;
-      if (sturm_coefs(D, 8) == 4) {
+      if (G == 16 || sturm_coefs(D, G) == 4) {
         double C[4];
         load_coefficients(f, in, D, l, C);
-        cnt = sturm_count_groups<8>(C, gtop, D, lane, raw);
+        cnt = sturm_count_groups<G>(C, gtop, D, lane, raw);
       } else {
         double C[8];
         load_coefficients(f, in, D, l, C);
-        cnt = sturm_count_groups<8>(C, gtop, D, lane, raw);
+        cnt = sturm_count_groups<G>(C, gtop, D, lane, raw);
       }
-      if (cnt < 0) cnt = -1000 - raw;
-      cnt = __shfl(cnt, (lane * G) & 63);   // pair `lane` of the group to lane `lane`
-    } else if (D > 64) {
-      const int row = lane >> 4;
-      const bool in = w0 + row < np;
-      int raw;
-      cnt = sturm_count_dd(rec + (w0 + (in ? row : 0)) * (int64_t)RL.stride + RL.f, in, D, lane, raw);
-      if (cnt < 0) cnt = -1000 - raw;
-      cnt = __shfl(cnt, (lane * 16) & 63);
-    } else {
-      const double* RA = rec + w0 * (int64_t)RL.stride;
-      int raw;
-      cnt = sturm_count_line_reg(RA[RL.f + lane], RA[RL.f + D], D, lane, raw);
-      if (cnt < 0) cnt = -1000 - raw;
     }
+    if (cnt < 0) cnt = -1000 - raw;
+    cnt = __shfl(cnt, (lane * G) & 63);   // pair `lane` of the wavefront to lane `lane`
     if (lane < per && w0 + lane < np) {
       const double* Rq = rec + (w0 + lane) * (int64_t)RL.stride;
       const int st = (int)Rq[RL.meta + M_STATUS];
@@ -1154,7 +1153,11 @@ __global__ __launch_bounds__(64) void k_root_counts(const double* rec, int H, in
 
 hipError_t launch_root_counts(const double* rec, int H, int64_t np, int* sturm, int* real, int waves,
                               hipStream_t st) {
-  hipLaunchKernelGGL(k_root_counts, dim3((unsigned)waves), dim3(64), 0, st, rec, H, np, sturm, real);
+  const dim3 grid((unsigned)waves), block(64);
+  if (H > 11) hipLaunchKernelGGL((k_root_counts<16, true>), grid, block, 0, st, rec, H, np, sturm, real);
+  else if (H == 11) hipLaunchKernelGGL((k_root_counts<64, false>), grid, block, 0, st, rec, H, np, sturm, real);
+  else if (sturm_lanes(H, np) == 16) hipLaunchKernelGGL((k_root_counts<16, false>), grid, block, 0, st, rec, H, np, sturm, real);
+  else hipLaunchKernelGGL((k_root_counts<8, false>), grid, block, 0, st, rec, H, np, sturm, real);
   return hipGetLastError();
 }
 
@@ -1318,19 +1321,11 @@ static void launch_newton_g(const SolveArgs& a, LearnArgs L, int waves, int occ,
   else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5, G>), grid, block, lds, st, nullptr, done, 0, a, L);
 }
 
-// Eight lanes per Sturm chain, so eight frequencies per wavefront, where that leaves
-// the device two rounds of resident wavefronts; with fewer frequencies four per
-// wavefront (sixteen lanes) fill it more evenly, except up to degree 31, where
-// eight lanes are also the shorter chain.  Measured with 8 / 16 lanes, whole
-// periodograms: H = 6 311 / 305 us at 50 thousand frequencies, 475 / 473 at 100, 755 /
-// 810 at 200; H = 10 418 / 405, 655 / 675 and 1140 / 1170.
-constexpr int64_t kEightLanesFrom = 100000;
-
 template <int H>
 static void launch_newton_h(const SolveArgs& a, const LearnArgs& L, int waves, int occ, int n_cu, hipStream_t st,
                             hipEvent_t done) {
-  if constexpr (6 * H - 2 >= 32) {
-    if (L.np < kEightLanesFrom) return launch_newton_g<H, 16>(a, L, waves, occ, n_cu, st, done);
+  if constexpr (sturm_lanes(H, 0) == 16) {
+    if (sturm_lanes(H, L.np) == 16) return launch_newton_g<H, 16>(a, L, waves, occ, n_cu, st, done);
   }
   launch_newton_g<H, 8>(a, L, waves, occ, n_cu, st, done);
 }
