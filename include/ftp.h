@@ -152,8 +152,9 @@ typedef struct {
   int mlp_fused;        /* learned: 1 = one kernel for the four network layers (LDS-staged
                            weights, activations kept per wavefront), 0 = four GEMM
                            launches; identical results */
-  int newton_occ;       /* Newton + Sturm (H <= 10): the build compiled for 4, 5 or 6
-                           resident wavefronts per SIMD (fewer registers per lane at more) */
+  int newton_occ;       /* Newton + Sturm (H <= 10): the build compiled for 5 or 6
+                           resident wavefronts per SIMD (fewer registers per lane at 6);
+                           4 selects the build for 5 */
 } ftp_tuning;
 
 #define FTP_TUNE_FORCE 1u   /* ftp_autotune: measure even if the cache holds an entry */

@@ -2036,7 +2036,7 @@ int ftp_autotune(ftp_plan* P, const double* t, const double* y, const double* si
   const int cand[] = {4, 8, 12, 16, 24, 32, 48, 64, 128, 256};
   const int ncand = (int)(sizeof(cand) / sizeof(cand[0]));
   const int cand01[] = {0, 1};
-  const int cand_occ[] = {4, 5, 6};
+  const int cand_occ[] = {5, 6};   // (4 selects the build for 5)
   auto measure = [&](float* best) -> int {
     P->tune = cur;
     float m0 = 0.f, m1 = 0.f;
@@ -2054,10 +2054,10 @@ int ftp_autotune(ftp_plan* P, const double* t, const double* y, const double* si
     if ((rc = measure(&best_ms))) break;
     const bool is_mlp = knobs[k] == &cur.mlp_fused, is_occ = knobs[k] == &cur.newton_occ;
     const int* cv = is_mlp ? cand01 : (is_occ ? cand_occ : cand);
-    const int ncv = is_mlp ? 2 : (is_occ ? 3 : ncand);
+    const int ncv = is_mlp || is_occ ? 2 : ncand;
     for (int ci = 0; ci < ncv; ++ci) {
       const int v = cv[ci];
-      if (v == best_v) continue;
+      if (v == best_v || (is_occ && v == 5 && best_v == 4)) continue;
       const int keep = *knobs[k];
       *knobs[k] = v;
       float m = 0.f;

@@ -695,9 +695,9 @@ __device__ __forceinline__ bool newton_settled(double sc, double& prev) {
 //
 // Bound by vector issue and the latency of its serial chains (67 % of the
 // slots at six wavefronts per SIMD), so H is a template parameter: strides, loop
-// counts and LDS offsets are immediates, and five wavefronts fit without spills.
-// Six spill some 12 registers (1.37 GB moved at H = 10, 300 thousand frequencies,
-// where 0.29 are needed) in the same time: the traffic hides behind the issue.
+// counts and LDS offsets are immediates and few registers spill (see OCC below).  The
+// six-wave build moves 1.37 GB at H = 10 (300 thousand frequencies), where 0.29 are
+// needed, in the same time as the five-wave one: the traffic hides behind the issue.
 // That, the merge of both halves per pass (its scalar half
 // shortened in a second step, 6 %), the tabulated starts, phases left to the
 // scoring and eight lanes per Sturm chain also above degree 31 (10 %): H = 10, 300
@@ -864,9 +864,10 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
 }
 
 // OCC: resident wavefronts per SIMD the register allocation is made for (5: up
-// to 96 VGPRs, 6: up to 80, some 12 spilled); which is faster depends on the
-// workload and the grid (512 lightcurves at H = 4 37.5 ms at five, 36.9 at six; H =
-// 10 the same), so the launch shape picks it (below 5 takes the former).
+// to 96 VGPRs, 6: up to 80); which is faster depends on the workload and the grid
+// (512 lightcurves at H = 4 37.5 ms at five, 36.9 at six; H = 10 the same), so the
+// launch shape picks it (4 takes the former).  Spilled registers at five / six: 6-8 /
+// 14-20 with sixteen lanes per chain or H <= 5, 20-28 / 32-53 with eight above.
 template <int H, int OCC, int G>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
