@@ -540,10 +540,11 @@ template <int NSL>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_score(SolveArgs a, const double* rec, int64_t p0, int64_t np,
                                                                                       const int64_t* list,
                                                                                       const unsigned* list_n) {
-  // the fallback tiers run beside the side stream's scoring: their waves
-  // take issue priority over it on a shared SIMD (the tiers are few, latency-bound
-  // waves on the step's critical path)
-  __builtin_amdgcn_s_setprio(2);
+  // On a list this is the last of the fallback tiers, whose waves take issue priority
+  // over the side stream's scoring on a shared SIMD (the tiers are few, latency-bound
+  // waves on the step's critical path); without one it may be that scoring itself
+  // (H >= 11).
+  if (list) __builtin_amdgcn_s_setprio(2);
   extern __shared__ double sms[];
   const int lane = wave_lane();
   const int H = a.H, K = 3 * H - 1, D = 2 * K;
