@@ -138,8 +138,9 @@ typedef struct {
 } ftp_stats;
 
 /* Launch shapes of the per-frequency kernels, in wavefronts per compute
- * unit (1..256), and the implementation of the network's forward pass.  They change timing only: every frequency is computed by one
- * wavefront whatever the grid, so results are identical for every setting.
+ * unit (1..256), and the implementation of the network's forward pass.  They
+ * change timing only: every frequency sees the same arithmetic whatever the
+ * grid, so results are identical for every setting.
  * The companion-QR and Aberth kernels, whose work per frequency varies with
  * their iteration counts, take frequencies from a work queue; assembly,
  * Newton + Sturm and scoring stride over them. */

@@ -19,12 +19,15 @@ FLAGS = [
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC,
 ]
 # Per-file code generation flags (each file's device code is compiled on its
-# own: no kernel calls device code of another file).  The assembly, scoring,
-# companion-QR and Aberth kernels are built without machine-level loop-invariant
+# own: no kernel calls device code of another file).  The assembly, scoring
+# and Aberth kernels are built without machine-level loop-invariant
 # code motion, which otherwise keeps constants of their loop bodies in vector
 # registers for the whole loop and pushes them past their register budgets
 # (measured: assembly, scoring and the Aberth tier faster without it); the
-# Newton kernel's short loops gain from the motion and keep it.
+# Newton kernel's short loops gain from the motion and keep it, and so does the
+# companion QR, far from its budget (with / without: H = 13 uniform, 65 matrices of
+# N = 76, 2.77 / 2.95 ms; N = 16 166 / 169 us; N = 34 and 28 the same; N = 58 24.9 /
+# 24.7 ms).
 FILE_FLAGS = {
     "ftp_solve.hip": ["-mllvm", "-disable-machine-licm"],
     "ftp_aberth.hip": ["-mllvm", "-disable-machine-licm"],

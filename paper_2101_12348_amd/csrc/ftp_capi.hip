@@ -74,7 +74,6 @@ hipError_t launch_chamfer(const float* out, int64_t B, int Kseeds, const float* 
                           float lam, float* loss_b, float* dout, uint16_t* dout_bf, hipStream_t st);
 hipError_t launch_adam(float* w, uint16_t* wb, const float* g, float* m, float* v, int64_t n, float lr, float b1,
                        float b2, float eps, float c1, float c2, const TransposedWeights& wt, hipStream_t st);
-hipError_t launch_f32_to_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t st);
 hipError_t launch_features(double* rec, int H, int64_t np, uint16_t* X, int64_t ldx, int waves, hipStream_t st,
                            const int64_t* list = nullptr, const unsigned* list_count = nullptr);
 hipError_t launch_start_table(double2* out, int H, bool equal, hipStream_t st);

@@ -1,7 +1,7 @@
 // Learned root proposal (a project addition to the method): Newton on the
 // real phase polynomial from network seeds, verified by a Sturm count.
 //
-// For each frequency (one wavefront):
+// For each frequency:
 //   * the number of distinct real roots of R is counted with a Sturm sequence
 //     of the Cayley polynomial f(x) (theta = phi0 + 2 atan x) over the whole
 //     real line;
@@ -12,17 +12,18 @@
 //     each step evaluated on the Cayley polynomial f with the iterate kept as
 //     tan((theta - phi0) / 2) or its reciprocal (newton_u_step); converged
 //     roots closer than 1e-8 rad are merged, one root per pass, after every
-//     iteration from the fourth, and Newton stops once the merged roots reach
-//     the count;
+//     iteration from the second that leaves as many converged, and Newton stops
+//     once the merged roots reach the count;
 //   * if they do, the Newton roots are the candidate set; otherwise the
 //     frequency goes to the Aberth iteration (then, if that does not
 //     converge, to the companion-matrix solve) through device work lists.
-// For H <= 10 a wavefront takes eight frequencies, or four (k_newton_sturm4): their
+// For H <= 10 a wavefront takes up to eight frequencies (k_newton_sturm4): their
 // Sturm sequences run one per group of eight or sixteen lanes with up to eight
-// coefficients per lane in registers, and Newton runs on two of them at a time (32 starts each, at most D).  For H = 11 a wavefront takes one
-// (k_newton_sturm, 4H starts), its Sturm sequence one coefficient per lane (the
-// degree-64 coefficient carried as a scalar; see sturm_begin); above, four whose
-// sequences run in double-double, a 16-lane row each (sturm_count_dd).
+// coefficients per lane in registers, and Newton runs on two of them at a time (32
+// starts each, at most D).  For H = 11 a wavefront takes one (k_newton_sturm, 4H
+// starts), its Sturm sequence one coefficient per lane (the degree-64 coefficient
+// carried as a scalar; see sturm_begin); above, up to four whose sequences run in
+// double-double, a 16-lane row each (sturm_count_dd).
 #include <hip/hip_ext.h>
 #include "ftp_solve_common.h"
 #include "ftp_args.h"
@@ -207,14 +208,15 @@ __device__ __forceinline__ dd dd_rcp(dd y) {
   return dd_quick(r, r * e);
 }
 __device__ __forceinline__ dd dd_ldexp(dd x, int e) { return dd{ldexp(x.hi, e), ldexp(x.lo, e)}; }
-// Lane `addr` / 4 of the wavefront, and the previous lane of the 16-lane row.
-__device__ __forceinline__ double row_bperm_d(int addr, double v) {
+// v from lane addr / 4 (ds_bpermute, all lanes active)
+__device__ __forceinline__ double bperm_d(int addr, double v) {
   const unsigned long long u = (unsigned long long)__double_as_longlong(v);
   const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u & 0xffffffffull));
   const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u >> 32));
   return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
-__device__ __forceinline__ dd dd_bperm(int addr, dd v) { return dd{row_bperm_d(addr, v.hi), row_bperm_d(addr, v.lo)}; }
+__device__ __forceinline__ dd dd_bperm(int addr, dd v) { return dd{bperm_d(addr, v.hi), bperm_d(addr, v.lo)}; }
+// Value of the previous lane of the 16-lane row.
 __device__ __forceinline__ dd dd_ror1(dd v) { return dd{dpp_d<0x121>(v.hi), dpp_d<0x121>(v.lo)}; }   // row_ror:1
 
 // Sturm chains for 64 < D < 96 in double-double, four per wavefront, one per
@@ -350,14 +352,6 @@ __device__ int sturm_count_dd(const double* f, bool on, int D, int lane, int& ra
   sturm_dd_step<1>(A, B, S, 1, l, row4);
   raw = D - 2 * S.vp;
   return S.ok ? raw : -1;
-}
-
-// v from lane addr / 4 (ds_bpermute, all lanes active)
-__device__ __forceinline__ double bperm_d(int addr, double v) {
-  const unsigned long long u = (unsigned long long)__double_as_longlong(v);
-  const int lo = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u & 0xffffffffull));
-  const int hi = __builtin_amdgcn_ds_bpermute(addr, (int)(unsigned)(u >> 32));
-  return __longlong_as_double((long long)(((unsigned long long)(unsigned)hi << 32) | (unsigned)lo));
 }
 
 // Sturm chains, one per group of G lanes (8: eight per wavefront; 16: four), D <

@@ -325,11 +325,6 @@ __global__ __launch_bounds__(256) void k_adam(float* w, uint16_t* wb, const floa
   }
 }
 
-__global__ __launch_bounds__(256) void k_f32_to_bf16(const float* x, uint16_t* y, int64_t n) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i < n) y[i] = f2bf(x[i]);
-}
-
 // Network features of pairs [0, np) of a record chunk (one wavefront per
 // pair), written to X (row stride ldx >= 2 (D + 1), the rest of the row
 // zeroed); the canonical rotation goes to the record for the Newton kernel.
@@ -622,11 +617,6 @@ hipError_t launch_adam(float* w, uint16_t* wb, const float* g, float* m, float* 
                        float b2, float eps, float c1, float c2, const TransposedWeights& wt, hipStream_t st) {
   hipLaunchKernelGGL(k_adam, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, w, wb, g, m, v, n, lr, b1, b2,
                      eps, c1, c2, wt);
-  return hipGetLastError();
-}
-
-hipError_t launch_f32_to_bf16(const float* x, uint16_t* y, int64_t n, hipStream_t st) {
-  hipLaunchKernelGGL(k_f32_to_bf16, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, x, y, n);
   return hipGetLastError();
 }
 

@@ -631,7 +631,7 @@ __device__ __forceinline__ void cs_pi(double x, double& s, double& c) { sincospi
 // Of the last pass only the k whose modes are gathered are written (half of them
 // at an oversampling of two).
 //
-// Bound by memory latency at four wavefronts per SIMD (40-70 % of the issue
+// Bound by memory latency at four wavefronts per SIMD, two in FP64 (40-70 % of the issue
 // slots, the most in earlier passes, whose twiddles cost a sine and cosine per
 // element).  Against one radix-4 step per trip through LDS (FP32, then FP64): a
 // grid pair of 2^24 + 2^23 points 344 -> 249 us and 660 -> 485 us for three passes,

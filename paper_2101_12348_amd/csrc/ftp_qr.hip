@@ -139,7 +139,7 @@ __host__ __device__ inline constexpr int qr_doubles(int N, int G) { return (hcol
 //
 // Bound: a pass is one serial chain (two reflectors, an LDS round trip, the
 // broadcasts) of ~170 instructions that a lone wavefront issues in ~1700
-// cycles, so throughput is the matrices in flight (LDS capacity: 11 per CU at
+// cycles, so throughput is the matrices in flight (LDS capacity: ten per CU at
 // N = 58) until the vector issue limits it (near half of its slots are used).
 // Two steps per pass halve the LDS traffic and share the addressing; packed
 // columns double the matrices in flight against a dense matrix.  Measured

@@ -3,8 +3,8 @@
 // companion matrix, and the scoring of every root (Section 2: the phase
 // condition is necessary, not sufficient, so each solution is scored).
 //
-// Three kernels, one wavefront per trial frequency, exchanging a per-pair
-// record through HBM (RecLayout):
+// Three kernels, each with as many trial frequencies per wavefront as fill it,
+// exchanging a per-pair record through HBM (RecLayout):
 //   k_assemble : gather and deconvolve the NFFT sums (or read given sums);
 //                assemble mu (MM), eta (YM) and the trig coefficients r_d of
 //                R(theta) = i psi^{-K} p(psi), K = 3H - 1; pick a rotation
@@ -15,7 +15,8 @@
 //   k_qr       : eigenvalues of the real companion matrix of f (ftp_qr.hip);
 //   k_score    : P = YM^2 / (YY MM) at every candidate, best by P with the
 //                documented tie rule, Newton polish on R(theta) kept only if P
-//                does not drop, outputs theta_2, theta_1, theta_3.
+//                does not drop, outputs theta_2, theta_1, theta_3 (k_score4: the
+//                same for Newton's roots up to H = 10, without the polish).
 #include <hip/hip_ext.h>
 #include "ftp_solve_common.h"
 
@@ -409,7 +410,7 @@ __global__ __launch_bounds__(64 * kAsmWaves) __attribute__((amdgpu_waves_per_eu(
     const int k0 = hm ? __ffs(hm) - 1 : 0;
     const double phi0 = constant ? 0.0 : kTwoPi * k0 / 16.0;
     const bool write = has && !bad;
-    if (HT >= 11 || (HT == 0 && D >= 64)) {
+    if (HT == 0 && D >= 64) {
       f_by_horner(W, scr, K, D, hl, k0, tab_c, tab_s, write && !constant, Rr + RL.f);
     } else {
       // 2 rho_j = 2 r_{j-K} e^{i (j-K) phi0}, j = 0..K - 1, and rho_K (every lane
@@ -705,9 +706,6 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   }
 }
 
-
-// Writes the deconvolved sums of every pair (3H complex per pair: Z_w(k j),
-// k = 1..2H, then Z_y(k j), k = 1..H with the 1/sqrt(YY) normalisation undone).
 // Maximum of a double over each 16-lane row, in every lane of the row.
 __device__ __forceinline__ double row_max_d(double v) {
   v = fmax(v, dpp_d<0xB1>(v));    // quad_perm [1, 0, 3, 2]
@@ -934,6 +932,8 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(H >= 8 ? 3 :
   }
 }
 
+// Writes the deconvolved sums of every pair (3H complex per pair: Z_w(k j),
+// k = 1..2H, then Z_y(k j), k = 1..H with the 1/sqrt(YY) normalisation undone).
 template <typename R>
 __global__ __launch_bounds__(64) void k_gather_sums(SolveArgs a, double* out) {
   const int lane = wave_lane();

@@ -42,26 +42,6 @@ __host__ __device__ inline constexpr int cayley_row(int K) { return (((K + 2) / 
 // Template products for the coefficients of MM: H per e = 1..2H (assemble_mu).
 __host__ __device__ inline constexpr int template_products(int H) { return 2 * H * H; }
 
-// Shared-memory size (bytes) of one wave's per-frequency working set.  The
-// Cayley-Horner buffers (4 (D+1) complex) alias the companion matrix, which is
-// only built after them.
-__host__ __device__ inline size_t solve_region_a(int H) {
-  const size_t D = 6 * H - 2;
-  const size_t mat = D * (D + 1), hor = 8 * (D + 1);
-  return ((mat > hor ? mat : hor) + 1) & ~(size_t)1;
-}
-__host__ __device__ inline size_t solve_lds_bytes(int H) {
-  const int K = 3 * H - 1, D = 2 * K, n = D;
-  size_t nd = solve_region_a(H);                    // Hessenberg matrix / Horner buffers
-  nd += 2 * (((size_t)n + 1) & ~(size_t)1);         // eigenvalues (re, im)
-  nd += 2 * (3 * H + 1);                            // Z
-  nd += 2 * (2 * H + 1);                            // mu
-  nd += 2 * (H + 1);                                // eta
-  nd += 2 * (K + 1);                                // r
-  nd += ((size_t)D + 2) & ~(size_t)1;               // f
-  nd += 2 * H;                                      // alpha
-  return nd * sizeof(double);
-}
 // Per-pair record in HBM passed between the assemble, root and score kernels
 // (doubles): r_d (d = 0..K, complex), mu_e (e = 0..2H, complex), eta_k and
 // Z_w(k) (k = 1..H, complex), meta (see the M_* slots), f_c (c = 0..D, the
