@@ -216,7 +216,9 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_train_rows(TrainArgs a) {
     for (int i = 0; i < kTileRows; ++i) s += of[i * kTileOutLd + tid];
     part[3 * W + tid] = s;
   }
-  // backward: gradient at the output of layer l - 1 from that of layer l
+  // backward: gradient at the output of layer l - 1 from that of layer l (rows past
+  // the batch stay zero also where a weight is not finite)
+  const int rows = (int)min((int64_t)kTileRows, a.B - row0);
 #pragma unroll 1
   for (int l = 3; l >= 1; --l) {
 #pragma unroll
@@ -231,7 +233,7 @@ __global__ __launch_bounds__(64 * kTileWaves) void k_train_rows(TrainArgs a) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const int r = 16 * i + 4 * (lane >> 4) + v;
-          const float x = bf16_positive(hh[l - 1][r * kTileLd + n]) ? acc[i][v] : 0.f;
+          const float x = r < rows && bf16_positive(hh[l - 1][r * kTileLd + n]) ? acc[i][v] : 0.f;
           cs += x;
           xa[r * kTileLd + n] = bf16_rne(x);
         }

@@ -1,6 +1,6 @@
 """Loss and gradients of a network whose outputs are not finite or nearly
 overflow: the row-tile kernel (width 256) and one GEMM per layer (width 48).
-Zero weights, so every output is its bias of the last layer."""
+Zero weights there, so every output is its bias of the last layer."""
 import numpy as np
 import pytest
 
@@ -58,3 +58,26 @@ def test_terms_do_not_overflow_before_they_are_divided(width):
     L, d = MO.chamfer_loss(np.tile(b4, (B, 1)).astype(np.float64), roots.astype(np.float64), nroots, lam=0.5)
     assert np.max(np.abs(loss / L - 1)) <= 1e-5
     assert np.max(np.abs(g / np.sum(d, axis=0) - 1)) <= 1e-4
+
+
+@pytest.mark.parametrize("width", [256, 48])
+@pytest.mark.parametrize("batch", [1, 5, 33])
+def test_rows_past_the_batch_do_not_meet_a_weight_that_is_not_finite(width, batch):
+    import torch
+    import paper_2101_12348_amd as F
+
+    # unit 3 of the first layer is off for every row of the batch and would be on for a
+    # row of zeros; the weight behind it is NaN: its gradients are zero
+    rng = np.random.default_rng(9)
+    w = (rng.standard_normal(F.mlp_param_count(DIN, width, DOUT)) / 16).astype(np.float32)
+    W1 = w[:width * DIN].reshape(width, DIN)
+    b1 = w[width * DIN:width * DIN + width]
+    W1[3], b1[3] = -1.0, 1.0
+    w[width * DIN + width + 7 * width + 3] = np.nan   # second layer, unit 7
+    net = F.Mlp(DIN, width, DOUT, weights=w)
+    X = torch.ones((batch, DIN), dtype=torch.bfloat16, device="cuda")
+    roots = torch.as_tensor(rng.uniform(0, 6, (batch, R)).astype(np.float32), device="cuda")
+    _, g = net.loss_grad(X, roots, torch.full((batch,), R, dtype=torch.int32, device="cuda"))
+    g = g.cpu().numpy()
+    assert g[width * DIN + 3] == 0.0
+    assert np.all(g[3 * DIN:4 * DIN] == 0.0)
