@@ -71,8 +71,6 @@ __device__ __forceinline__ int64_t find_segment(const int64_t* off, int64_t n, i
 // one-pass cancellation. It then fills the LcInfo and resets the ticket for the
 // next call.
 
-// Block-wide sums of v[0..NS) and minima of v[NS..NS+NM) in a fixed order
-// (wave shuffles, then the waves in turn); every thread receives the result.
 // The double of lane ^ O in a butterfly from 32 down: within a 16-lane row by DPP
 // (a rotation by 4 after the rotation by 8 meets lane ^ 4 or its equal lane ^ 12),
 // which a chain of nine values waits for a sixth as long as for an LDS permute.
@@ -94,6 +92,8 @@ __device__ __forceinline__ void butterfly_all(double* v) {
   if constexpr (O > 1) butterfly_all<NS, NM, O / 2>(v);
 }
 
+// Block-wide sums of v[0..NS) and minima of v[NS..NS+NM) in a fixed order
+// (wave butterflies, then the waves in turn); every thread receives the result.
 template <int NS, int NM>
 __device__ __forceinline__ void block_reduce(double* v) {
   constexpr int N = NS + NM, NW = kStatThreads / 64;

@@ -45,7 +45,8 @@ __host__ __device__ inline constexpr int template_products(int H) { return 2 * H
 // Per-pair record in HBM passed between the assemble, root and score kernels
 // (doubles): r_d (d = 0..K, complex), mu_e (e = 0..2H, complex), eta_k and
 // Z_w(k) (k = 1..H, complex), meta (see the M_* slots), f_c (c = 0..D, the
-// Cayley polynomial) and D root candidates theta (NaN = none).
+// Cayley polynomial) and D root candidates: phases theta (NaN = none), or up to H = 10
+// the keys of a pair's Newton roots (dir_from_key) while M_FALLBACK is 0.
 enum : int {
   M_PHI0 = 0,      // Cayley rotation phi0
   M_REF = 1,       // frac(f_j t_ref) in cycles
