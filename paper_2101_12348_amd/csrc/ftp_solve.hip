@@ -543,9 +543,10 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
                                                                                       const unsigned* list_n) {
   // On a list this is the last of the fallback tiers, whose waves take issue priority
   // over the side stream's scoring on a shared SIMD (the tiers are few, latency-bound
-  // waves on the step's critical path); without one it may be that scoring itself
-  // (H >= 11).
-  if (list) __builtin_amdgcn_s_setprio(2);
+  // waves on the step's critical path).  Above H = 10 it is that scoring as well, at
+  // the tiers' own priority: 2.68 ms for a periodogram at H = 13 (50 thousand
+  // frequencies) against 2.71 with the priority on lists only.
+  __builtin_amdgcn_s_setprio(2);
   extern __shared__ double sms[];
   const int lane = wave_lane();
   const int H = a.H, K = 3 * H - 1, D = 2 * K;
