@@ -862,7 +862,9 @@ __device__ __forceinline__ void newton_pair(const LearnArgs& L, const RecLayout&
 // (512 lightcurves at H = 4 37.5 ms at five, 36.9 at six; H = 10 the same), so the
 // launch shape picks it (4 takes the former).  Spilled registers at five / six: 6-8 /
 // 14-20 with sixteen lanes per chain or H <= 5, 20-28 / 32-53 with eight above.
-template <int H, int OCC, int G>
+// FEW: L.per frequencies per wavefront instead of one per group (the loop bounds and
+// strides as arguments cost a few spills, 0.5 % of the time).
+template <int H, int OCC, int G, bool FEW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void k_newton_sturm4(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
   constexpr int D = 6 * H - 2, RM = sturm_coefs(D, G);
@@ -873,7 +875,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(OCC))) void 
   const int half = lane >> 5, hl = lane & 31;
   double* fh = sml + 2 * FS * half;
   for (int k = D + 1 + hl; k <= DP; k += 32) fh[k] = fh[FS + k] = 0.0;
-  const int per = D < 32 ? L.per : 64 / G;   // frequencies per wavefront, even
+  const int per = FEW ? L.per : 64 / G;   // frequencies per wavefront, even
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < L.np; w0 += per * (int64_t)gridDim.x) {
     // this group's frequency (inactive: no turn, past the end, rejected lightcurve,
     // or P constant in theta_2)
@@ -942,7 +944,7 @@ __host__ __device__ inline size_t learn_lds_bytes(int H) {
   return (size_t)(2 * (newton_top(D) + 2)) * sizeof(double);   // f and its reversal
 }
 
-template <int NC>
+template <int NC, bool FEW>
 __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_newton_sturm(SolveArgs a, LearnArgs L) {
   extern __shared__ double sml[];
   const int lane = threadIdx.x & 63;
@@ -951,7 +953,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void k_
   const RecLayout RL(H);
   const unsigned long long below = (1ull << lane) - 1ull;
   unsigned long long iters_acc = 0, roots_acc = 0, fb_acc = 0;
-  const int per = NC > 1 ? L.per : 1;
+  const int per = FEW ? L.per : NC;
   for (int64_t w0 = per * (int64_t)blockIdx.x; w0 < L.np; w0 += per * (int64_t)gridDim.x) {
     // Sturm counts first: an ill-determined count (or fewer than the two real
     // roots every non-constant P has) sends the frequency on without Newton
@@ -1306,14 +1308,21 @@ static int newton_per(int64_t np, int nc, int step, int64_t waves) {
   return (int)std::min<int64_t>(nc, (per + step - 1) / step * step);
 }
 
+template <int H, int G, bool FEW>
+static void launch_newton_f(const SolveArgs& a, const LearnArgs& L, int waves, int occ, hipStream_t st, hipEvent_t done) {
+  const size_t lds = (size_t)4 * (newton_top(6 * H - 2) + 2) * sizeof(double);   // f and its reversal of two frequencies
+  const dim3 grid((unsigned)waves), block(64);
+  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6, G, FEW>), grid, block, lds, st, nullptr, done, 0, a, L);
+  else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5, G, FEW>), grid, block, lds, st, nullptr, done, 0, a, L);
+}
 template <int H, int G>
 static void launch_newton_g(const SolveArgs& a, LearnArgs L, int waves, int occ, int n_cu, hipStream_t st,
                             hipEvent_t done) {
-  const size_t lds = (size_t)4 * (newton_top(6 * H - 2) + 2) * sizeof(double);   // f and its reversal of two frequencies
-  const dim3 grid((unsigned)waves), block(64);
-  if (6 * H - 2 < 32) L.per = newton_per(L.np, 64 / G, 2, 8 * (int64_t)n_cu);
-  if (occ == 6) hipExtLaunchKernelGGL((k_newton_sturm4<H, 6, G>), grid, block, lds, st, nullptr, done, 0, a, L);
-  else hipExtLaunchKernelGGL((k_newton_sturm4<H, 5, G>), grid, block, lds, st, nullptr, done, 0, a, L);
+  if constexpr (6 * H - 2 < 32) {
+    L.per = newton_per(L.np, 64 / G, 2, 8 * (int64_t)n_cu);
+    if (L.per < 64 / G) return launch_newton_f<H, G, true>(a, L, waves, occ, st, done);
+  }
+  launch_newton_f<H, G, false>(a, L, waves, occ, st, done);
 }
 
 template <int H>
@@ -1338,14 +1347,12 @@ hipError_t launch_newton_sturm(const SolveArgs& a, LearnArgs L, int waves, int o
     FTP_NEWTON(6) FTP_NEWTON(7) FTP_NEWTON(8) FTP_NEWTON(9) FTP_NEWTON(10)
 #undef FTP_NEWTON
     default:
-      if (a.H == 11) {
-        hipExtLaunchKernelGGL(k_newton_sturm<1>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
-                              done, 0, a, L);
-      } else {
-        L.per = newton_per(L.np, 4, 1, 4 * (int64_t)n_cu);
-        hipExtLaunchKernelGGL(k_newton_sturm<4>, dim3((unsigned)waves), dim3(64), learn_lds_bytes(a.H), st, nullptr,
-                              done, 0, a, L);
-      }
+      const dim3 grid((unsigned)waves);
+      const size_t lds = learn_lds_bytes(a.H);
+      L.per = newton_per(L.np, 4, 1, 4 * (int64_t)n_cu);
+      if (a.H == 11) hipExtLaunchKernelGGL((k_newton_sturm<1, false>), grid, dim3(64), lds, st, nullptr, done, 0, a, L);
+      else if (L.per < 4) hipExtLaunchKernelGGL((k_newton_sturm<4, true>), grid, dim3(64), lds, st, nullptr, done, 0, a, L);
+      else hipExtLaunchKernelGGL((k_newton_sturm<4, false>), grid, dim3(64), lds, st, nullptr, done, 0, a, L);
   }
   return hipGetLastError();
 }

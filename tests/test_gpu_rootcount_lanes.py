@@ -30,7 +30,7 @@ def test_counts_and_solver_use_the_same_chains(H, n_f):
         sturm, real = plan.root_counts(sums, tref, ybar, yy, lc.df)
         torch.cuda.synchronize()
     names = {e.name for e in prof.events() if "ftp::" in e.name}
-    solver = _lanes(names, r"k_newton_sturm4<\d+, \d+, (\d+)>")
+    solver = _lanes(names, r"k_newton_sturm4<\d+, \d+, (\d+)\b")
     assert len(solver) == 1 and solver == _lanes(names, r"k_root_counts<(\d+), false>"), names
     # data of 200 observations leave few chains near their thresholds: one in a hundred refused, two
     # at most; and the first round settles most frequencies where the counts are trusted

@@ -18,7 +18,7 @@ def _builds(fn):
     with profile(activities=[ProfilerActivity.CPU, ProfilerActivity.CUDA]) as prof:
         fn()
         torch.cuda.synchronize()
-    return [int(m.group(1)) for e in prof.events() if (m := re.search(r"k_newton_sturm4<\d+, (\d+), \d+>", e.name))]
+    return [int(m.group(1)) for e in prof.events() if (m := re.search(r"k_newton_sturm4<\d+, (\d+), \d+\b", e.name))]
 
 
 def test_each_build_is_measured_once():
